@@ -64,9 +64,21 @@ typedef enum {
     SSE_ERR_UNSUPPORTED = 9 /* valid request that this library does not implement */
 } sse_status;
 
+/*
+ * Forms.  Sigma is computed in one of two forms, chosen per plan by sizes.  The
+ * spectral form, for all but short sums and small problems, takes the (q, w) sums
+ * as products of discrete Fourier transforms over the momenta and over blocks of
+ * energies, in binary64 arithmetic in every precision (a complex64 precision then
+ * names its storage); its rounding error is relative to the largest values of a
+ * block of energies.  The direct form takes the sums as they stand, in the
+ * arithmetic that the precision names.  It runs where the spectral form would not
+ * be faster, for a desc with tile_e or chunk_taps set, in a workspace too small
+ * for the other, and over again where the spectral form meets a value that is not
+ * finite.
+ */
 typedef enum {
     SSE_FP64 = 0,  /* complex128 storage, binary64 arithmetic throughout */
-    /* SSE_FP32 and SSE_BF16X3 (complex64 storage, the matrix cores): for each
+    /* SSE_FP32 and SSE_BF16X3 (complex64 storage; direct form on the matrix cores): for each
        neighbour b the tap sum over (qz, w) runs window by window -- one window
        is one qz row and one chunk of at most chunk_taps frequencies (all that
        fit the LDS window when chunk_taps = 0) -- with the tap products and the
@@ -93,8 +105,8 @@ typedef struct {
     int32_t Nw;    /* phonon frequencies, 1..128 */
     int32_t ncomp; /* 1, or 2 = lesser and greater stacked */
     int32_t prec;  /* sse_precision */
-    int32_t tile_e; /* energies per output tile; 0 = the library's default (the largest
-                       that fills a workgroup); clamped to [1, that default] */
+    int32_t tile_e; /* energies per output tile of the direct form; 0 = the library's default
+                       (the largest that fills a workgroup); clamped to [1, that default] */
     int32_t chunk_taps; /* at most this many frequencies per tap chunk (one staged G
                            window); 0 = as many as the window holds.  Under
                            SSE_FP32/SSE_BF16X3 it bounds the fp32 part of the tap sum;
@@ -121,8 +133,10 @@ typedef struct sse_plan_s *sse_plan_t;
 /*
  * Validate a problem and build a plan.  w_shift: host array [Nw] of energy
  * index shifts, |s_w| < NE (may be negative; need not be sorted).
- * *workspace_bytes receives the device workspace size every call with this
- * plan needs.  SSE_ERR_SHAPE if NA, Nkz, NE < 1, NB outside 1..50, Norb outside
+ * *workspace_bytes receives the device workspace size for every call with this
+ * plan, at most 8 GiB beyond what the direct form needs; a single-instance plan
+ * also takes a smaller one that holds the direct form's (256 bytes in binary64
+ * arithmetic).  SSE_ERR_SHAPE if NA, Nkz, NE < 1, NB outside 1..50, Norb outside
  * 1..30, N3D != 3, Nqz outside 1..Nkz, Nw outside 1..128, ncomp not 1 or 2, a
  * shift out of range, or a tensor larger than 2^62 elements.
  */
@@ -134,7 +148,8 @@ sse_status sse_plan(const sse_desc *desc, const int32_t *w_shift, sse_plan_t *pl
  * by one persistent kernel launch per component.  descs[t] and w_shift[t] as
  * in sse_plan; all instances must share Norb, N3D, ncomp, prec and alpha.
  * Each instance's tile shape is its desc's tile_e (an autotuner picks it per
- * size bucket).  The launch keeps a fixed grid of two workgroups per compute
+ * size bucket).  Instances in the spectral form run in launches of their own, as many
+ * together as fit the workspace; the persistent launch takes the others.  It keeps a fixed grid of two workgroups per compute
  * unit pulling tiles -- (instance, atom, kz, energy tile) -- from eight work
  * queues, one per XCD, each holding whole atoms (all kz and energy tiles of an
  * atom share G rows) ordered by decreasing tile cost; an empty queue's
@@ -160,14 +175,15 @@ sse_status sse_compute(sse_plan_t plan, const int32_t *neigh, const double *dH, 
  * sse_compute without a workspace argument, for callers that cannot allocate
  * device memory (code under stream capture, tight serving loops, harnesses
  * that forbid allocation).  Same arguments, result and statuses as
- * sse_compute, and the same kernels; the scratch those kernels need (the
- * status word and, for SSE_FP32/SSE_BF16X3, the MFMA fragments and the split
+ * sse_compute, and the same kernels (the direct form's if the spectral one needs
+ * more scratch than there is); the scratch those kernels need (the status word,
+ * the transforms or, for SSE_FP32/SSE_BF16X3, the MFMA fragments and the split
  * of G) lives in a static device array of SSE_NOALLOC_SCRATCH_BYTES on the
  * current device, whose address is looked up the first time the current device
  * calls this function.  The call allocates nothing (no hipMalloc, no pinned
  * host memory, no events): it enqueues the work on `stream`, which must belong
  * to the current device, copies the status word back and synchronizes the
- * stream.  SSE_ERR_UNSUPPORTED if the plan needs more scratch than the array
+ * stream.  SSE_ERR_UNSUPPORTED if the direct form needs more scratch than the array
  * holds (then use sse_compute), SSE_ERR_ARG for a batch plan or a NULL pointer.
  * Every call on one GPU shares that GPU's array: calls that overlap in time on
  * one GPU (from several threads or streams) race and must not be made.

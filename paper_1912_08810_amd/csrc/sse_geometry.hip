@@ -7,6 +7,7 @@
 
 #include "sse_internal.h"
 #include "sse_mfma.h"
+#include "sse_spectral.h"
 
 namespace sse {
 
@@ -171,6 +172,149 @@ PiGeom pi_geometry(int Norb, int NB, const int32_t *w_shift, int Nw)
                             (size_t)(pik::kWaves / 2) * 16 * gm.mtiles * 16 * ntn_of(gm.nbw) * 8);
     gm.ok = rmax >= 1 && gm.lds_bytes <= budget;
     return gm;
+}
+
+SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32_t *w_shift)
+{
+    SpecParams p{};
+    p.NA = d.NA;
+    p.NB = d.NB;
+    p.Norb = d.Norb;
+    p.NN = d.Norb * d.Norb;
+    p.Nkz = d.Nkz;
+    p.Nqz = d.Nqz;
+    p.NE = d.NE;
+    p.Nw = d.Nw;
+    p.ncomp = d.ncomp;
+    p.L = g.L;
+    p.V = g.V;
+    p.C = g.C;
+    p.logC = g.logC;
+    p.rowp = g.rowp;
+    p.npt = g.npt;
+    p.P = g.P;
+    p.npg = g.npg;
+    p.smin = g.smin;
+    p.smax = g.smax;
+    p.nblk = g.nblk;
+    p.na_cap = g.na;
+    p.antiherm = d.dt_antiherm;
+    p.g_elems = (int64_t)d.Nkz * d.NE * d.NA * p.NN;
+    p.d_elems = (int64_t)d.Nqz * d.Nw * d.NA * d.NB * kNF;
+    p.off_tw = (int64_t)g.off_tw;
+    p.off_dht = (int64_t)g.off_dht;
+    p.off_d = (int64_t)g.off_d;
+    p.off_g = (int64_t)g.off_g;
+    p.off_s = (int64_t)g.off_s;
+    p.alpha_re = d.alpha_re;
+    p.alpha_im = d.alpha_im;
+    for (int w = 0; w < d.Nw; ++w)
+        p.shift[w] = w_shift[w];
+    return p;
+}
+
+namespace {
+
+size_t up(size_t x) { return (x + speck::kAlign - 1) & ~(speck::kAlign - 1); }
+
+// Workspace layout for the most components, then energy blocks, then sandwich
+// atoms per pass that fit budget; false if an eighth of the atoms does not fit.
+bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
+{
+    const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
+    const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
+    const size_t tw = up(((size_t)g->L + (size_t)d.Nkz * d.Nkz) * 16);
+    const size_t fixed = tw + up((size_t)d.NA * d.NB * kN3D * NN * 8) + 4 * speck::kAlign + 4096;
+    for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
+        const size_t base = fixed + g->nc * db, per = 2 * g->nc * gb;
+        if (budget < base + (g->nc > 1 ? per : gb + gb / 8))
+            continue;
+        g->nb = (int)std::min<size_t>(g->nblk, std::max<size_t>(1, (budget - base) / per));
+        g->na = d.NA;
+        if (base + per > budget)  // one component, one block, some atoms
+            g->na = (int)std::max<size_t>(1, (budget - base - gb) / (NN * row));
+        g->off_tw = speck::kAlign;  // behind the non-finite flag
+        g->off_dht = g->off_tw + tw;
+        g->off_d = g->off_dht + up((size_t)d.NA * d.NB * kN3D * NN * 8);
+        g->off_g = g->off_d + up(g->nc * db);
+        g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
+        g->bytes = g->off_s + up((size_t)g->nc * g->nb * g->na * NN * row) + 4096;
+        return true;
+    }
+    return false;
+}
+
+}  // namespace
+
+SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift)
+{
+    static const int kSizes[][2] = {{4, 4}, {4, 6}, {4, 8}, {6, 8}, {8, 8}, {8, 9}, {8, 10},
+                                    {8, 12}, {10, 12}, {12, 12}, {10, 16}, {12, 16}, {16, 16}};
+    SpectralGeom best;
+    // an explicit tile shape asks for the direct kernel that has tiles
+    if (d.Norb > speck::kMaxNorb || d.Nkz > 64 || d.tile_e > 0 || d.chunk_taps > 0)
+        return best;
+    const int64_t NN = (int64_t)d.Norb * d.Norb;
+    if (d.NA * NN > (1 << 28) || (int64_t)d.NA * d.NB > (1 << 28))
+        return best;
+    int smin = w_shift[0], smax = w_shift[0];
+    for (int w = 0; w < d.Nw; ++w) {
+        smin = std::min(smin, w_shift[w]);
+        smax = std::max(smax, w_shift[w]);
+    }
+    const bool c64 = d.prec != SSE_FP64;
+    double best_cost = 0.0;
+    for (const auto &sz : kSizes) {
+        SpectralGeom g;
+        g.r1 = sz[0];
+        g.r2 = sz[1];
+        g.L = g.r1 * g.r2;
+        g.smin = smin;
+        g.smax = smax;
+        g.V = g.L - (smax - smin);
+        if (g.V < 1)
+            continue;
+        g.nblk = (d.NE + g.V - 1) / g.V;
+        g.npt = d.Nkz * g.L;
+        g.P = speck::kSandBlock / d.Norb;
+        g.npg = (g.npt + g.P - 1) / g.P;
+        g.sand_lds = (size_t)NN * g.P * 16 + kN3D * NN * 8;
+        for (g.logC = 1; g.logC <= 3; ++g.logC) {
+            g.C = 1 << g.logC;
+            // rows of one momentum and channel start 16 / C sixteen-byte banks apart
+            g.rowp = g.r1 * (g.r2 + 1);
+            while (g.rowp % 16 != 16 / g.C)
+                ++g.rowp;
+            g.fft_lds = (size_t)d.Nkz * g.C * g.rowp * 16;
+            if (g.fft_lds > speck::kLdsOne)
+                continue;
+            const int items = d.Nkz * g.C * g.r2;
+            g.fft_threads = std::min(speck::kFftBlock, (items + 63) / 64 * 64);
+            if (!spectral_layout(d, speck::kSoftBytes, &g) && !spectral_layout(d, speck::kHardBytes, &g))
+                continue;
+            // transform points computed, weighted by what pieces of under 64 bytes and
+            // one workgroup per CU cost the transforms
+            const int piece = g.C * (c64 ? 8 : 16);
+            const double cost = (double)g.nblk * g.L * (1.0 + (piece < 64 ? 0.15 : 0.0) + (piece < 32 ? 0.3 : 0.0) +
+                                                        (g.fft_lds > speck::kLdsTwo ? 0.1 : 0.0));
+            if (best_cost == 0.0 || cost < best_cost) {
+                best_cost = cost;
+                best = g;
+                best.on = true;
+            }
+        }
+    }
+    if (!best.on)
+        return best;
+    // Estimated microseconds of the two forms
+    const double pts = (double)d.Nkz * best.nblk * best.L * d.NA * NN;
+    const double spec = 25.0 + d.ncomp * (pts * d.NB * (24.0 * d.Norb + 72.0) / 45e6 + pts * 64.0 / 3.5e6);
+    const double flops = (double)d.Nkz * d.NE * d.NA * NN * d.NB *
+                         ((d.dt_antiherm ? 36.0 : 72.0) * d.Nqz * d.Nw + 48.0 * d.Norb);
+    const bool mfma = d.prec == SSE_FP32 || d.prec == SSE_BF16X3;
+    const double rate = d.prec == SSE_BF16X3 ? 100e6 : d.prec == SSE_FP32 ? 50e6 : 55e6;
+    const double direct = 10.0 + d.ncomp * std::max(flops / rate, 5.0 * d.NB * d.Nqz);
+    return spec < direct && (!mfma || flops > 3e10) ? best : SpectralGeom();
 }
 
 }  // namespace sse

@@ -82,6 +82,7 @@ struct BatchLaunch {
     unsigned long long *counters;  // kQueues pull counters (workspace, cleared per launch)
     int32_t qbeg[kQueues + 1];
     int64_t qcount[kQueues];
+    int32_t n;                     // instances (fp64_redo_batch_launch)
     int32_t nkz[kMaxBatch];
     TensorPtrs ptr[kMaxBatch];
 };
@@ -284,6 +285,11 @@ TileGeom fp64_geometry(int Norb, int NE, const TapTable &taps_unchunked, int te_
                        int chunk_cap, TapTable *taps_out);
 // ah: D~ anti-Hermitian per 3 x 3 block (only i <= j read; half the tap FMAs).
 hipError_t fp64_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, hipStream_t s);
+// The same sums where *flag is not zero, nothing otherwise: a fixed grid that walks the tiles.
+hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes,
+                            const uint32_t *flag, hipStream_t s);
+// The same over the bl.n instances of a batch (bl.params, bl.ptr), the flag of each at its ptr.aux.
+hipError_t fp64_redo_batch_launch(const BatchLaunch &bl, bool c64, bool ah, size_t lds_bytes, hipStream_t s);
 hipError_t fp64_persistent_launch(const BatchLaunch &bl, bool c64, bool ah, int grid,
                                   size_t lds_bytes, hipStream_t s);
 

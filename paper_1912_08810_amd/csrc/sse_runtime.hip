@@ -16,6 +16,7 @@
 
 #include "sse_internal.h"
 #include "sse_mfma.h"
+#include "sse_spectral.h"
 
 using namespace sse;
 
@@ -54,6 +55,9 @@ struct Instance {
     TileGeom geom;
     size_t afrag_bytes = 0;  // MFMA path: workspace for the A fragments (+ split G, bf16x3)
     int32_t shift[kMaxTaps] = {};  // the caller's shift table, in frequency order
+    SpectralGeom spec;  // spectral form, if it is the better one
+    TapTable redo_taps;  // binary64 direct kernel behind the spectral form: its tiles
+    TileGeom redo_geom;
 };
 
 constexpr size_t kStatusBytes = 256;  // status word region at the start of the workspace
@@ -63,7 +67,21 @@ constexpr size_t kStatusBytes = 256;  // status word region at the start of the 
 struct sse_plan_s {
     std::vector<Instance> inst;
     size_t ws_bytes = kStatusBytes;
+    size_t direct_bytes = kStatusBytes;  // what the direct kernels alone need (single plans)
     bool batch = false;
+    std::vector<int> direct;    // batch plans: instances of the persistent launch, in order
+    // spectral instances: waves that share the workspace region at spec_off; a wave is
+    // one instance of several passes, or instances of one pass each, done together
+    struct Wave {
+        std::vector<int> inst;
+        std::vector<size_t> off;       // workspace offset of each
+        std::vector<SpecParams> hp;
+        SpecParams *d_params = nullptr;  // device tables, for waves of several
+        Fp64Params *d_redo = nullptr;
+        size_t redo_lds = 0;
+    };
+    std::vector<Wave> waves;
+    size_t spec_off = 0;
     // ---- batch plans: device tables, built at the first submission
     std::once_flag tables_once;
     hipError_t tables_err = hipSuccess;
@@ -82,6 +100,10 @@ struct sse_plan_s {
         (void)hipFree(d_chunk_inst);
         (void)hipFree(d_chunk_atom);
         (void)hipFree(d_chunk_start);
+        for (Wave &w : waves) {
+            (void)hipFree(w.d_params);
+            (void)hipFree(w.d_redo);
+        }
     }
 };
 
@@ -192,6 +214,10 @@ sse_status build_instance(const sse_desc *d, const int32_t *w_shift, Instance *o
     const int64_t nwg = (int64_t)out->geom.n_etiles * d->Nkz * d->NA;
     if (nwg > 0x7fffffffLL)
         return fail(SSE_ERR_SHAPE, "sse_plan: %lld tiles exceed one launch", (long long)nwg);
+    if (spectral_sigma_launch)
+        out->spec = spectral_geometry(*d, w_shift);
+    if (out->spec.on)
+        out->redo_geom = fp64_geometry(d->Norb, d->NE, t, 0, 0, &out->redo_taps);
     return SSE_OK;
 }
 
@@ -199,6 +225,19 @@ size_t elem_bytes(int prec) { return prec == SSE_FP64 ? 16 : 8; }
 bool fp64_arith(int prec) { return prec == SSE_FP64 || prec == SSE_FP64C64; }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+Fp64Params fp64_params(const sse_desc &d, const TileGeom &geom, const TapTable &taps);
+
+// The spectral form of one instance, every component, then the direct binary64
+// kernel that takes over if the status word's non-finite flag was raised.
+sse_status enqueue_spectral(const Instance &I, const sse_args &a, uint32_t *dstatus, bool clear, void *wsfree,
+                            hipStream_t s)
+{
+    hipError_t e = spectral_sigma_launch(I.d, I.spec, I.shift, a, dstatus, clear,
+                                         fp64_params(I.d, I.redo_geom, I.redo_taps), I.redo_geom.lds_bytes,
+                                         wsfree, s);
+    return e == hipSuccess ? SSE_OK : hip_fail(e, "spectral kernel launch");
+}
 
 sse_status enqueue_instance(const Instance &I, const sse_args &a, uint32_t *dstatus, void *wsfree,
                             hipStream_t s)
@@ -295,9 +334,8 @@ sse_status enqueue_instance(const Instance &I, const sse_args &a, uint32_t *dsta
 }
 
 // Per-instance static launch parameters (sizes, taps, geometry; no pointers).
-Fp64Params fp64_params(const Instance &I)
+Fp64Params fp64_params(const sse_desc &d, const TileGeom &geom, const TapTable &taps)
 {
-    const sse_desc &d = I.d;
     Fp64Params p{};
     p.NA = d.NA;
     p.NB = d.NB;
@@ -307,13 +345,13 @@ Fp64Params fp64_params(const Instance &I)
     p.Nqz = d.Nqz;
     p.NE = d.NE;
     p.Nw = d.Nw;
-    p.TE = I.geom.TE;
-    p.n_etiles = I.geom.n_etiles;
-    p.n_wg = (int64_t)I.geom.n_etiles * d.Nkz * d.NA;
-    p.lds_win = I.geom.lds_win;
+    p.TE = geom.TE;
+    p.n_etiles = geom.n_etiles;
+    p.n_wg = (int64_t)geom.n_etiles * d.Nkz * d.NA;
+    p.lds_win = geom.lds_win;
     p.alpha_re = d.alpha_re;
     p.alpha_im = d.alpha_im;
-    p.taps = I.taps;
+    p.taps = taps;
     fill_tap_pairs(p);
     return p;
 }
@@ -341,17 +379,38 @@ MfmaParams mfma_params(const Instance &I)
     return p;
 }
 
-// Work queues of a batch plan: atoms of all instances, instances in order of
+// Work queues of a batch plan: atoms of all direct instances, instances in order of
 // decreasing tile cost, dealt round-robin to the eight queues.
 hipError_t build_batch_tables(sse_plan_s *P)
 {
-    const int n = (int)P->inst.size();
+    for (sse_plan_s::Wave &w : P->waves) {
+        if (w.inst.size() < 2)
+            continue;
+        std::vector<Fp64Params> redo;
+        for (int t : w.inst) {
+            const Instance &I = P->inst[t];
+            w.hp.push_back(spectral_params(I.d, I.spec, I.shift));
+            redo.push_back(fp64_params(I.d, I.redo_geom, I.redo_taps));
+            w.redo_lds = std::max(w.redo_lds, I.redo_geom.lds_bytes);
+        }
+        const size_t np = w.hp.size() * sizeof(SpecParams), nr = redo.size() * sizeof(Fp64Params);
+        hipError_t e;
+        if ((e = hipMalloc((void **)&w.d_params, np)) != hipSuccess ||
+            (e = hipMalloc((void **)&w.d_redo, nr)) != hipSuccess ||
+            (e = hipMemcpy(w.d_params, w.hp.data(), np, hipMemcpyHostToDevice)) != hipSuccess ||
+            (e = hipMemcpy(w.d_redo, redo.data(), nr, hipMemcpyHostToDevice)) != hipSuccess)
+            return e;
+    }
+    const int n = (int)P->direct.size();
+    if (n == 0)
+        return hipSuccess;
     std::vector<int> order(n);
     for (int t = 0; t < n; ++t)
         order[t] = t;
+    auto inst = [&](int t) -> const Instance & { return P->inst[P->direct[t]]; };
     auto cost = [&](int t) {
-        const sse_desc &d = P->inst[t].d;
-        return (double)d.NB * d.Nqz * d.Nw * P->inst[t].geom.TE;
+        const sse_desc &d = inst(t).d;
+        return (double)d.NB * d.Nqz * d.Nw * inst(t).geom.TE;
     };
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost(x) > cost(y); });
     std::vector<std::vector<int32_t>> qi(kQueues), qa(kQueues);
@@ -359,7 +418,7 @@ hipError_t build_batch_tables(sse_plan_s *P)
     std::vector<int64_t> qtot(kQueues, 0);
     int64_t c = 0;
     for (int t : order) {
-        const Instance &I = P->inst[t];
+        const Instance &I = inst(t);
         const int64_t tiles = (int64_t)I.d.Nkz * I.geom.n_etiles;
         for (int a = 0; a < I.d.NA; ++a, ++c) {
             const int x = (int)(c % kQueues);
@@ -384,10 +443,10 @@ hipError_t build_batch_tables(sse_plan_s *P)
     std::vector<unsigned char> params(psz * n);
     for (int t = 0; t < n; ++t) {
         if (fp64) {
-            Fp64Params fp = fp64_params(P->inst[t]);
+            Fp64Params fp = fp64_params(inst(t).d, inst(t).geom, inst(t).taps);
             memcpy(params.data() + psz * t, &fp, psz);
         } else {
-            MfmaParams mp = mfma_params(P->inst[t]);
+            MfmaParams mp = mfma_params(inst(t));
             memcpy(params.data() + psz * t, &mp, psz);
         }
     }
@@ -438,9 +497,32 @@ sse_status enqueue_batch(sse_plan_s *P, const sse_args *args, char *ws, uint32_t
         if (e != hipSuccess)
             return hip_fail(e, "validate_neigh launch");
     }
+    for (const sse_plan_s::Wave &w : P->waves) {
+        if (w.inst.size() == 1) {
+            const int t = w.inst[0];
+            sse_status st = enqueue_spectral(P->inst[t], args[t], dstatus, false, ws + P->spec_off, s);
+            if (st != SSE_OK)
+                return st;
+            continue;
+        }
+        const sse_desc *dp[kMaxBatch];
+        const SpectralGeom *gp[kMaxBatch];
+        const sse_args *ap[kMaxBatch];
+        const int nw = (int)w.inst.size();
+        for (int i = 0; i < nw; ++i) {
+            dp[i] = &P->inst[w.inst[i]].d;
+            gp[i] = &P->inst[w.inst[i]].spec;
+            ap[i] = &args[w.inst[i]];
+        }
+        e = spectral_batch_launch(nw, dp, gp, ap, w.off.data(), w.hp.data(), w.d_params, w.d_redo, w.redo_lds,
+                                  dstatus, ws + P->spec_off, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "spectral batch launch");
+    }
     unsigned long long *counters = (unsigned long long *)(ws + kStatusBytes);
     const size_t eb = elem_bytes(d0.prec);
-    for (int c = 0; c < d0.ncomp; ++c) {
+    const int nd = (int)P->direct.size();
+    for (int c = 0; c < d0.ncomp && nd > 0; ++c) {
         BatchLaunch bl{};
         bl.params = P->d_params;
         bl.chunk_inst = P->d_chunk_inst;
@@ -456,21 +538,22 @@ sse_status enqueue_batch(sse_plan_s *P, const sse_args *args, char *ws, uint32_t
         void *split_out[kMaxBatch];
         int64_t split_n[kMaxBatch];
         int nsplit = 0;
-        for (int t = 0; t < n; ++t) {
-            const sse_desc &d = P->inst[t].d;
+        for (int t = 0; t < nd; ++t) {
+            const int it = P->direct[t];
+            const sse_desc &d = P->inst[it].d;
             const size_t NN = (size_t)d.Norb * d.Norb;
             const size_t g_elems = (size_t)d.Nkz * d.NE * d.NA * NN;
             const size_t d_elems = (size_t)d.Nqz * d.Nw * d.NA * d.NB * kNF;
             bl.nkz[t] = d.Nkz;
-            bl.ptr[t].neigh = args[t].neigh;
-            bl.ptr[t].dH = args[t].dH;
-            bl.ptr[t].G = (const char *)args[t].G + c * g_elems * eb;
-            bl.ptr[t].D = (const char *)args[t].Dt + c * d_elems * eb;
-            bl.ptr[t].Sigma = (char *)args[t].Sigma + c * g_elems * eb;
-            bl.ptr[t].aux = ws + P->afrag_off[t];
+            bl.ptr[t].neigh = args[it].neigh;
+            bl.ptr[t].dH = args[it].dH;
+            bl.ptr[t].G = (const char *)args[it].G + c * g_elems * eb;
+            bl.ptr[t].D = (const char *)args[it].Dt + c * d_elems * eb;
+            bl.ptr[t].Sigma = (char *)args[it].Sigma + c * g_elems * eb;
+            bl.ptr[t].aux = ws + P->afrag_off[it];
             if (d.prec == SSE_BF16X3) {
-                char *split = ws + P->afrag_off[t] +
-                              mfma_split_offset(d.prec, d.NA, d.NB, d.Nqz, P->inst[t].groups);
+                char *split = ws + P->afrag_off[it] +
+                              mfma_split_offset(d.prec, d.NA, d.NB, d.Nqz, P->inst[it].groups);
                 split_in[nsplit] = (const float2 *)bl.ptr[t].G;
                 split_out[nsplit] = split;
                 split_n[nsplit] = (int64_t)g_elems;
@@ -485,7 +568,7 @@ sse_status enqueue_batch(sse_plan_s *P, const sse_args *args, char *ws, uint32_t
         }
         if (!fp64_arith(d0.prec)) {
             // every instance's A fragments in one launch
-            e = mfma_prep_batch_launch(d0.prec, bl, n, s);
+            e = mfma_prep_batch_launch(d0.prec, bl, nd, s);
             if (e != hipSuccess)
                 return hip_fail(e, "MFMA prep launch");
         }
@@ -524,7 +607,8 @@ sse_status sse_plan(const sse_desc *desc, const int32_t *w_shift, sse_plan_t *pl
         delete p;
         return st;
     }
-    p->ws_bytes = kStatusBytes + align256(p->inst[0].afrag_bytes);
+    p->direct_bytes = kStatusBytes + align256(p->inst[0].afrag_bytes);
+    p->ws_bytes = std::max(p->direct_bytes, kStatusBytes + align256(p->inst[0].spec.bytes));
     *plan = p;
     if (workspace_bytes)
         *workspace_bytes = p->ws_bytes;
@@ -545,7 +629,8 @@ sse_status sse_plan_batch(const sse_desc *descs, const int32_t *const *w_shift, 
     p->batch = true;
     p->inst.resize(n);
     p->afrag_off.resize(n);
-    size_t ws = 2 * kStatusBytes;  // status word, then the queue counters
+    size_t ws = 2 * kStatusBytes, spec = 0, used = 0;  // status word, then the queue counters
+    int open = -1;  // the wave that takes more instances
     for (int t = 0; t < n; ++t) {
         const sse_desc &d0 = descs[0], &dt = descs[t];
         if (dt.Norb != d0.Norb || dt.ncomp != d0.ncomp || dt.prec != d0.prec ||
@@ -560,11 +645,29 @@ sse_status sse_plan_batch(const sse_desc *descs, const int32_t *const *w_shift, 
             delete p;
             return st;
         }
+        if (const SpectralGeom &g = p->inst[t].spec; g.on) {
+            const bool one = g.nc == dt.ncomp && g.nb == g.nblk && g.na == dt.NA;
+            const size_t bytes = align256(g.bytes);
+            const bool join = one && open >= 0 && used + bytes <= speck::kSoftBytes;
+            if (!join) {
+                used = 0;
+                p->waves.emplace_back();
+            }
+            sse_plan_s::Wave &w = p->waves.back();
+            w.inst.push_back(t);
+            w.off.push_back(used);
+            used += bytes;
+            spec = std::max(spec, used);
+            open = one ? (int)p->waves.size() - 1 : -1;
+            continue;
+        }
+        p->direct.push_back(t);
         p->afrag_off[t] = ws;
         ws += align256(p->inst[t].afrag_bytes);
         p->lds_bytes = std::max(p->lds_bytes, p->inst[t].geom.lds_bytes);
     }
-    p->ws_bytes = ws;
+    p->spec_off = ws;
+    p->ws_bytes = ws + spec;
     *plan = p;
     if (workspace_bytes)
         *workspace_bytes = p->ws_bytes;
@@ -704,7 +807,9 @@ sse_status sse_submit(sse_plan_t plan, const sse_args *args, void *workspace,
 {
     if (!plan || !args || !ticket)
         return fail(SSE_ERR_ARG, "sse_submit: NULL plan, args or ticket");
-    if (!workspace || workspace_bytes < plan->ws_bytes)
+    // a single plan's workspace may be the direct kernels' alone: then they run
+    const size_t least = plan->batch ? plan->ws_bytes : plan->direct_bytes;
+    if (!workspace || workspace_bytes < least)
         return fail(SSE_ERR_ARG, "sse_submit: workspace of %zu bytes needed", plan->ws_bytes);
     for (size_t t = 0; t < plan->inst.size(); ++t) {
         const sse_args &a = args[t];
@@ -717,13 +822,16 @@ sse_status sse_submit(sse_plan_t plan, const sse_args *args, void *workspace,
     if (st != SSE_OK)
         return st;
     uint32_t *dstatus = (uint32_t *)workspace;
-    hipError_t e = launch_clear_status(dstatus, s);
+    const bool spectral = !plan->batch && plan->inst[0].spec.on && workspace_bytes >= plan->ws_bytes;
+    hipError_t e = spectral ? hipSuccess : launch_clear_status(dstatus, s);
     if (e != hipSuccess) {
         ticket_release(tk);
         return hip_fail(e, "clear_status launch");
     }
     if (plan->batch)
         st = enqueue_batch(plan, args, (char *)workspace, dstatus, s);
+    else if (spectral)
+        st = enqueue_spectral(plan->inst[0], args[0], dstatus, true, (char *)workspace + kStatusBytes, s);
     else
         st = enqueue_instance(plan->inst[0], args[0], dstatus, (char *)workspace + kStatusBytes, s);
     if (st != SSE_OK) {
@@ -846,22 +954,24 @@ sse_status sse_compute_noalloc(sse_plan_t plan, const int32_t *neigh, const doub
         return fail(SSE_ERR_ARG, "sse_compute_noalloc: needs a single-instance plan");
     if (!neigh || !dH || !G || !Dt || !Sigma)
         return fail(SSE_ERR_ARG, "sse_compute_noalloc: NULL tensor pointer");
-    if (plan->ws_bytes > (size_t)SSE_NOALLOC_SCRATCH_BYTES)
+    if (plan->direct_bytes > (size_t)SSE_NOALLOC_SCRATCH_BYTES)
         return fail(SSE_ERR_UNSUPPORTED,
                     "sse_compute_noalloc: the plan needs %zu bytes of scratch, the static scratch "
                     "holds %zu (use sse_compute with a workspace)",
-                    plan->ws_bytes, (size_t)SSE_NOALLOC_SCRATCH_BYTES);
+                    plan->direct_bytes, (size_t)SSE_NOALLOC_SCRATCH_BYTES);
     void *ws = nullptr;
     sse_status st = scratch_for_current_device(&ws);
     if (st != SSE_OK)
         return st;
     hipStream_t s = (hipStream_t)stream;
     uint32_t *dstatus = (uint32_t *)ws;
-    hipError_t e = launch_clear_status(dstatus, s);
+    const bool spectral = plan->inst[0].spec.on && plan->ws_bytes <= (size_t)SSE_NOALLOC_SCRATCH_BYTES;
+    hipError_t e = spectral ? hipSuccess : launch_clear_status(dstatus, s);
     if (e != hipSuccess)
         return hip_fail(e, "clear_status launch");
     sse_args a{neigh, dH, G, Dt, Sigma};
-    st = enqueue_instance(plan->inst[0], a, dstatus, (char *)ws + kStatusBytes, s);
+    st = spectral ? enqueue_spectral(plan->inst[0], a, dstatus, true, (char *)ws + kStatusBytes, s)
+                  : enqueue_instance(plan->inst[0], a, dstatus, (char *)ws + kStatusBytes, s);
     if (st != SSE_OK)
         return st;
     uint32_t hs = 0xffffffffu;

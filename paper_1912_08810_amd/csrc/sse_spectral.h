@@ -1,0 +1,121 @@
+// sse_spectral.h -- declarations of the spectral form of the self-energies: the
+// (qz, w) sums of Eq. (3) are a cyclic convolution over the momenta and a linear
+// one over the energies, so they are taken as products of discrete Fourier
+// transforms (overlap-save blocks of L energies), all in binary64.
+#pragma once
+
+#include "sse_internal.h"
+
+namespace sse {
+
+namespace speck {
+constexpr int kSandBlock = 256;     // threads of the sandwich kernel
+constexpr int kFftBlock = 512;      // most threads of a transform kernel
+constexpr size_t kLdsTwo = 79 * 1024;   // LDS of a workgroup when two share a CU
+constexpr size_t kLdsOne = 158 * 1024;  // LDS of a workgroup alone on a CU
+constexpr int kMaxNorb = 16;        // orbitals that the sandwich kernel is built for
+constexpr size_t kAlign = 256;
+// Workspace: what a pass may hold beside its D~ and one energy block of G (soft),
+// and the most a plan asks for (hard; above it the direct kernels run).
+constexpr size_t kSoftBytes = (size_t)5 << 30;
+constexpr size_t kHardBytes = (size_t)8 << 30;
+}  // namespace speck
+
+// Geometry and workspace layout of the spectral form of one instance.
+struct SpectralGeom {
+    bool on = false;
+    int L = 0, r1 = 0, r2 = 0;   // energies per transform, L = r1 r2
+    int V = 0, nblk = 0;         // output energies per block, blocks
+    int C = 0, logC = 0;         // channels (orbital pairs of atoms) per transform workgroup
+    int rowp = 0;                // LDS stride of one (momentum, channel) row, complex values
+    int fft_threads = 0;
+    size_t fft_lds = 0;
+    int smin = 0, smax = 0;
+    int npt = 0;                 // transform points per block: Nkz L
+    int P = 0, npg = 0;          // points per sandwich workgroup, groups of them
+    size_t sand_lds = 0;
+    // one pass holds nc components, nb energy blocks, and the sandwich's output for na atoms
+    int nc = 0, nb = 0, na = 0;
+    size_t off_tw = 256, off_dht = 0, off_d = 0, off_g = 0, off_s = 0, bytes = 0;
+};
+
+// Sizes, tables and workspace layout of one instance, as the kernels take them.
+struct SpecParams {
+    int32_t NA, NB, Norb, NN, Nkz, Nqz, NE, Nw, ncomp;
+    int32_t L, V, C, logC, rowp, npt, P, npg, smin, smax, nblk;
+    int32_t na_cap;             // atoms that the sandwich's output has room for
+    int32_t antiherm;
+    int64_t g_elems, d_elems;   // one component of G and of D~
+    int64_t off_tw, off_dht, off_d, off_g, off_s;
+    double alpha_re, alpha_im;
+    int32_t shift[kMaxTaps];    // the caller's shifts, in frequency order
+};
+
+// What one call works on: its tensors (of the pass's first component) and workspace.
+// Workspace: the non-finite flag, then
+//   tw   [L] exp(-2 pi i j / L), then [Nkz][Nkz] exp(-2 pi i k k' / Nkz)
+//   dht  [NA][NB][3][n][n'] = dH[a, b, j][n'][n]
+//   Dh   [components][NA][NB][9][npt]
+//   Gh   [components][blocks][NA NN][npt]
+//   Sh   [components][blocks][na_cap NN][npt]
+struct SpecPtrs {
+    const int32_t *neigh;
+    const double *dH;
+    const void *G, *D;
+    void *Sigma;
+    char *ws;
+};
+
+// The part of the work that one pass does: energy blocks [blk0, blk0 + nb), atoms
+// [a0, a0 + na) of the sandwich's output (components: the grid's y extent).
+struct SpecPass {
+    int32_t blk0, nb, a0, na;
+};
+
+struct SpecOne {
+    SpecParams p;
+    SpecPtrs t;
+    SpecPass s;
+    uint32_t *status;
+    int32_t clear;
+};
+
+// Instances of a batch in one launch: instance i (params[idx[i]]) has workgroups
+// [start[i], start[i + 1]); each is done in one pass.
+struct SpecMany {
+    const SpecParams *params;
+    uint32_t *status;
+    int32_t n;
+    int32_t clear;
+    int32_t start[kMaxBatch + 1];
+    uint8_t idx[kMaxBatch];
+    SpecPtrs t[kMaxBatch];
+};
+
+// Chooses L, the channels per workgroup and the workspace; g.on says whether the
+// spectral form is the better one for this problem (host, sse_geometry.hip).
+SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift);
+
+SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32_t *w_shift);
+
+// Sigma of every component (sse_spectral.hip), then the direct kernel (redo: its
+// sizes and taps) where the non-finite flag asks for it.  clear: the call also
+// clears the status word.  Weak: a build of the host runtime alone (its CPU test)
+// has no kernels to launch, and runs the direct launchers.
+__attribute__((weak)) hipError_t spectral_sigma_launch(const sse_desc &d, const SpectralGeom &g,
+                                                       const int32_t *w_shift, const sse_args &a,
+                                                       uint32_t *status, bool clear,
+                                                       const Fp64Params &redo, size_t redo_lds,
+                                                       void *ws, hipStream_t s);
+
+// The instances of a batch that one pass each can do, together: geom[i], args and
+// workspace offset of each; hp are their parameters, params and redo device tables of
+// the same n instances.
+__attribute__((weak)) hipError_t spectral_batch_launch(int n, const sse_desc *const *d,
+                                                       const SpectralGeom *const *g, const sse_args *const *a,
+                                                       const size_t *ws_off, const SpecParams *hp,
+                                                       const SpecParams *params,
+                                                       const Fp64Params *redo, size_t redo_lds,
+                                                       uint32_t *status, char *ws, hipStream_t s);
+
+}  // namespace sse

@@ -1,0 +1,62 @@
+// spectral_geometry over problem sizes and shift tables: every energy is an output
+// of exactly one block, the transforms' rows and the sandwich's points fit their LDS,
+// and the workspace regions of a pass follow each other within the plan's bytes.
+#include <cstdio>
+#include <vector>
+
+#include "sse_spectral.h"
+
+using namespace sse;
+
+static int fails = 0, on = 0, total = 0;
+#define NEED(c) do { if (!(c)) { printf("line %d: NA=%d NB=%d Norb=%d Nkz=%d NE=%d Nw=%d: %s\n", __LINE__, d.NA, d.NB, d.Norb, d.Nkz, d.NE, d.Nw, #c); ++fails; } } while (0)
+
+int main()
+{
+    for (int prec : {0, 1, 2, 3})
+    for (int ncomp : {1, 2})
+    for (int NA : {1, 7, 64, 1024, 20000})
+    for (int NB : {1, 4, 50})
+    for (int Norb : {1, 3, 10, 13, 16, 17, 30})
+    for (int Nkz : {1, 3, 7, 21, 64, 70})
+    for (int NE : {1, 9, 64, 399, 1000})
+    for (int Nw : {1, 8, 40, 128})
+    for (int step : {1, -2, 7}) {
+        sse_desc d{};
+        d.NA = NA; d.NB = NB; d.Norb = Norb; d.N3D = 3; d.Nkz = Nkz; d.Nqz = (Nkz + 1) / 2;
+        d.NE = NE; d.Nw = Nw; d.ncomp = ncomp; d.prec = prec;
+        std::vector<int32_t> s(Nw);
+        for (int w = 0; w < Nw; ++w)
+            s[w] = NE > 1 ? step * w % (NE - 1) : 0;
+        SpectralGeom g = spectral_geometry(d, s.data());
+        ++total;
+        NEED(g.on || g.bytes == 0);
+        if (!g.on)
+            continue;
+        ++on;
+        const size_t NN = (size_t)Norb * Norb, row = (size_t)g.npt * 16;
+        NEED(Norb <= speck::kMaxNorb && g.L == g.r1 * g.r2 && g.L <= 256 && g.npt == Nkz * g.L);
+        NEED(g.V == g.L - (g.smax - g.smin) && g.V >= 1);
+        NEED(g.V * g.nblk >= NE && g.V * (g.nblk - 1) < NE);
+        for (int w = 0; w < Nw; ++w)
+            NEED(g.smax - s[w] >= 0 && g.smax - s[w] + g.V <= g.L);
+        NEED(g.C == 1 << g.logC && g.rowp >= (g.r1 - 1) * (g.r2 + 1) + g.r2);
+        NEED((size_t)Nkz * g.C * g.rowp * 16 == g.fft_lds && g.fft_lds <= speck::kLdsOne);
+        NEED(g.fft_threads % 64 == 0 && g.fft_threads >= 64 && g.fft_threads <= speck::kFftBlock);
+        NEED(g.P == speck::kSandBlock / Norb && g.P * g.npg >= g.npt && g.P * (g.npg - 1) < g.npt);
+        NEED(g.sand_lds == NN * g.P * 16 + 3 * NN * 8 && g.sand_lds <= speck::kLdsOne);
+        NEED(g.nc >= 1 && g.nc <= ncomp && g.nb >= 1 && g.nb <= g.nblk && g.na >= 1 && g.na <= NA);
+        NEED(g.off_tw >= 256 && g.off_dht >= g.off_tw + (g.L + (size_t)Nkz * Nkz) * 16);
+        NEED(g.off_d >= g.off_dht + NA * NB * 3 * NN * 8);
+        NEED(g.off_g >= g.off_d + g.nc * ((size_t)NA * NB * 9 * row));
+        NEED(g.off_s >= g.off_g + (size_t)g.nc * g.nb * NA * NN * row);
+        NEED(g.bytes >= g.off_s + (size_t)g.nc * g.nb * g.na * NN * row);
+        NEED(g.bytes <= speck::kHardBytes && ((g.off_tw | g.off_dht | g.off_d | g.off_g | g.off_s) & 15) == 0);
+        d.tile_e = 2;
+        NEED(!spectral_geometry(d, s.data()).on);
+    }
+    printf("%d of %d problems take the spectral form, %d failures\n", on, total, fails);
+    if (!fails && on > 1000)
+        printf("OK\n");
+    return fails != 0;
+}
