@@ -23,8 +23,8 @@
 // pass reads and writes whole runs of points.  Rounding is that of binary64
 // transforms: relative to the largest values of a block, as in any sum over them.
 // Device scale (NA = 1024, NB = 4, Norb = 10, Nkz = Nqz = 7, NE = 1000, Nw = 30, both
-// components, complex128): 1609 ms per call in the direct kernel, 139 ms here, of
-// which the transforms (at the rate of a copy, 4.4 TB/s) 26 ms, the sandwich 112 ms.
+// components, complex128): 1609 ms per call in the direct kernel, 84 ms here, of
+// which the transforms (at the rate of a copy, 4.4 TB/s) 26 ms, the sandwich 57 ms.
 // Inputs that are not finite, or so large that a transform overflows, raise a flag;
 // the direct kernel then recomputes Sigma (its sums meet fewer elements).
 #include <hip/hip_runtime.h>
@@ -378,20 +378,36 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_inverse(const A ar
         atomicOr(J.flag(), 1u);
 }
 
+// Keeps a value's computation where it stands: the compiler would otherwise sink the
+// FMAs of a loop past the branches that follow it, holding every operand meanwhile.
+__device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
+
 // S^[a][m, n'][point] = sum_b sum_ij D^_ij[point] (dH_i . G^_f[point] . dH_j^T)[m][n'].
-// A workgroup takes P points of one atom; a lane takes row m of one point, so that
-// per neighbour it holds M_i[m, :] = (dH_i G^)[m, :] (three rows of CB columns),
-// combines them into T_j[m, n] = sum_i D^_ij M_i[m, n] and adds T_j[m, n] dH_j[:, n] to
-// its row of S^, with dH_j wave-uniform (scalar loads).  Only G^ passes through LDS
-// (read by the Norb lanes of a point): 1560 FMAs against 100 16-byte reads per lane
-// and neighbour at Norb = 10.
-template <int No, int CB, typename A>
-__global__ __launch_bounds__(kSB, 2) void k_spec_sandwich(const A arg)
+// A workgroup takes P points of one atom; a lane takes row m of one point.  Per
+// neighbour and block of CB columns it forms M_i[m, n] = (dH_i G^)[m, n] from LDS, then
+// T_j[m, n] = sum_i D^_ij M_i[m, n] and adds T_j[m, n] dH_j[:, n] to its row of S^ with the
+// wave-uniform dH_j in scalar registers.  Both halves are pipelined by hand (the
+// compiler waits for every read where it is used): kAhead LDS reads are in flight
+// ahead of the FMAs that need them, and the scalar loads of step (j, n + 1) during
+// step (j, n), one wait per step (scalar loads complete out of order, so a wait for
+// one is a wait for all).  The next neighbour's G^ is copied into LDS during the
+// second half, which does not read it.
+//
+// Bound: binary64 FMA issue, and the power it takes.  At device scale (Norb = 10) the
+// vector units are busy 72% of the cycles, 1560 of 1740 vector instructions per lane
+// and neighbour are FMAs, LDS is busy 38% of the cycles, and the clock sinks from 2.4
+// to 1.9 GHz: 3.6 ms per energy block of 160, 7.0 ms before the hand pipelining (FMA
+// issue at 2.4 GHz: 1.9 ms).  Leaving out the copies, the scalar loads or the LDS
+// reads shortens it by 8 to 14% each: none of them alone is what it waits for.
+template <int No, int CB, int W, typename A>
+__global__ __launch_bounds__(kSB, W) void k_spec_sandwich(const A arg)
 {
     extern __shared__ double2 lds[];
     const Job J = job(arg);
     const auto &p = *J.p;
+    constexpr int kAhead = CB < 4 ? CB : 4;  // at most a row: h holds two
     constexpr int NN = No * No, P = kSB / No;
+    constexpr int NC = (No + CB - 1) / CB;                  // column blocks; the last may be ragged
     double *hs = reinterpret_cast<double *>(lds + NN * P);  // [3][No][No]
     // all XCDs work on one group of points at a time (its G^ rows stay in the
     // last-level cache); an XCD takes neighbouring atoms
@@ -403,44 +419,61 @@ __global__ __launch_bounds__(kSB, 2) void k_spec_sandwich(const A arg)
     if (al >= J.s.na || x >= (int64_t)p.npg * J.s.nb)
         return;
     const int pg = (int)(x % p.npg), blk = (int)(x / p.npg);
-    const int a = J.s.a0 + al, pt0 = pg * P;
+    const int a = J.s.a0 + al, pt0 = pg * P, npt = p.npt;
     const int tid = threadIdx.x, m = tid / P, pt = tid - m * P;
-    const bool act = m < No && pt0 + pt < p.npt;
+    const bool act = m < No && pt0 + pt < npt;
     const int mr = act ? m : 0, pr = act ? pt : 0;
-    const double2 *Gh = J.Gh() + ((size_t)blockIdx.y * J.s.nb + blk) * p.NA * NN * p.npt + pt0;
-    const double2 *Dh = J.Dh() + ((size_t)blockIdx.y * p.NA + a) * p.NB * kNF * p.npt + pt0 + pr;
-    const int np = min(P, p.npt - pt0);
+    const double2 *Gh = J.Gh() + ((size_t)blockIdx.y * J.s.nb + blk) * p.NA * NN * npt + pt0;
+    const double2 *Dh = J.Dh() + ((size_t)blockIdx.y * p.NA + a) * p.NB * kNF * npt + pt0;
+    const int np = min(P, npt - pt0);
+    const_ptr<int32_t> neigh = ro(J.t.neigh) + (size_t)a * p.NB;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    auto next_valid = [&](int b) {
+        while (b < p.NB && (unsigned)neigh[b] >= (unsigned)p.NA)
+            ++b;
+        return b;
+    };
+    // start the copies of neighbour b's G^ points (those past the last point repeat it)
+    // and dH into LDS; 32-bit offsets from uniform bases
+    auto issue = [&](int b) {
+        int t = tid;
+        asm volatile("" : "+v"(t));  // recomputed per neighbour rather than held
+        const char *g = reinterpret_cast<const char *>(Gh + (size_t)neigh[b] * NN * npt);
+        uint32_t *dst = reinterpret_cast<uint32_t *>(lds) + wave * 64 * 4;
+#pragma unroll
+        for (int i = 0; i < (NN * P + kSB - 1) / kSB; ++i) {
+            const int u = t + i * kSB, c = u / P, q = min(u - c * P, np - 1);
+            if (NN * P % kSB == 0 || u < NN * P)
+                lds_copy<4>(g + (unsigned)((c * npt + q) * 16), dst + i * kSB * 4);
+        }
+        const char *h = reinterpret_cast<const char *>(J.t.dH + ((size_t)a * p.NB + b) * kN3D * NN);
+        uint32_t *hd = reinterpret_cast<uint32_t *>(hs) + wave * 64;
+#pragma unroll
+        for (int i = 0; i < (kN3D * NN * 2 + kSB - 1) / kSB; ++i)
+            if (t + i * kSB < kN3D * NN * 2)
+                lds_copy<1>(h + (unsigned)((t + i * kSB) * 4), hd + i * kSB);
+    };
 
     double sr[No], si[No];
 #pragma unroll
     for (int n = 0; n < No; ++n)
         sr[n] = si[n] = 0.0;
-    for (int b = 0; b < p.NB; ++b) {
-        const int f = ro(J.t.neigh)[(size_t)a * p.NB + b];
-        if ((unsigned)f >= (unsigned)p.NA)
-            continue;
-        __syncthreads();  // the previous neighbour's reads are done
-        const double2 *g = Gh + (size_t)f * NN * p.npt;
-        if (np == P) {
-            copy_window<4, kSB>(reinterpret_cast<uint32_t *>(lds), reinterpret_cast<const uint32_t *>(g),
-                                (int64_t)p.npt * 4, 0, NN, NN, P * 4, reinterpret_cast<const uint32_t *>(g));
-        } else {
-            for (int i = tid; i < NN * P; i += kSB) {
-                const int c = i / P, q = i - c * P;
-                lds[i] = q < np ? g[(size_t)c * p.npt + q] : make_double2(0.0, 0.0);
-            }
-        }
-        const double *h = J.t.dH + ((size_t)a * p.NB + b) * kN3D * NN;
-        for (int i = tid; i < kN3D * NN; i += kSB)
-            hs[i] = h[i];
-        double2 d[kNF];
-#pragma unroll
-        for (int i = 0; i < kNF; ++i)
-            d[i] = Dh[((size_t)b * kNF + i) * p.npt];
-        __syncthreads();
+    int b = next_valid(0);
+    if (b < p.NB)
+        issue(b);
+    while (b < p.NB) {
+        const int bn = next_valid(b + 1);
+        __syncthreads();  // neighbour b has landed
         const_ptr<double> ht = ro(J.dht() + ((size_t)a * p.NB + b) * kN3D * NN);
+        const double2 *db = Dh + (size_t)b * kNF * npt;
 #pragma unroll 1
-        for (int c0 = 0; c0 < No; c0 += CB) {
+        for (int cb = 0; cb < NC; ++cb) {
+            const int c0 = cb * CB;
+            double2 d[kN3D];  // D^_ij of the current j
+#pragma unroll
+            for (int i = 0; i < kN3D; ++i)
+                d[i] = (db + (size_t)i * kN3D * npt)[pr];
             double xr[kN3D][CB], xi[kN3D][CB];
 #pragma unroll
             for (int i = 0; i < kN3D; ++i)
@@ -449,54 +482,88 @@ __global__ __launch_bounds__(kSB, 2) void k_spec_sandwich(const A arg)
                     xr[i][n] = xi[i][n] = 0.0;
             const double *hm = hs + mr * No;
             const double2 *gp = lds + c0 * P + pr;
-#pragma unroll 2
-            for (int l = 0; l < No; ++l) {
-                double hv[kN3D];
+            double2 v[kAhead];
+            double h[2][kN3D];
+            // element el = (l, n) of the walk over G^[l, c0 + n]
+            auto read = [&](int el) {
+                const int l = el / CB, n = el - l * CB;
+                if (n == 0)
 #pragma unroll
-                for (int i = 0; i < kN3D; ++i)
-                    hv[i] = hm[i * NN + l];
+                    for (int i = 0; i < kN3D; ++i)
+                        h[l & 1][i] = hm[i * NN + l];
+                // past the last column of a ragged block: a column whose result is dropped
+                v[el % kAhead] = gp[(l * No + (No % CB == 0 || c0 + n < No ? n : 0)) * P];
+            };
 #pragma unroll
-                for (int n = 0; n < CB; ++n) {
-                    // past the last column of a ragged block: a column whose result is dropped
-                    const int nn = No % CB == 0 || c0 + n < No ? n : 0;
-                    const double2 v = gp[(l * No + nn) * P];
+            for (int el = 0; el < kAhead; ++el)
+                read(el);
 #pragma unroll
-                    for (int i = 0; i < kN3D; ++i) {
-                        xr[i][n] = fma(hv[i], v.x, xr[i][n]);
-                        xi[i][n] = fma(hv[i], v.y, xi[i][n]);
-                    }
+            for (int el = 0; el < No * CB; ++el) {
+                const int l = el / CB, n = el - l * CB;
+                const double2 g = v[el % kAhead];
+#pragma unroll
+                for (int i = 0; i < kN3D; ++i) {
+                    xr[i][n] = fma(h[l & 1][i], g.x, xr[i][n]);
+                    xi[i][n] = fma(h[l & 1][i], g.y, xi[i][n]);
+                    pin(xr[i][n]);
+                    pin(xi[i][n]);
+                }
+                if (el + kAhead < No * CB)
+                    read(el + kAhead);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (cb == NC - 1) {
+                __syncthreads();  // every wave is done with G^ and dH of neighbour b
+                if (bn < p.NB)
+                    issue(bn);
+            }
+            double w[2][No];
+            auto read_h = [&](int step) {
+                const int j = step / CB, n = step % CB;
+                const int nn = No % CB == 0 || c0 + n < No ? c0 + n : 0;
+#pragma unroll
+                for (int q = 0; q < No; ++q)
+                    w[step & 1][q] = ht[(j * No + nn) * No + q];
+            };
+            read_h(0);
+#pragma unroll
+            for (int step = 0; step < kN3D * CB; ++step) {
+                const int j = step / CB, n = step % CB;
+                double tr = 0.0, ti = 0.0;
+#pragma unroll
+                for (int i = 0; i < kN3D; ++i) {
+                    tr = fma(d[i].x, xr[i][n], fma(-d[i].y, xi[i][n], tr));
+                    ti = fma(d[i].x, xi[i][n], fma(d[i].y, xr[i][n], ti));
+                }
+                if (No % CB != 0 && c0 + n >= No)
+                    tr = ti = 0.0;
+                if (n == CB - 1 && j + 1 < kN3D)
+#pragma unroll
+                    for (int i = 0; i < kN3D; ++i)
+                        d[i] = (db + ((size_t)i * kN3D + j + 1) * npt)[pr];
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (step + 1 < kN3D * CB)
+                    read_h(step + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int q = 0; q < No; ++q) {
+                    sr[q] = fma(tr, w[step & 1][q], sr[q]);
+                    si[q] = fma(ti, w[step & 1][q], si[q]);
                 }
             }
-#pragma unroll
-            for (int j = 0; j < kN3D; ++j)
-#pragma unroll
-                for (int n = 0; n < CB; ++n) {
-                    if (No % CB != 0 && c0 + n >= No)
-                        continue;
-                    double tr = 0.0, ti = 0.0;
-#pragma unroll
-                    for (int i = 0; i < kN3D; ++i) {
-                        const double2 v = d[i * kN3D + j];
-                        tr = fma(v.x, xr[i][n], fma(-v.y, xi[i][n], tr));
-                        ti = fma(v.x, xi[i][n], fma(v.y, xr[i][n], ti));
-                    }
-                    const_ptr<double> hj = ht + (j * No + c0 + n) * No;
-#pragma unroll
-                    for (int q = 0; q < No; ++q) {
-                        sr[q] = fma(tr, hj[q], sr[q]);
-                        si[q] = fma(ti, hj[q], si[q]);
-                    }
-                }
         }
+        b = bn;
     }
     bool bad = false;
     if (act) {
-        double2 *o = J.Sh() + (((size_t)blockIdx.y * J.s.nb + blk) * p.na_cap * NN + (size_t)al * NN + m * No) * p.npt +
+        double2 *o = J.Sh() + (((size_t)blockIdx.y * J.s.nb + blk) * p.na_cap * NN + (size_t)al * NN + m * No) * npt +
                      pt0 + pt;
 #pragma unroll
         for (int n = 0; n < No; ++n) {
             bad |= !(finite(sr[n]) && finite(si[n]));
-            o[(size_t)n * p.npt] = make_double2(sr[n], si[n]);
+            o[(size_t)n * npt] = make_double2(sr[n], si[n]);
         }
     }
     if (__any(bad) && (threadIdx.x & 63) == 0)
@@ -556,18 +623,22 @@ hipError_t transform_launch(int L, const A &arg, const Shape &h, bool fwd, hipSt
     return hipErrorInvalidValue;
 }
 
-// columns per block: three rows of M, one of S^ and D^ within 256 registers
-constexpr int col_block(int No) { return No <= 10 ? No : (No + 1) / 2; }
+// Columns per block and waves per SIMD of the sandwich kernel: half the columns keep
+// M, S^ and D^ of a lane within 168 registers up to 10 orbitals, so that three waves
+// share a SIMD.  At device scale 3.6 ms per energy block against 4.2 with all ten
+// columns at two waves (a Norb of 12: 1.01 ms per call at two waves, 1.07 at three).
+constexpr int col_block(int No) { return No <= 5 ? No : (No + 1) / 2; }
+constexpr int waves(int No) { return No <= 10 ? 3 : 2; }
 
 template <int No, typename A>
 hipError_t sandwich_launch(int norb, const A &arg, const Shape &h, hipStream_t s)
 {
     if (norb == No) {
         static bool done = false;
-        const hipError_t e = allow_lds(k_spec_sandwich<No, col_block(No), A>, speck::kLdsOne, done);
+        const hipError_t e = allow_lds(k_spec_sandwich<No, col_block(No), waves(No), A>, speck::kLdsOne, done);
         if (e != hipSuccess)
             return e;
-        hipLaunchKernelGGL((k_spec_sandwich<No, col_block(No), A>), h.grid, dim3(h.threads), h.lds, s, arg);
+        hipLaunchKernelGGL((k_spec_sandwich<No, col_block(No), waves(No), A>), h.grid, dim3(h.threads), h.lds, s, arg);
         return hipGetLastError();
     }
     if constexpr (No < speck::kMaxNorb)

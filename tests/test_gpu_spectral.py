@@ -39,6 +39,7 @@ CASES = {
     "many_momenta": (P(NA=5, NB=2, Norb=4, Nkz=23, Nqz=17, NE=50, Nw=8), 0),
     "one_momentum": (P(NA=8, NB=7, Norb=6, Nkz=1, Nqz=1, NE=300, Nw=40), 0),
     "norb_1": (P(NA=40, NB=4, Norb=1, Nkz=5, Nqz=5, NE=200, Nw=20), 0),
+    "norb_2": (P(NA=30, NB=4, Norb=2, Nkz=3, Nqz=3, NE=150, Nw=20), 0),
     "norb_9": (P(NA=7, NB=4, Norb=9, Nkz=3, Nqz=3, NE=61, Nw=9), 0),
     "norb_13_ragged_columns": (P(NA=7, NB=4, Norb=13, Nkz=3, Nqz=3, NE=61, Nw=9), 0),
     "norb_16": (P(NA=7, NB=4, Norb=16, Nkz=3, Nqz=3, NE=61, Nw=9), 0),
