@@ -233,7 +233,8 @@ sse_status sse_check_submit(sse_plan_t plan, const sse_args *args, const int32_t
  * holds both components, complex128 [2][Nkz, NE, NA, Norb, Norb] (lesser
  * first); Pi is complex128 [ncomp][Nqz, Nw, NA, NB + 1, 3, 3] (ncomp = 1: the
  * lesser only), overwritten, in the layout of the phonon Green's function
- * (Sec. 2) with the diagonal block in slot NB.  Workspace: at least 256 bytes.
+ * (Sec. 2) with the diagonal block in slot NB.  Workspace: the plan's, for the
+ * spectral form; at least 256 bytes, for the direct one.
  * SSE_ERR_UNSUPPORTED for another precision or Norb > 16; SSE_ERR_NEIGH (at
  * poll) for a neighbour index outside [0, NA), whose block is left zero.
  * Returns at once with a ticket (sse_poll / sse_wait).

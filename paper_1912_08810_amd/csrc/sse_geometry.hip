@@ -244,15 +244,44 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
     return false;
 }
 
-}  // namespace
+// The same for Pi: one or both components, then energy blocks; two transforms of G
+// per component (X and the opposite Y), every atom.
+bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
+{
+    const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
+    const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
+    const size_t tw = up(((size_t)g->L + (size_t)d.Nkz * d.Nkz) * 16);
+    const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
+    const size_t fixed = tw + dht + 4 * speck::kAlign + 4096;
+    // the output pass holds a transform row per momentum and its sums per frequency
+    if (((size_t)g->L + (size_t)d.Nkz * (g->L + 1 + d.Nw)) * 16 > speck::kLdsOne)
+        return false;
+    for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
+        const size_t base = fixed + g->nc * db, per = 2 * g->nc * gb;
+        if (budget < base + per)
+            continue;
+        g->nb = (int)std::min<size_t>(g->nblk, (budget - base) / per);
+        g->na = d.NA;
+        g->off_tw = speck::kAlign;
+        g->off_dht = g->off_tw + tw;
+        g->off_d = g->off_dht + dht;
+        g->off_g = g->off_d + up(g->nc * db);
+        g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
+        g->bytes = g->off_s + up((size_t)g->nc * g->nb * gb) + 4096;
+        return true;
+    }
+    return false;
+}
 
-SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift)
+// The cheapest transform length whose pass fits: points computed, weighted by what
+// pieces of under 64 bytes and one workgroup per CU cost the transforms.
+template <typename Layout>
+SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, Layout layout)
 {
     static const int kSizes[][2] = {{4, 4}, {4, 6}, {4, 8}, {6, 8}, {8, 8}, {8, 9}, {8, 10},
                                     {8, 12}, {10, 12}, {12, 12}, {10, 16}, {12, 16}, {16, 16}};
     SpectralGeom best;
-    // an explicit tile shape asks for the direct kernel that has tiles
-    if (d.Norb > speck::kMaxNorb || d.Nkz > 64 || d.tile_e > 0 || d.chunk_taps > 0)
+    if (d.Norb > speck::kMaxNorb || d.Nkz > 64)
         return best;
     const int64_t NN = (int64_t)d.Norb * d.Norb;
     if (d.NA * NN > (1 << 28) || (int64_t)d.NA * d.NB > (1 << 28))
@@ -290,10 +319,8 @@ SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift)
                 continue;
             const int items = d.Nkz * g.C * g.r2;
             g.fft_threads = std::min(speck::kFftBlock, (items + 63) / 64 * 64);
-            if (!spectral_layout(d, speck::kSoftBytes, &g) && !spectral_layout(d, speck::kHardBytes, &g))
+            if (!layout(d, speck::kSoftBytes, &g) && !layout(d, speck::kHardBytes, &g))
                 continue;
-            // transform points computed, weighted by what pieces of under 64 bytes and
-            // one workgroup per CU cost the transforms
             const int piece = g.C * (c64 ? 8 : 16);
             const double cost = (double)g.nblk * g.L * (1.0 + (piece < 64 ? 0.15 : 0.0) + (piece < 32 ? 0.3 : 0.0) +
                                                         (g.fft_lds > speck::kLdsTwo ? 0.1 : 0.0));
@@ -304,17 +331,52 @@ SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift)
             }
         }
     }
-    if (!best.on)
-        return best;
-    // Estimated microseconds of the two forms
-    const double pts = (double)d.Nkz * best.nblk * best.L * d.NA * NN;
-    const double spec = 25.0 + d.ncomp * (pts * d.NB * (24.0 * d.Norb + 72.0) / 45e6 + pts * 64.0 / 3.5e6);
-    const double flops = (double)d.Nkz * d.NE * d.NA * NN * d.NB *
-                         ((d.dt_antiherm ? 36.0 : 72.0) * d.Nqz * d.Nw + 48.0 * d.Norb);
+    return best;
+}
+
+// Estimated microseconds of the spectral form (both self-energies have the same work).
+double spectral_us(const sse_desc &d, const SpectralGeom &g)
+{
+    const double pts = (double)d.Nkz * g.nblk * g.L * d.NA * d.Norb * d.Norb;
+    return 25.0 + d.ncomp * (pts * d.NB * (24.0 * d.Norb + 72.0) / 45e6 + pts * 64.0 / 3.5e6);
+}
+
+double direct_flops(const sse_desc &d)
+{
+    return (double)d.Nkz * d.NE * d.NA * d.Norb * d.Norb * d.NB *
+           ((d.dt_antiherm ? 36.0 : 72.0) * d.Nqz * d.Nw + 48.0 * d.Norb);
+}
+
+}  // namespace
+
+SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift)
+{
+    // an explicit tile shape asks for the direct kernel that has tiles
+    if (d.tile_e > 0 || d.chunk_taps > 0)
+        return SpectralGeom();
+    const SpectralGeom g = best_geometry(d, w_shift, spectral_layout);
+    if (!g.on)
+        return g;
+    const double flops = direct_flops(d);
     const bool mfma = d.prec == SSE_FP32 || d.prec == SSE_BF16X3;
     const double rate = d.prec == SSE_BF16X3 ? 100e6 : d.prec == SSE_FP32 ? 50e6 : 55e6;
     const double direct = 10.0 + d.ncomp * std::max(flops / rate, 5.0 * d.NB * d.Nqz);
-    return spec < direct && (!mfma || flops > 3e10) ? best : SpectralGeom();
+    return spectral_us(d, g) < direct && (!mfma || flops > 3e10) ? g : SpectralGeom();
+}
+
+SpectralGeom spectral_pi_geometry(const sse_desc &d, const int32_t *w_shift)
+{
+    if (d.prec != SSE_FP64)
+        return SpectralGeom();
+    SpectralGeom g = best_geometry(d, w_shift, spectral_pi_layout);
+    if (!g.on)
+        return g;
+    // the sum over a point's rows reuses the Y^ region for nine values per lane
+    g.sand_lds = std::max((size_t)d.Norb * d.Norb, (size_t)kNF * d.Norb) * g.P * 16 +
+                 (size_t)kN3D * d.Norb * d.Norb * 8;
+    // the direct kernel walks all energies of all momenta in steps of 3.2 us
+    const double direct = 10.0 + d.ncomp * std::max(direct_flops(d) / 30e6, 3.2 * d.Nkz * d.NE);
+    return spectral_us(d, g) < direct ? g : SpectralGeom();
 }
 
 }  // namespace sse

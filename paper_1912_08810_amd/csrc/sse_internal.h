@@ -226,6 +226,7 @@ struct PiParams {
     int32_t tw[kMaxTaps];
     int32_t ts[kMaxTaps];
     int64_t n_wg;      // NA * Nqz * nbgroups * nchunk
+    const uint32_t *flag;  // not NULL: nothing is computed where it is zero
     double beta_re, beta_im;
 };
 

@@ -165,6 +165,9 @@ template <int MT, int NTN>
 __global__ __launch_bounds__(kBlock, 1) void k_pi_mfma(const PiParams p)
 {
     extern __shared__ double2 lds[];
+    // behind the spectral form: only if that met a value that is not finite
+    if (p.flag && ro(p.flag)[0] == 0u)
+        return;
     constexpr int ZC = 16 * NTN;                  // Zb row: 2 (b, i, j) columns, padded
     const int NN = p.NN, No = p.Norb, R = p.R, nbw = p.nbw;
     const int NNp = NN + (NN & 1);                // orbital pairs padded to an even count

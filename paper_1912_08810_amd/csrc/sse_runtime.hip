@@ -55,7 +55,8 @@ struct Instance {
     TileGeom geom;
     size_t afrag_bytes = 0;  // MFMA path: workspace for the A fragments (+ split G, bf16x3)
     int32_t shift[kMaxTaps] = {};  // the caller's shift table, in frequency order
-    SpectralGeom spec;  // spectral form, if it is the better one
+    SpectralGeom spec;  // spectral form of Sigma, if it is the better one
+    SpectralGeom pi_spec;  // and of Pi (single plans)
     TapTable redo_taps;  // binary64 direct kernel behind the spectral form: its tiles
     TileGeom redo_geom;
 };
@@ -67,7 +68,8 @@ constexpr size_t kStatusBytes = 256;  // status word region at the start of the 
 struct sse_plan_s {
     std::vector<Instance> inst;
     size_t ws_bytes = kStatusBytes;
-    size_t direct_bytes = kStatusBytes;  // what the direct kernels alone need (single plans)
+    size_t direct_bytes = kStatusBytes;  // single plans: what the direct kernels alone need,
+    size_t sigma_bytes = kStatusBytes;   // and Sigma in the plan's form
     bool batch = false;
     std::vector<int> direct;    // batch plans: instances of the persistent launch, in order
     // spectral instances: waves that share the workspace region at spec_off; a wave is
@@ -608,7 +610,10 @@ sse_status sse_plan(const sse_desc *desc, const int32_t *w_shift, sse_plan_t *pl
         return st;
     }
     p->direct_bytes = kStatusBytes + align256(p->inst[0].afrag_bytes);
-    p->ws_bytes = std::max(p->direct_bytes, kStatusBytes + align256(p->inst[0].spec.bytes));
+    if (spectral_pi_launch)
+        p->inst[0].pi_spec = spectral_pi_geometry(*desc, w_shift);
+    p->sigma_bytes = std::max(p->direct_bytes, kStatusBytes + align256(p->inst[0].spec.bytes));
+    p->ws_bytes = std::max(p->sigma_bytes, kStatusBytes + align256(p->inst[0].pi_spec.bytes));
     *plan = p;
     if (workspace_bytes)
         *workspace_bytes = p->ws_bytes;
@@ -822,7 +827,7 @@ sse_status sse_submit(sse_plan_t plan, const sse_args *args, void *workspace,
     if (st != SSE_OK)
         return st;
     uint32_t *dstatus = (uint32_t *)workspace;
-    const bool spectral = !plan->batch && plan->inst[0].spec.on && workspace_bytes >= plan->ws_bytes;
+    const bool spectral = !plan->batch && plan->inst[0].spec.on && workspace_bytes >= plan->sigma_bytes;
     hipError_t e = spectral ? hipSuccess : launch_clear_status(dstatus, s);
     if (e != hipSuccess) {
         ticket_release(tk);
@@ -965,7 +970,7 @@ sse_status sse_compute_noalloc(sse_plan_t plan, const int32_t *neigh, const doub
         return st;
     hipStream_t s = (hipStream_t)stream;
     uint32_t *dstatus = (uint32_t *)ws;
-    const bool spectral = plan->inst[0].spec.on && plan->ws_bytes <= (size_t)SSE_NOALLOC_SCRATCH_BYTES;
+    const bool spectral = plan->inst[0].spec.on && plan->sigma_bytes <= (size_t)SSE_NOALLOC_SCRATCH_BYTES;
     hipError_t e = spectral ? hipSuccess : launch_clear_status(dstatus, s);
     if (e != hipSuccess)
         return hip_fail(e, "clear_status launch");
@@ -1015,9 +1020,16 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
     if (st != SSE_OK)
         return st;
     uint32_t *dstatus = (uint32_t *)workspace;
-    hipError_t e = launch_clear_status(dstatus, s);
-    if (e == hipSuccess)
-        e = launch_validate_neigh(neigh, (int64_t)d.NA * d.NB, d.NA, dstatus, s);
+    char *wsfree = (char *)workspace + kStatusBytes;
+    const bool spectral = I.pi_spec.on && workspace_bytes >= kStatusBytes + I.pi_spec.bytes;
+    hipError_t e;
+    if (spectral) {
+        e = spectral_pi_launch(d, I.pi_spec, I.shift, neigh, dH, G, Pi, dstatus, wsfree, s);
+    } else {
+        e = launch_clear_status(dstatus, s);
+        if (e == hipSuccess)
+            e = launch_validate_neigh(neigh, (int64_t)d.NA * d.NB, d.NA, dstatus, s);
+    }
     const size_t NN = (size_t)d.Norb * d.Norb;
     const size_t g_elems = (size_t)d.Nkz * d.NE * d.NA * NN;
     const size_t pi_elems = (size_t)d.Nqz * d.Nw * d.NA * (d.NB + 1) * kNF;
@@ -1045,6 +1057,7 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
         memcpy(pp.tw, gm.tw, sizeof pp.tw);
         memcpy(pp.ts, gm.ts, sizeof pp.ts);
         pp.n_wg = n_wg;
+        pp.flag = spectral ? (const uint32_t *)wsfree : nullptr;
         pp.beta_re = d.alpha_re;
         pp.beta_im = d.alpha_im;
         e = pi_launch(pp, gm.lds_bytes, s);

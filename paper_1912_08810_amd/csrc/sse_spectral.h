@@ -36,7 +36,8 @@ struct SpectralGeom {
     size_t sand_lds = 0;
     // one pass holds nc components, nb energy blocks, and the sandwich's output for na atoms
     int nc = 0, nb = 0, na = 0;
-    size_t off_tw = 256, off_dht = 0, off_d = 0, off_g = 0, off_s = 0, bytes = 0;
+    // Sigma: D^, G^ and S^ at off_d, off_g, off_s; Pi: P^, X^ and Y^ there
+    size_t off_tw = 0, off_dht = 0, off_d = 0, off_g = 0, off_s = 0, bytes = 0;
 };
 
 // Sizes, tables and workspace layout of one instance, as the kernels take them.
@@ -58,6 +59,9 @@ struct SpecParams {
 //   Dh   [components][NA][NB][9][npt]
 //   Gh   [components][blocks][NA NN][npt]
 //   Sh   [components][blocks][na_cap NN][npt]
+// For Pi (G the shifted component X or the opposite one Y, Sigma the result Pi)
+//   Dh   P^ [components][NA][NB][9][npt], the products summed over the energy blocks
+//   Gh   X^, Sh   Y^   [components][blocks][NA NN][npt]
 struct SpecPtrs {
     const int32_t *neigh;
     const double *dH;
@@ -70,6 +74,9 @@ struct SpecPtrs {
 // [a0, a0 + na) of the sandwich's output (components: the grid's y extent).
 struct SpecPass {
     int32_t blk0, nb, a0, na;
+    int32_t e_off, nrow;  // forward transforms: rows [e_off, e_off + nrow) from a block's first energy,
+    int64_t src_c;        // elements from one component's input to the next,
+    int64_t dst;          // and the workspace offset of the result
 };
 
 struct SpecOne {
@@ -91,6 +98,9 @@ struct SpecMany {
     uint8_t idx[kMaxBatch];
     SpecPtrs t[kMaxBatch];
 };
+
+// The same as spectral_geometry for the phonon self-energy.
+SpectralGeom spectral_pi_geometry(const sse_desc &d, const int32_t *w_shift);
 
 // Chooses L, the channels per workgroup and the workspace; g.on says whether the
 // spectral form is the better one for this problem (host, sse_geometry.hip).
@@ -117,5 +127,11 @@ __attribute__((weak)) hipError_t spectral_batch_launch(int n, const sse_desc *co
                                                        const SpecParams *params,
                                                        const Fp64Params *redo, size_t redo_lds,
                                                        uint32_t *status, char *ws, hipStream_t s);
+
+// Pi of every component; the non-finite flag for the direct kernel is at the start of ws.
+__attribute__((weak)) hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g,
+                                                    const int32_t *w_shift, const int32_t *neigh, const double *dH,
+                                                    const void *G, void *Pi, uint32_t *status, void *ws,
+                                                    hipStream_t s);
 
 }  // namespace sse

@@ -89,7 +89,7 @@ __device__ __forceinline__ Job job(const SpecMany &m)
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
     const_ptr<SpecParams> p = ro(m.params) + m.idx[lo];
-    return Job{p, m.t[lo], SpecPass{0, p->nblk, 0, p->NA}, x - m.start[lo], m.start[lo + 1] - m.start[lo]};
+    return Job{p, m.t[lo], SpecPass{0, p->nblk, 0, p->NA, -p->smax, p->L, p->g_elems, p->off_g}, x - m.start[lo], m.start[lo + 1] - m.start[lo]};
 }
 
 // Flag and status word, twiddle tables and dH^T; a grid-stride loop over the latter.
@@ -226,7 +226,9 @@ __device__ __forceinline__ double2 k_sum(const double2 (&v)[kNkzReg], const_ptr<
 // straight from global memory (R1 loads in flight per thread), twiddles, R2-point
 // transforms in LDS, then the transform over k on the way out.  A workgroup takes C
 // consecutive channels (64-byte pieces of each energy row) and all Nkz momenta.
-template <typename T, int R1, int R2, typename A>
+// S is the sign of the exponents: -1, or +1 for the opposite component of the phonon
+// self-energy, whose transform is wanted at the negated point.
+template <typename T, int R1, int R2, int S, typename A>
 __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A arg)
 {
     extern __shared__ double2 lds[];
@@ -239,9 +241,9 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A ar
         return;
     const int64_t x = xcd_remap(J.bid, (int64_t)ngrp * J.s.nb);
     const int blk = (int)(x / ngrp), ch0 = (int)(x - (int64_t)blk * ngrp) << p.logC;
-    const T *src = (const T *)J.t.G + (size_t)blockIdx.y * p.g_elems;
+    const T *src = (const T *)J.t.G + (int64_t)blockIdx.y * J.s.src_c;
     const double2 *tw = J.tw();
-    const int ebase = (J.s.blk0 + blk) * p.V - p.smax;
+    const int ebase = (J.s.blk0 + blk) * p.V + J.s.e_off, nrow = J.s.nrow;
     for (int it = threadIdx.x; it < Nkz * C * R2; it += blockDim.x) {
         const int ch = it & (C - 1), r = it >> p.logC, k = r / R2, n2 = r - k * R2;
         const bool ok = ch0 + ch < NC;
@@ -249,23 +251,23 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A ar
         double2 v[R1];
 #pragma unroll
         for (int n1 = 0; n1 < R1; ++n1) {
-            const int e = ebase + n1 * R2 + n2;
-            v[n1] = ok && e >= 0 && e < p.NE ? to_d2(row[(int64_t)e * NC]) : make_double2(0.0, 0.0);
+            const int r = n1 * R2 + n2, e = ebase + r;
+            v[n1] = ok && r < nrow && e >= 0 && e < p.NE ? to_d2(row[(int64_t)e * NC]) : make_double2(0.0, 0.0);
         }
-        dft::transform<R1, -1>(v);
+        dft::transform<R1, S>(v);
         double2 *o = lds + (size_t)(k * C + ch) * rowp + n2;
         o[0] = v[0];
 #pragma unroll
         for (int k1 = 1; k1 < R1; ++k1) {
             const double2 t = tw[k1 * n2];
-            o[k1 * (R2 + 1)] = dft::cmul(v[k1], t.x, t.y);
+            o[k1 * (R2 + 1)] = dft::cmul(v[k1], t.x, -S * t.y);
         }
     }
     __syncthreads();
-    second_step<R1, R2, -1>(lds, Nkz * C, rowp);
+    second_step<R1, R2, S>(lds, Nkz * C, rowp);
     __syncthreads();
     const_ptr<double2> twk = ro(tw + L);
-    double2 *out = J.Gh() + (((size_t)blockIdx.y * J.s.nb + blk) * NC + ch0) * p.npt;
+    double2 *out = reinterpret_cast<double2 *>(J.t.ws + J.s.dst) + (((size_t)blockIdx.y * J.s.nb + blk) * NC + ch0) * p.npt;
     for (int it = threadIdx.x; it < L * C; it += blockDim.x) {
         const int ch = it / L, eps = it - ch * L;
         if (ch0 + ch >= NC)
@@ -278,13 +280,13 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A ar
             for (int k = 0; k < kNkzReg; ++k)
                 v[k] = k < Nkz ? y[(size_t)k * C * rowp] : make_double2(0.0, 0.0);
             for (int kap = 0; kap < Nkz; ++kap)
-                o[(size_t)kap * L] = k_sum<-1>(v, twk + kap * Nkz, Nkz);
+                o[(size_t)kap * L] = k_sum<S>(v, twk + kap * Nkz, Nkz);
         } else {
             for (int kap = 0; kap < Nkz; ++kap) {
                 double xr = 0.0, xi = 0.0;
                 for (int k = 0; k < Nkz; ++k) {
                     const double2 v = y[(size_t)k * C * rowp];
-                    const double c = twk[kap * Nkz + k].x, s = twk[kap * Nkz + k].y;
+                    const double c = twk[kap * Nkz + k].x, s = -S * twk[kap * Nkz + k].y;
                     xr = fma(v.x, c, fma(-v.y, s, xr));
                     xi = fma(v.x, s, fma(v.y, c, xi));
                 }
@@ -570,6 +572,258 @@ __global__ __launch_bounds__(kSB, W) void k_spec_sandwich(const A arg)
         atomicOr(J.flag(), 1u);
 }
 
+// The phonon self-energy (Eqs. (4)-(5)): P_ij[q, w] = sum_k sum_e tr(dH_i^T X[k + q, e + s_w, a]
+// dH_j Y[k, e, f]) is a correlation over (k, e), so with X^ the transform of the shifted
+// component and Y^ that of the opposite one at the negated point,
+//   P^_ij[point] = tr(dH_i^T X^ dH_j Y^) = sum_m sum_n U_i[n, m] W_j[m, n],
+//   W_j = dH_j Y^,  U_i = dH_i^T X^,
+// summed over the energy blocks (block n: V energies of Y, and of X the L rows from
+// e0 + smin).  As in k_spec_sandwich a workgroup takes P points of one atom and a lane
+// one point and row m: W_j[m, :] comes from LDS, U_i[n, m] from the lane's column m of X^
+// with wave-uniform dH_i, and the sum over m goes through LDS once per neighbour.
+// The same pipelining, and the same bound.  NA = 128, NE = 500, otherwise as the device-
+// scale problem, both components: 204.6 ms per call in the direct kernel, 5.6 ms here, of
+// which this kernel 3.9 ms and the four transforms 1.8 ms (the CPU-scale configuration:
+// 1270 and 63 us).
+template <int No, int CB, int W>
+__global__ __launch_bounds__(kSB, W) void k_spec_pi(const SpecOne arg)
+{
+    extern __shared__ double2 lds[];
+    const Job J = job(arg);
+    const auto &p = *J.p;
+    constexpr int kAhead = CB < 4 ? CB : 4;  // at most a row: h holds two
+    constexpr int NN = No * No, P = kSB / No;
+    constexpr int NC = (No + CB - 1) / CB;   // column blocks; the last may be ragged
+    double *hs = reinterpret_cast<double *>(lds + (NN > kNF * No ? NN : kNF * No) * P);  // [3][No][No]
+    const int na8 = (p.NA + 7) >> 3, per = na8 * 8;
+    const int in = (int)(J.bid % per), pg = (int)(J.bid / per);
+    const int a = (in & 7) * na8 + (in >> 3);
+    if (a >= p.NA || pg >= p.npg)
+        return;
+    const int pt0 = pg * P, npt = p.npt;
+    const int tid = threadIdx.x, m = tid / P, pt = tid - m * P;
+    const int np = min(P, npt - pt0);
+    const bool act = m < No && pt < np;
+    const int mr = act ? m : 0, pr = act ? pt : 0;
+    const size_t comp = (size_t)blockIdx.y * J.s.nb * p.NA * NN * npt + pt0;
+    double2 *Ph = J.Dh() + ((size_t)blockIdx.y * p.NA + a) * p.NB * kNF * npt + pt0;
+    const_ptr<int32_t> neigh = ro(J.t.neigh) + (size_t)a * p.NB;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+    // start the copies of neighbour b's Y^ points (those past the last point repeat it) and dH
+    auto issue = [&](int blk, int b) {
+        int t = tid;
+        asm volatile("" : "+v"(t));  // recomputed per neighbour rather than held
+        const char *g = reinterpret_cast<const char *>(J.Sh() + comp + ((size_t)blk * p.NA + neigh[b]) * NN * npt);
+        uint32_t *dst = reinterpret_cast<uint32_t *>(lds) + wave * 64 * 4;
+#pragma unroll
+        for (int i = 0; i < (NN * P + kSB - 1) / kSB; ++i) {
+            const int u = t + i * kSB, c = u / P, q = min(u - c * P, np - 1);
+            if (NN * P % kSB == 0 || u < NN * P)
+                lds_copy<4>(g + (unsigned)((c * npt + q) * 16), dst + i * kSB * 4);
+        }
+        const char *h = reinterpret_cast<const char *>(J.t.dH + ((size_t)a * p.NB + b) * kN3D * NN);
+        uint32_t *hd = reinterpret_cast<uint32_t *>(hs) + wave * 64;
+#pragma unroll
+        for (int i = 0; i < (kN3D * NN * 2 + kSB - 1) / kSB; ++i)
+            if (t + i * kSB < kN3D * NN * 2)
+                lds_copy<1>(h + (unsigned)((t + i * kSB) * 4), hd + i * kSB);
+    };
+
+    for (int blk = 0; blk < J.s.nb; ++blk) {
+        const bool add = J.s.blk0 + blk > 0;  // the first block's sums overwrite
+        double2 xc[No];                       // column m of X^
+        {
+            const double2 *xg = J.Gh() + comp + ((size_t)blk * p.NA + a) * NN * npt;
+#pragma unroll
+            for (int l = 0; l < No; ++l)
+                xc[l] = (xg + (size_t)l * No * npt)[(unsigned)(mr * npt + pr)];
+        }
+        for (int b = 0; b < p.NB; ++b) {
+            double2 *po = Ph + (size_t)b * kNF * npt;
+            if ((unsigned)neigh[b] >= (unsigned)p.NA) {
+                for (int i = tid; i < kNF * P; i += kSB)
+                    if (i % P < np && !add)
+                        po[(size_t)(i / P) * npt + i % P] = make_double2(0.0, 0.0);
+                continue;
+            }
+            __syncthreads();  // the previous neighbour's sums are read
+            issue(blk, b);
+            __syncthreads();
+            const_ptr<double> ht = ro(J.dht() + ((size_t)a * p.NB + b) * kN3D * NN);
+            double sr[kNF], si[kNF];
+#pragma unroll
+            for (int i = 0; i < kNF; ++i)
+                sr[i] = si[i] = 0.0;
+#pragma unroll 1
+            for (int cb = 0; cb < NC; ++cb) {
+                const int c0 = cb * CB;
+                double xr[kN3D][CB], xi[kN3D][CB];  // W_j[m, c0 + n]
+#pragma unroll
+                for (int j = 0; j < kN3D; ++j)
+#pragma unroll
+                    for (int n = 0; n < CB; ++n)
+                        xr[j][n] = xi[j][n] = 0.0;
+                const double *hm = hs + mr * No;
+                const double2 *gp = lds + c0 * P + pr;
+                double2 v[kAhead];
+                double h[2][kN3D];
+                auto read = [&](int el) {
+                    const int l = el / CB, n = el - l * CB;
+                    if (n == 0)
+#pragma unroll
+                        for (int j = 0; j < kN3D; ++j)
+                            h[l & 1][j] = hm[j * NN + l];
+                    v[el % kAhead] = gp[(l * No + (No % CB == 0 || c0 + n < No ? n : 0)) * P];
+                };
+#pragma unroll
+                for (int el = 0; el < kAhead; ++el)
+                    read(el);
+#pragma unroll
+                for (int el = 0; el < No * CB; ++el) {
+                    const int l = el / CB, n = el - l * CB;
+                    const double2 g = v[el % kAhead];
+#pragma unroll
+                    for (int j = 0; j < kN3D; ++j) {
+                        xr[j][n] = fma(h[l & 1][j], g.x, xr[j][n]);
+                        xi[j][n] = fma(h[l & 1][j], g.y, xi[j][n]);
+                        pin(xr[j][n]);
+                        pin(xi[j][n]);
+                    }
+                    if (el + kAhead < No * CB)
+                        read(el + kAhead);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                // step (i, n): dH_i[:, n] is read during the step before
+                double w[2][No];
+                auto read_h = [&](int step) {
+                    const int i = step / CB, n = step % CB;
+                    const int nn = No % CB == 0 || c0 + n < No ? c0 + n : 0;
+#pragma unroll
+                    for (int q = 0; q < No; ++q)
+                        w[step & 1][q] = ht[(i * No + nn) * No + q];
+                };
+                read_h(0);
+#pragma unroll
+                for (int step = 0; step < kN3D * CB; ++step) {
+                    const int i = step / CB, n = step % CB;
+                    __builtin_amdgcn_sched_barrier(0);
+                    __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (step + 1 < kN3D * CB)
+                        read_h(step + 1);
+                    __builtin_amdgcn_sched_barrier(0);
+                    double ur = 0.0, ui = 0.0;
+#pragma unroll
+                    for (int q = 0; q < No; ++q) {
+                        ur = fma(w[step & 1][q], xc[q].x, ur);
+                        ui = fma(w[step & 1][q], xc[q].y, ui);
+                    }
+                    if (No % CB != 0 && c0 + n >= No)
+                        ur = ui = 0.0;
+#pragma unroll
+                    for (int j = 0; j < kN3D; ++j) {
+                        double &zr = sr[i * kN3D + j], &zi = si[i * kN3D + j];
+                        zr = fma(ur, xr[j][n], fma(-ui, xi[j][n], zr));
+                        zi = fma(ur, xi[j][n], fma(ui, xr[j][n], zi));
+                    }
+                }
+            }
+            __syncthreads();  // every wave is done with Y^
+            if (m < No)
+#pragma unroll
+                for (int i = 0; i < kNF; ++i)
+                    lds[(i * No + m) * P + pt] = make_double2(sr[i], si[i]);
+            __syncthreads();
+            for (int i = tid; i < kNF * P; i += kSB) {
+                const int ij = i / P, q = i - ij * P;
+                if (q >= np)
+                    continue;
+                double2 *o = po + (size_t)ij * npt + q;
+                double2 s = add ? *o : make_double2(0.0, 0.0);
+                for (int r = 0; r < No; ++r) {
+                    const double2 t = lds[(ij * No + r) * P + q];
+                    s.x += t.x;
+                    s.y += t.y;
+                }
+                *o = s;
+            }
+        }
+    }
+}
+
+// Pi[q, w, a, b, i, j] = beta / (Nkz L) sum_kappa sum_eps P^_ij[kappa, eps]
+// exp(2 pi i (kappa q / Nkz + eps (s_w - smin) / L)), one workgroup per (a, b, i, j): the
+// eps sum per (kappa, w), split over 2^lg neighbouring lanes where there are few of them,
+// then the kappa sum per (q, w).  Also the neighbour-table check.
+__global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
+{
+    extern __shared__ double2 lds[];
+    const Job J = job(arg);
+    const auto &p = *J.p;
+    const int L = p.L, Nkz = p.Nkz, Nw = p.Nw, tid = threadIdx.x;
+    double2 *tw = lds;                // [L]
+    double2 *ph = tw + L;             // [Nkz][L + 1]
+    double2 *A = ph + Nkz * (L + 1);  // [Nkz][Nw]
+    const int64_t ab = J.bid / kNF;
+    const int ij = (int)(J.bid - ab * kNF);
+    const int a = (int)(ab / p.NB), b = (int)(ab - (int64_t)a * p.NB);
+    if (blockIdx.y == 0 && ij == 0 && tid == 0) {
+        const int f = J.t.neigh[ab];
+        if (f < 0 || f >= p.NA)
+            atomicOr(arg.status, kStatusBadNeigh);
+    }
+    for (int i = tid; i < L; i += kSB)
+        tw[i] = J.tw()[i];
+    const double2 *src = J.Dh() + (((size_t)blockIdx.y * p.NA * p.NB + ab) * kNF + ij) * p.npt;
+    for (int i = tid; i < p.npt; i += kSB)
+        ph[i + i / L] = src[i];
+    __syncthreads();
+    int lg = 0;
+    while (lg < 4 && (Nkz * Nw << (lg + 1)) <= kSB)
+        ++lg;
+    const int G = 1 << lg, part = tid & (G - 1);
+    // the lanes of a group take the same trips: the bound is a multiple of the group
+    for (int i = tid >> lg; i < Nkz * Nw; i += kSB >> lg) {
+        const int k = i / Nw, w = i - k * Nw, t0 = p.shift[w] - p.smin, st = (t0 << lg) % L;
+        double xr = 0.0, xi = 0.0;
+        int j = t0 * part % L;
+        for (int e = part; e < L; e += G) {
+            const double2 v = ph[k * (L + 1) + e], t = tw[j];  // t conjugated
+            xr = fma(v.x, t.x, fma(v.y, t.y, xr));
+            xi = fma(v.y, t.x, fma(-v.x, t.y, xi));
+            j += st;
+            j -= j >= L ? L : 0;
+        }
+        for (int h = 1; h < G; h <<= 1) {
+            xr += __shfl_xor(xr, h);
+            xi += __shfl_xor(xi, h);
+        }
+        if (part == 0)
+            A[i] = make_double2(xr, xi);
+    }
+    __syncthreads();
+    const_ptr<double2> twk = ro(J.tw() + L);
+    double2 *Pi = (double2 *)J.t.Sigma + (size_t)blockIdx.y * p.Nqz * Nw * p.NA * (p.NB + 1) * kNF;
+    const double sc = 1.0 / ((double)Nkz * L), br = p.alpha_re * sc, bi = p.alpha_im * sc;
+    bool bad = false;
+    for (int i = tid; i < p.Nqz * Nw; i += kSB) {
+        const int q = i / Nw, w = i - q * Nw;
+        double xr = 0.0, xi = 0.0;
+        for (int k = 0; k < Nkz; ++k) {
+            const double2 v = A[k * Nw + w];
+            const double c = twk[q * Nkz + k].x, s = -twk[q * Nkz + k].y;
+            xr = fma(v.x, c, fma(-v.y, s, xr));
+            xi = fma(v.x, s, fma(v.y, c, xi));
+        }
+        bad |= !(finite(xr) && finite(xi));
+        Pi[(((size_t)q * Nw + w) * p.NA + a) * (p.NB + 1) * kNF + b * kNF + ij] =
+            make_double2(br * xr - bi * xi, br * xi + bi * xr);
+    }
+    if (__any(bad) && (tid & 63) == 0)
+        atomicOr(J.flag(), 1u);
+}
+
 template <typename K>
 hipError_t allow_lds(K kernel, size_t bytes, bool &done)
 {
@@ -587,38 +841,43 @@ struct Shape {
     size_t lds;
 };
 
-template <typename T, int R1, int R2, typename A>
-hipError_t transform_as(const A &arg, const Shape &h, bool fwd, hipStream_t s)
+// Directions of the transforms: G to points, points to Sigma, and G to negated points.
+enum Direction { kForward, kInverse, kOpposite };
+
+template <Direction D, typename T, int R1, int R2, typename A>
+hipError_t transform_as(const A &arg, const Shape &h, hipStream_t s)
 {
-    static bool df = false, di = false;
-    hipError_t e = fwd ? allow_lds(k_spec_forward<T, R1, R2, A>, speck::kLdsOne, df)
-                       : allow_lds(k_spec_inverse<T, R1, R2, A>, speck::kLdsOne, di);
-    if (e != hipSuccess)
-        return e;
-    if (fwd)
-        hipLaunchKernelGGL((k_spec_forward<T, R1, R2, A>), h.grid, dim3(h.threads), h.lds, s, arg);
+    static bool done = false;
+    auto launch = [&](auto kernel) {
+        const hipError_t e = allow_lds(kernel, speck::kLdsOne, done);
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(kernel, h.grid, dim3(h.threads), h.lds, s, arg);
+        return hipGetLastError();
+    };
+    if constexpr (D == kInverse)
+        return launch(k_spec_inverse<T, R1, R2, A>);
     else
-        hipLaunchKernelGGL((k_spec_inverse<T, R1, R2, A>), h.grid, dim3(h.threads), h.lds, s, arg);
-    return hipGetLastError();
+        return launch(k_spec_forward<T, R1, R2, D == kForward ? -1 : 1, A>);
 }
 
-template <typename T, typename A>
-hipError_t transform_launch(int L, const A &arg, const Shape &h, bool fwd, hipStream_t s)
+template <Direction D, typename T, typename A>
+hipError_t transform_launch(int L, const A &arg, const Shape &h, hipStream_t s)
 {
     switch (L) {
-    case 16: return transform_as<T, 4, 4>(arg, h, fwd, s);
-    case 24: return transform_as<T, 4, 6>(arg, h, fwd, s);
-    case 32: return transform_as<T, 4, 8>(arg, h, fwd, s);
-    case 48: return transform_as<T, 6, 8>(arg, h, fwd, s);
-    case 64: return transform_as<T, 8, 8>(arg, h, fwd, s);
-    case 72: return transform_as<T, 8, 9>(arg, h, fwd, s);
-    case 80: return transform_as<T, 8, 10>(arg, h, fwd, s);
-    case 96: return transform_as<T, 8, 12>(arg, h, fwd, s);
-    case 120: return transform_as<T, 10, 12>(arg, h, fwd, s);
-    case 144: return transform_as<T, 12, 12>(arg, h, fwd, s);
-    case 160: return transform_as<T, 10, 16>(arg, h, fwd, s);
-    case 192: return transform_as<T, 12, 16>(arg, h, fwd, s);
-    case 256: return transform_as<T, 16, 16>(arg, h, fwd, s);
+    case 16: return transform_as<D, T, 4, 4>(arg, h, s);
+    case 24: return transform_as<D, T, 4, 6>(arg, h, s);
+    case 32: return transform_as<D, T, 4, 8>(arg, h, s);
+    case 48: return transform_as<D, T, 6, 8>(arg, h, s);
+    case 64: return transform_as<D, T, 8, 8>(arg, h, s);
+    case 72: return transform_as<D, T, 8, 9>(arg, h, s);
+    case 80: return transform_as<D, T, 8, 10>(arg, h, s);
+    case 96: return transform_as<D, T, 8, 12>(arg, h, s);
+    case 120: return transform_as<D, T, 10, 12>(arg, h, s);
+    case 144: return transform_as<D, T, 12, 12>(arg, h, s);
+    case 160: return transform_as<D, T, 10, 16>(arg, h, s);
+    case 192: return transform_as<D, T, 12, 16>(arg, h, s);
+    case 256: return transform_as<D, T, 16, 16>(arg, h, s);
     }
     return hipErrorInvalidValue;
 }
@@ -661,6 +920,10 @@ template <typename T>
 hipError_t sigma_passes(SpecOne o, const SpectralGeom &g, hipStream_t s)
 {
     const SpecParams &p = o.p;
+    o.s.e_off = -p.smax;
+    o.s.nrow = p.L;
+    o.s.src_c = p.g_elems;
+    o.s.dst = p.off_g;
     (void)hipGetLastError();
     hipLaunchKernelGGL(k_spec_setup<SpecOne>, dim3((unsigned)setup_wgs(p)), dim3(256), 0, s, o);
     hipError_t e = hipGetLastError();
@@ -676,14 +939,14 @@ hipError_t sigma_passes(SpecOne o, const SpectralGeom &g, hipStream_t s)
         for (o.s.blk0 = 0; o.s.blk0 < g.nblk && e == hipSuccess; o.s.blk0 += g.nb) {
             o.s.nb = std::min(g.nb, g.nblk - o.s.blk0);
             Shape h{dim3((unsigned)fft_wgs(p, p.NA, o.s.nb), nc), (unsigned)g.fft_threads, g.fft_lds};
-            e = transform_launch<T>(g.L, o, h, true, s);
+            e = transform_launch<kForward, T>(g.L, o, h, s);
             for (o.s.a0 = 0; o.s.a0 < p.NA && e == hipSuccess; o.s.a0 += g.na) {
                 o.s.na = std::min(g.na, p.NA - o.s.a0);
                 e = sandwich_launch<1>(p.Norb, o, Shape{dim3((unsigned)sandwich_wgs(p, o.s.na, o.s.nb), nc), kSB,
                                                         g.sand_lds}, s);
                 h.grid.x = (unsigned)fft_wgs(p, o.s.na, o.s.nb);
                 if (e == hipSuccess)
-                    e = transform_launch<T>(g.L, o, h, false, s);
+                    e = transform_launch<kInverse, T>(g.L, o, h, s);
             }
         }
     }
@@ -738,7 +1001,7 @@ hipError_t sigma_batch(const SpecMany &all, const SpecParams *hp, const Spectral
                                    return true;
                                },
                                [&](int j) { return fft_wgs(hp[j], hp[j].NA, hp[j].nblk); });
-            e = transform_launch<T>(g[i]->L, m, h, fwd, s);
+            e = fwd ? transform_launch<kForward, T>(g[i]->L, m, h, s) : transform_launch<kInverse, T>(g[i]->L, m, h, s);
         }
     };
     transforms(true);
@@ -803,6 +1066,80 @@ hipError_t spectral_batch_launch(int n, const sse_desc *const *d, const Spectral
                                    (const char *)a[i]->Dt + (size_t)c * hp[i].d_elems * eb,
                                    (char *)a[i]->Sigma + (size_t)c * hp[i].g_elems * eb, m.t[i].ws};
         e = fp64_redo_batch_launch(bl, c64, d[0]->dt_antiherm != 0, redo_lds, s);
+    }
+    return e;
+}
+
+namespace {
+
+constexpr int pi_col_block(int No) { return No <= 5 ? No : (No + 1) / 2; }
+constexpr int pi_waves(int No) { return No <= 10 ? 3 : 2; }
+
+template <int No>
+hipError_t pi_sandwich_launch(const SpecOne &o, const Shape &h, hipStream_t s)
+{
+    if (o.p.Norb == No) {
+        static bool done = false;
+        const hipError_t e = allow_lds(k_spec_pi<No, pi_col_block(No), pi_waves(No)>, speck::kLdsOne, done);
+        if (e != hipSuccess)
+            return e;
+        hipLaunchKernelGGL((k_spec_pi<No, pi_col_block(No), pi_waves(No)>), h.grid, dim3(h.threads), h.lds, s, o);
+        return hipGetLastError();
+    }
+    if constexpr (No < speck::kMaxNorb)
+        return pi_sandwich_launch<No + 1>(o, h, s);
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g, const int32_t *w_shift,
+                              const int32_t *neigh, const double *dH, const void *G, void *Pi, uint32_t *status,
+                              void *ws, hipStream_t s)
+{
+    SpecOne o{};
+    o.p = spectral_params(d, g, w_shift);
+    o.t = SpecPtrs{neigh, dH, nullptr, nullptr, nullptr, (char *)ws};
+    o.status = status;
+    o.clear = 1;
+    const SpecParams &p = o.p;
+    const size_t pi_elems = (size_t)d.Nqz * d.Nw * d.NA * (d.NB + 1) * kNF;
+    const size_t out_lds = ((size_t)g.L + (size_t)d.Nkz * (g.L + 1) + (size_t)d.Nkz * d.Nw) * sizeof(double2);
+    static bool done = false;
+    hipError_t e = allow_lds(k_spec_pi_out, speck::kLdsOne, done);
+    if (e != hipSuccess)
+        return e;
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(k_spec_setup<SpecOne>, dim3((unsigned)setup_wgs(p)), dim3(256), 0, s, o);
+    e = hipGetLastError();
+    const double2 *Gc = (const double2 *)G;
+    for (int c = 0; c < d.ncomp && e == hipSuccess; c += g.nc) {
+        const unsigned nc = (unsigned)std::min(g.nc, d.ncomp - c);
+        for (o.s.blk0 = 0; o.s.blk0 < g.nblk && e == hipSuccess; o.s.blk0 += g.nb) {
+            o.s.nb = std::min(g.nb, g.nblk - o.s.blk0);
+            const Shape h{dim3((unsigned)fft_wgs(p, p.NA, o.s.nb), nc), (unsigned)g.fft_threads, g.fft_lds};
+            o.t.G = Gc + (size_t)c * p.g_elems;
+            o.s.e_off = p.smin;
+            o.s.nrow = p.L;
+            o.s.src_c = p.g_elems;
+            o.s.dst = p.off_g;
+            e = transform_launch<kForward, double2>(g.L, o, h, s);
+            if (e != hipSuccess)
+                break;
+            o.t.G = Gc + (size_t)(1 - c) * p.g_elems;
+            o.s.e_off = 0;
+            o.s.nrow = p.V;
+            o.s.src_c = -p.g_elems;
+            o.s.dst = p.off_s;
+            e = transform_launch<kOpposite, double2>(g.L, o, h, s);
+            if (e == hipSuccess)
+                e = pi_sandwich_launch<1>(o, Shape{dim3((unsigned)sandwich_wgs(p, p.NA, 1), nc), kSB, g.sand_lds}, s);
+        }
+        if (e != hipSuccess)
+            break;
+        o.t.Sigma = (double2 *)Pi + (size_t)c * pi_elems;
+        hipLaunchKernelGGL(k_spec_pi_out, dim3((unsigned)(d.NA * d.NB * kNF), nc), dim3(kSB), out_lds, s, o);
+        e = hipGetLastError();
     }
     return e;
 }

@@ -25,9 +25,12 @@ def _plan(prob, prec=0, ncomp=1, **kw):
 
 
 def _is_spectral(prob, prec=0, ncomp=1):
-    """A spectral plan asks for more workspace than the direct kernels (a chunk cap
-    that changes nothing asks for those)."""
-    return _plan(prob, prec, ncomp).workspace_bytes > _plan(prob, prec, ncomp, chunk_taps=128).workspace_bytes
+    """A batch plan (Sigma alone) asks for more workspace where an instance takes the
+    spectral form than where a chunk cap that changes nothing asks for the direct one."""
+    from paper_1912_08810_amd import sse
+    need = [sse.sse_plan_batch(_plan(prob, prec, ncomp, **kw).descs, [prob.shifts()]).workspace_bytes
+            for kw in ({}, {"chunk_taps": 128})]
+    return need[0] > need[1]
 
 
 CASES = {
@@ -146,3 +149,66 @@ def test_batch_of_spectral_and_direct_instances_is_bitwise_one_by_one():
         assert torch.equal(dp.Sigma.view(torch.int64), b.view(torch.int64)), i
         if i != 3:
             assert gu.rel_fro(dp.sigma_host(1), gu.oracle_full(dp, 1)) <= 1e-12
+
+
+PI_CASES = {
+    "one_block": P(NA=9, NB=4, Norb=10, Nkz=3, Nqz=3, NE=37, Nw=6),
+    "block_exact": P(NA=6, NB=2, Norb=4, Nkz=3, Nqz=3, NE=2 * (160 - 11), Nw=12),
+    "ragged_blocks": P(NA=6, NB=3, Norb=5, Nkz=4, Nqz=4, NE=401, Nw=30),
+    "nqz_below_nkz": P(NA=8, NB=3, Norb=7, Nkz=7, Nqz=2, NE=90, Nw=9),
+    "nine_momenta": P(NA=6, NB=2, Norb=3, Nkz=9, Nqz=9, NE=70, Nw=8),
+    "one_momentum": P(NA=8, NB=7, Norb=6, Nkz=1, Nqz=1, NE=300, Nw=40),
+    "norb_1": P(NA=20, NB=4, Norb=1, Nkz=5, Nqz=5, NE=200, Nw=20),
+    "norb_2": P(NA=20, NB=4, Norb=2, Nkz=3, Nqz=3, NE=150, Nw=20),
+    "norb_9": P(NA=7, NB=4, Norb=9, Nkz=3, Nqz=3, NE=61, Nw=9),
+    "norb_13_ragged_columns": P(NA=7, NB=4, Norb=13, Nkz=3, Nqz=3, NE=61, Nw=9),
+    "norb_16": P(NA=7, NB=4, Norb=16, Nkz=3, Nqz=3, NE=61, Nw=9),
+    "signed_gaps": P(NA=8, NB=4, Norb=10, Nkz=5, Nqz=5, NE=66, Nw=8, shift=(17, -9, 4, 4, 31, -20, 0, 11)),
+}
+
+
+def _run_pi_in(dp, nbytes, ncomp=2):
+    """sse_pi_compute in a workspace of nbytes (0: the plan's): 256 bytes run the direct kernel."""
+    import torch
+    from paper_1912_08810_amd import sse
+    plan = _plan(dp.prob, 0, ncomp)
+    ws = torch.empty(nbytes or plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+    Pi = torch.full((ncomp, sse.pi_elems(plan.descs[0]) * 2), 3.0, dtype=torch.float64, device="cuda")
+    st = sse.sse_pi_compute(plan, dp.neigh, dp.dH, dp.G, Pi, ws, torch.cuda.current_stream(), check=False)
+    torch.cuda.synchronize()
+    return st, Pi
+
+
+@pytest.mark.parametrize("name", PI_CASES)
+def test_pi_matches_oracle(name):
+    prob = PI_CASES[name]
+    dp = gu.DeviceProblem(prob, 950 + len(name), ncomp=2)
+    st, Pi = _run_pi_in(dp, 0)
+    assert st == 0
+    for c in range(2):
+        e = gu.rel_fro(gu.pi_host(Pi, c, prob), gu.oracle_pi_full(dp, c))
+        print(f"  {name} comp {c}: rel_fro={e:.3e}", flush=True)
+        assert e <= 1e-12
+    one, Pi1 = _run_pi_in(dp, 0, ncomp=1)
+    assert one == 0 and gu.rel_fro(gu.pi_host(Pi1, 0, prob), gu.pi_host(Pi, 0, prob)) <= 1e-14
+
+
+def test_pi_not_finite_and_invalid_neighbours_are_what_the_direct_kernel_gives():
+    import torch
+    from paper_1912_08810_amd import sse
+    prob = P(NA=9, NB=3, Norb=6, Nkz=3, Nqz=3, NE=45, Nw=5)
+    dp = gu.DeviceProblem(prob, 83, ncomp=2)
+    bad = dp.neigh_h.copy()
+    bad[2, 1], bad[5, 0] = -1, prob.NA
+    dp.neigh.copy_(torch.from_numpy(bad))
+    st, got = _run_pi_in(dp, 0)
+    st2, want = _run_pi_in(dp, 256)
+    assert st == st2 == sse.ERR_NEIGH
+    w = gu.pi_host(want, 0, prob)
+    assert not w[:, :, 2, 1].any() and not gu.pi_host(got, 0, prob)[:, :, 2, 1].any()
+    assert gu.rel_fro(got.cpu().numpy(), want.cpu().numpy()) <= 1e-13
+    G = dp.G.view(-1)
+    G[G.numel() // 3], G[G.numel() // 5] = float("inf"), float("nan")
+    got, want = _run_pi_in(dp, 0)[1], _run_pi_in(dp, 256)[1]
+    assert torch.isnan(want).any() and not torch.isnan(want).all()
+    assert torch.equal(got.view(torch.int64), want.view(torch.int64))
