@@ -1,5 +1,5 @@
 // sse_dft.h -- small discrete Fourier transforms on register arrays of binary64
-// complex values: sizes 2, 3, 4 and 5 written out, larger ones as Cooley-Tukey
+// complex values: sizes 2, 3, 4, 5 and 7 written out, larger ones as Cooley-Tukey
 // products of two of them, with the twiddle factors as compile-time constants
 // (trivial ones without a multiplication).
 #pragma once
@@ -98,7 +98,7 @@ __device__ __forceinline__ void static_for(F f)
 
 constexpr int first_factor(int N)
 {
-    return N % 4 == 0 && N > 4 ? 4 : N % 3 == 0 ? 3 : N % 2 == 0 ? 2 : 5;
+    return N % 4 == 0 && N > 4 ? 4 : N % 3 == 0 ? 3 : N % 2 == 0 ? 2 : N % 5 == 0 ? 5 : 7;
 }
 
 // In place: v[k] <- sum_n v[n] exp(2 pi i S n k / N).
@@ -138,6 +138,26 @@ __device__ __forceinline__ void transform(double2 (&v)[N])
         v[4] = make_double2(a.x + e.y, a.y - e.x);
         v[2] = make_double2(b.x - f.y, b.y + f.x);
         v[3] = make_double2(b.x + f.y, b.y - f.x);
+    } else if constexpr (N == 7) {
+        // pairs n, 7 - n: the factors' real parts act on sums, the imaginary ones on differences
+        double2 p[3], m[3];
+        static_for<3>([&](auto i) {
+            p[i] = add(v[i + 1], v[6 - i]);
+            m[i] = sub(v[i + 1], v[6 - i]);
+        });
+        const double2 z = v[0];
+        v[0] = add(add(z, p[0]), add(p[1], p[2]));
+        static_for<3>([&](auto i) {
+            constexpr int k = decltype(i)::value + 1;
+            constexpr double c1 = cos2pi(k, 7), c2 = cos2pi(2 * k % 7, 7), c3 = cos2pi(3 * k % 7, 7);
+            constexpr double s1 = S * sin2pi(k, 7), s2 = S * sin2pi(2 * k % 7, 7), s3 = S * sin2pi(3 * k % 7, 7);
+            const double2 a = make_double2(fma(c1, p[0].x, fma(c2, p[1].x, fma(c3, p[2].x, z.x))),
+                                           fma(c1, p[0].y, fma(c2, p[1].y, fma(c3, p[2].y, z.y))));
+            const double2 b = make_double2(fma(s1, m[0].x, fma(s2, m[1].x, s3 * m[2].x)),
+                                           fma(s1, m[0].y, fma(s2, m[1].y, s3 * m[2].y)));
+            v[k] = make_double2(a.x - b.y, a.y + b.x);
+            v[7 - k] = make_double2(a.x + b.y, a.y - b.x);
+        });
     } else {
         // n = B n1 + n2, k = k1 + A k2
         constexpr int A = first_factor(N), B = N / A;

@@ -414,38 +414,49 @@ __global__ __launch_bounds__(kBlock, 2) void k_sse_fp64(const Fp64Params p)
     fp64_tile<T, AH>(ro(&p), ptr, a, k, et, lds);
 }
 
-// Every tile of an instance, by a grid of any size.
+// Every tile of an instance, all components, by a grid of any size.
 template <typename T, bool AH>
-__device__ __forceinline__ void walk_tiles(const_ptr<Fp64Params> pp, const TensorPtrs &ptr, double2 *lds)
+__device__ __forceinline__ void walk_tiles(const_ptr<Fp64Params> pp, TensorPtrs ptr, int ncomp, double2 *lds)
 {
     const auto &p = *pp;
-    for (int64_t L = blockIdx.x; L < p.n_wg; L += gridDim.x) {
-        const int k = (int)(L % p.Nkz);
-        const int et = (int)(L / p.Nkz % p.n_etiles);
-        const int a = (int)(L / p.Nkz / p.n_etiles);
-        fp64_tile<T, AH>(pp, ptr, a, k, et, lds);
-        __syncthreads();
+    const int64_t g = (int64_t)p.Nkz * p.NE * p.NA * p.NN, d = (int64_t)p.Nqz * p.Nw * p.NA * p.NB * kNF;
+    for (int c = 0; c < ncomp; ++c) {
+        for (int64_t L = blockIdx.x; L < p.n_wg; L += gridDim.x) {
+            const int k = (int)(L % p.Nkz);
+            const int et = (int)(L / p.Nkz % p.n_etiles);
+            const int a = (int)(L / p.Nkz / p.n_etiles);
+            fp64_tile<T, AH>(pp, ptr, a, k, et, lds);
+            __syncthreads();
+        }
+        ptr.G = (const T *)ptr.G + g;
+        ptr.D = (const T *)ptr.D + d;
+        ptr.Sigma = (T *)ptr.Sigma + g;
     }
 }
 
 // A fixed grid walks the tiles if the flag asks for them (the spectral form met a
-// value that is not finite); else every workgroup ends at once.
+// value that is not finite); else every workgroup ends at once.  The last launch of a
+// spectral submission, so it also delivers the status word: a copy of four bytes would
+// be a launch of its own.
 template <typename T, bool AH>
-__global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo(const Fp64Params p, const uint32_t *flag)
+__global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo(const Fp64Params p, int ncomp, const uint32_t *flag,
+                                                             const uint32_t *status, uint32_t *host)
 {
     extern __shared__ double2 lds[];
+    if (blockIdx.x == 0 && threadIdx.x == 0 && host)
+        __hip_atomic_store(host, *status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     if (ro(flag)[0] == 0u)
         return;
-    walk_tiles<T, AH>(ro(&p), TensorPtrs{p.neigh, p.dH, p.G, p.D, p.Sigma}, lds);
+    walk_tiles<T, AH>(ro(&p), TensorPtrs{p.neigh, p.dH, p.G, p.D, p.Sigma}, ncomp, lds);
 }
 
 template <typename T, bool AH>
-__global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo_batch(const BatchLaunch bl)
+__global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo_batch(const BatchLaunch bl, int ncomp)
 {
     extern __shared__ double2 lds[];
     for (int i = 0; i < bl.n; ++i)
         if (ro(reinterpret_cast<const uint32_t *>(bl.ptr[i].aux))[0] != 0u)
-            walk_tiles<T, AH>(ro(reinterpret_cast<const Fp64Params *>(bl.params)) + i, bl.ptr[i], lds);
+            walk_tiles<T, AH>(ro(reinterpret_cast<const Fp64Params *>(bl.params)) + i, bl.ptr[i], ncomp, lds);
 }
 
 // Persistent form: a fixed grid pulls tiles from the batch's work queues
@@ -529,7 +540,8 @@ static hipError_t launch_as(const Fp64Params &p, size_t lds_bytes, hipStream_t s
 }
 
 template <typename T, bool AH>
-static hipError_t redo_as(const Fp64Params &p, size_t lds_bytes, const uint32_t *flag, hipStream_t s)
+static hipError_t redo_as(const Fp64Params &p, size_t lds_bytes, int ncomp, const uint32_t *flag,
+                          const uint32_t *status, uint32_t *host, hipStream_t s)
 {
     static bool done = false;
     hipError_t e = set_lds_attr(k_sse_fp64_redo<T, AH>, done);
@@ -537,37 +549,37 @@ static hipError_t redo_as(const Fp64Params &p, size_t lds_bytes, const uint32_t 
         return e;
     (void)hipGetLastError();
     const unsigned grid = (unsigned)std::min<int64_t>(p.n_wg, 512);  // two per CU
-    hipLaunchKernelGGL((k_sse_fp64_redo<T, AH>), dim3(grid), dim3(kBlock), lds_bytes, s, p, flag);
+    hipLaunchKernelGGL((k_sse_fp64_redo<T, AH>), dim3(grid), dim3(kBlock), lds_bytes, s, p, ncomp, flag, status,
+                       host);
     return hipGetLastError();
 }
 
-hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes,
-                            const uint32_t *flag, hipStream_t s)
+hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, int ncomp,
+                            const uint32_t *flag, const uint32_t *status, uint32_t *host, hipStream_t s)
 {
-    if (p.n_wg <= 0)
-        return hipSuccess;
-    if (c64)
-        return ah ? redo_as<float2, true>(p, lds_bytes, flag, s) : redo_as<float2, false>(p, lds_bytes, flag, s);
-    return ah ? redo_as<double2, true>(p, lds_bytes, flag, s) : redo_as<double2, false>(p, lds_bytes, flag, s);
+    auto as = c64 ? (ah ? redo_as<float2, true> : redo_as<float2, false>)
+                  : (ah ? redo_as<double2, true> : redo_as<double2, false>);
+    return as(p, lds_bytes, ncomp, flag, status, host, s);
 }
 
 template <typename T, bool AH>
-static hipError_t redo_batch_as(const BatchLaunch &bl, size_t lds_bytes, hipStream_t s)
+static hipError_t redo_batch_as(const BatchLaunch &bl, size_t lds_bytes, int ncomp, hipStream_t s)
 {
     static bool done = false;
     hipError_t e = set_lds_attr(k_sse_fp64_redo_batch<T, AH>, done);
     if (e != hipSuccess)
         return e;
     (void)hipGetLastError();
-    hipLaunchKernelGGL((k_sse_fp64_redo_batch<T, AH>), dim3(512), dim3(kBlock), lds_bytes, s, bl);
+    hipLaunchKernelGGL((k_sse_fp64_redo_batch<T, AH>), dim3(512), dim3(kBlock), lds_bytes, s, bl, ncomp);
     return hipGetLastError();
 }
 
-hipError_t fp64_redo_batch_launch(const BatchLaunch &bl, bool c64, bool ah, size_t lds_bytes, hipStream_t s)
+hipError_t fp64_redo_batch_launch(const BatchLaunch &bl, bool c64, bool ah, size_t lds_bytes, int ncomp,
+                                  hipStream_t s)
 {
-    if (c64)
-        return ah ? redo_batch_as<float2, true>(bl, lds_bytes, s) : redo_batch_as<float2, false>(bl, lds_bytes, s);
-    return ah ? redo_batch_as<double2, true>(bl, lds_bytes, s) : redo_batch_as<double2, false>(bl, lds_bytes, s);
+    auto as = c64 ? (ah ? redo_batch_as<float2, true> : redo_batch_as<float2, false>)
+                  : (ah ? redo_batch_as<double2, true> : redo_batch_as<double2, false>);
+    return as(bl, lds_bytes, ncomp, s);
 }
 
 hipError_t fp64_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, hipStream_t s)

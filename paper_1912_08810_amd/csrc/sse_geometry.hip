@@ -201,7 +201,6 @@ SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32
     p.antiherm = d.dt_antiherm;
     p.g_elems = (int64_t)d.Nkz * d.NE * d.NA * p.NN;
     p.d_elems = (int64_t)d.Nqz * d.Nw * d.NA * d.NB * kNF;
-    p.off_tw = (int64_t)g.off_tw;
     p.off_dht = (int64_t)g.off_dht;
     p.off_d = (int64_t)g.off_d;
     p.off_g = (int64_t)g.off_g;
@@ -223,8 +222,7 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 {
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
-    const size_t tw = up(((size_t)g->L + (size_t)d.Nkz * d.Nkz) * 16);
-    const size_t fixed = tw + up((size_t)d.NA * d.NB * kN3D * NN * 8) + 4 * speck::kAlign + 4096;
+    const size_t fixed = up((size_t)d.NA * d.NB * kN3D * NN * 8) + 4 * speck::kAlign + 4096;
     for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
         const size_t base = fixed + g->nc * db, per = 2 * g->nc * gb;
         if (budget < base + (g->nc > 1 ? per : gb + gb / 8))
@@ -233,8 +231,7 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
         g->na = d.NA;
         if (base + per > budget)  // one component, one block, some atoms
             g->na = (int)std::max<size_t>(1, (budget - base - gb) / (NN * row));
-        g->off_tw = speck::kAlign;  // behind the non-finite flag
-        g->off_dht = g->off_tw + tw;
+        g->off_dht = speck::kAlign;  // behind the non-finite flag
         g->off_d = g->off_dht + up((size_t)d.NA * d.NB * kN3D * NN * 8);
         g->off_g = g->off_d + up(g->nc * db);
         g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
@@ -250,11 +247,10 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 {
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
-    const size_t tw = up(((size_t)g->L + (size_t)d.Nkz * d.Nkz) * 16);
     const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
-    const size_t fixed = tw + dht + 4 * speck::kAlign + 4096;
+    const size_t fixed = dht + 4 * speck::kAlign + 4096;
     // the output pass holds a transform row per momentum and its sums per frequency
-    if (((size_t)g->L + (size_t)d.Nkz * (g->L + 1 + d.Nw)) * 16 > speck::kLdsOne)
+    if (((size_t)g->L + (size_t)d.Nkz * (g->L + 2 + d.Nw)) * 16 > speck::kLdsOne)
         return false;
     for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
         const size_t base = fixed + g->nc * db, per = 2 * g->nc * gb;
@@ -262,8 +258,7 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
             continue;
         g->nb = (int)std::min<size_t>(g->nblk, (budget - base) / per);
         g->na = d.NA;
-        g->off_tw = speck::kAlign;
-        g->off_dht = g->off_tw + tw;
+        g->off_dht = speck::kAlign;
         g->off_d = g->off_dht + dht;
         g->off_g = g->off_d + up(g->nc * db);
         g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
@@ -310,11 +305,12 @@ SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, Layout lay
         g.sand_lds = (size_t)NN * g.P * 16 + kN3D * NN * 8;
         for (g.logC = 1; g.logC <= 3; ++g.logC) {
             g.C = 1 << g.logC;
-            // rows of one momentum and channel start 16 / C sixteen-byte banks apart
+            // the rows of a momentum's C channels start 16 / C sixteen-byte banks apart
+            // (an odd multiple of that, so that they take all C places)
             g.rowp = g.r1 * (g.r2 + 1);
-            while (g.rowp % 16 != 16 / g.C)
+            while (g.rowp % (32 / g.C) != 16 / g.C)
                 ++g.rowp;
-            g.fft_lds = (size_t)d.Nkz * g.C * g.rowp * 16;
+            g.fft_lds = ((size_t)g.L + d.Nkz + (size_t)d.Nkz * g.C * g.rowp) * 16;
             if (g.fft_lds > speck::kLdsOne)
                 continue;
             const int items = d.Nkz * g.C * g.r2;

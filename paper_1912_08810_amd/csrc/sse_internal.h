@@ -226,7 +226,11 @@ struct PiParams {
     int32_t tw[kMaxTaps];
     int32_t ts[kMaxTaps];
     int64_t n_wg;      // NA * Nqz * nbgroups * nchunk
+    int32_t ncomp;     // component c: X + c x_c, Y - c x_c, Pi + c pi_c
+    int64_t x_c, pi_c;
     const uint32_t *flag;  // not NULL: nothing is computed where it is zero
+    const uint32_t *status;  // copied to *host at the end if host is not NULL (pinned memory)
+    uint32_t *host;
     double beta_re, beta_im;
 };
 
@@ -286,11 +290,14 @@ TileGeom fp64_geometry(int Norb, int NE, const TapTable &taps_unchunked, int te_
                        int chunk_cap, TapTable *taps_out);
 // ah: D~ anti-Hermitian per 3 x 3 block (only i <= j read; half the tap FMAs).
 hipError_t fp64_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, hipStream_t s);
-// The same sums where *flag is not zero, nothing otherwise: a fixed grid that walks the tiles.
-hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes,
-                            const uint32_t *flag, hipStream_t s);
+// The same sums for ncomp components (p's tensors are the first's) where *flag is not
+// zero, nothing otherwise: a fixed grid that walks the tiles.  In the end *host gets
+// *status (host: pinned memory, or NULL).
+hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, int ncomp,
+                            const uint32_t *flag, const uint32_t *status, uint32_t *host, hipStream_t s);
 // The same over the bl.n instances of a batch (bl.params, bl.ptr), the flag of each at its ptr.aux.
-hipError_t fp64_redo_batch_launch(const BatchLaunch &bl, bool c64, bool ah, size_t lds_bytes, hipStream_t s);
+hipError_t fp64_redo_batch_launch(const BatchLaunch &bl, bool c64, bool ah, size_t lds_bytes, int ncomp,
+                                  hipStream_t s);
 hipError_t fp64_persistent_launch(const BatchLaunch &bl, bool c64, bool ah, int grid,
                                   size_t lds_bytes, hipStream_t s);
 

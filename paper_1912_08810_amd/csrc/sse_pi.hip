@@ -272,8 +272,8 @@ __global__ __launch_bounds__(kBlock, 1) void k_pi_mfma(const PiParams p)
 
     for (int k = 0; k < p.Nkz; ++k) {
         const int kx = (k + q) % p.Nkz;
-        const double2 *Xk = p.X + ((size_t)kx * p.NE * p.NA + a) * NN;
-        const double2 *Yk = p.Y + (size_t)k * p.NE * row_stride;
+        const double2 *Xk = p.X + blockIdx.y * p.x_c + ((size_t)kx * p.NE * p.NA + a) * NN;
+        const double2 *Yk = p.Y - blockIdx.y * p.x_c + (size_t)k * p.NE * row_stride;
         __syncthreads();  // the previous k's last step is done with the ring, Us and Ys
         // ring rows s_lo .. s_hi (step 0's rows); Y of step 0
         for (int x = tid; x < (s_hi - s_lo + 1) * NN; x += kBlock) {
@@ -448,15 +448,18 @@ __global__ __launch_bounds__(kBlock, 1) void k_pi_mfma(const PiParams p)
             si += red[((size_t)v * rows + tt) * cols + 2 * bij + 1];
         }
         const int b = b0 + bij / kNF, ij = bij % kNF;
-        p.Pi[((size_t)q * p.Nw + p.tw[t0 + tt]) * qw_stride + ((size_t)a * (p.NB + 1) + b) * kNF +
+        p.Pi[blockIdx.y * p.pi_c + ((size_t)q * p.Nw + p.tw[t0 + tt]) * qw_stride + ((size_t)a * (p.NB + 1) + b) * kNF +
              ij] = make_double2(p.beta_re * sr - p.beta_im * si, p.beta_re * si + p.beta_im * sr);
     }
 }
 
 // Diagonal blocks (Eq. (4)): Pi[q, w, a, NB] = -sum_b Pi[q, w, a, b], summed
 // in b order, one thread per (q, w, a, i, j).
-__global__ void k_pi_diag(double2 *Pi, int64_t nqwa, int NB)
+__global__ void k_pi_diag(double2 *Pi, int64_t nqwa, int NB, int64_t pi_c, const uint32_t *status, uint32_t *host)
 {
+    Pi += blockIdx.y * pi_c;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && host)
+        __hip_atomic_store(host, *status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= nqwa * kNF)
         return;
@@ -485,7 +488,7 @@ hipError_t launch_as(const PiParams &p, size_t lds_bytes, hipStream_t s)
         done = true;
     }
     (void)hipGetLastError();
-    hipLaunchKernelGGL((k_pi_mfma<MT, NTN>), dim3((unsigned)p.n_wg), dim3(kBlock), lds_bytes, s,
+    hipLaunchKernelGGL((k_pi_mfma<MT, NTN>), dim3((unsigned)p.n_wg, (unsigned)p.ncomp), dim3(kBlock), lds_bytes, s,
                        p);
     return hipGetLastError();
 }
@@ -515,8 +518,8 @@ hipError_t pi_launch(const PiParams &p, size_t lds_bytes, hipStream_t s)
         return e;
     const int64_t nqwa = (int64_t)p.Nqz * p.Nw * p.NA;
     const int64_t n = nqwa * kNF;
-    hipLaunchKernelGGL(k_pi_diag, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, p.Pi, nqwa,
-                       p.NB);
+    hipLaunchKernelGGL(k_pi_diag, dim3((unsigned)((n + 255) / 256), (unsigned)p.ncomp), dim3(256), 0, s, p.Pi,
+                       nqwa, p.NB, p.pi_c, p.status, p.host);
     return hipGetLastError();
 }
 

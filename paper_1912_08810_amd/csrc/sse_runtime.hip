@@ -231,11 +231,12 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 Fp64Params fp64_params(const sse_desc &d, const TileGeom &geom, const TapTable &taps);
 
 // The spectral form of one instance, every component, then the direct binary64
-// kernel that takes over if the status word's non-finite flag was raised.
-sse_status enqueue_spectral(const Instance &I, const sse_args &a, uint32_t *dstatus, bool clear, void *wsfree,
-                            hipStream_t s)
+// kernel that takes over if the non-finite flag was raised; that also delivers the
+// status word to host, pinned memory or NULL.
+sse_status enqueue_spectral(const Instance &I, const sse_args &a, uint32_t *dstatus, bool clear, uint32_t *host,
+                            void *wsfree, hipStream_t s)
 {
-    hipError_t e = spectral_sigma_launch(I.d, I.spec, I.shift, a, dstatus, clear,
+    hipError_t e = spectral_sigma_launch(I.d, I.spec, I.shift, a, dstatus, clear, host,
                                          fp64_params(I.d, I.redo_geom, I.redo_taps), I.redo_geom.lds_bytes,
                                          wsfree, s);
     return e == hipSuccess ? SSE_OK : hip_fail(e, "spectral kernel launch");
@@ -485,6 +486,38 @@ sse_status enqueue_batch(sse_plan_s *P, const sse_args *args, char *ws, uint32_t
     const int n = (int)P->inst.size();
     const sse_desc &d0 = P->inst[0].d;
     hipError_t e;
+    bool clear = true;  // the first launch clears the status word
+    for (const sse_plan_s::Wave &w : P->waves) {
+        if (w.inst.size() == 1) {
+            const int t = w.inst[0];
+            sse_status st = enqueue_spectral(P->inst[t], args[t], dstatus, clear, nullptr, ws + P->spec_off, s);
+            if (st != SSE_OK)
+                return st;
+            clear = false;
+            continue;
+        }
+        const sse_desc *dp[kMaxBatch];
+        const SpectralGeom *gp[kMaxBatch];
+        const sse_args *ap[kMaxBatch];
+        const int nw = (int)w.inst.size();
+        for (int i = 0; i < nw; ++i) {
+            dp[i] = &P->inst[w.inst[i]].d;
+            gp[i] = &P->inst[w.inst[i]].spec;
+            ap[i] = &args[w.inst[i]];
+        }
+        e = spectral_batch_launch(nw, dp, gp, ap, w.off.data(), w.hp.data(), w.d_params, w.d_redo, w.redo_lds,
+                                  dstatus, clear, ws + P->spec_off, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "spectral batch launch");
+        clear = false;
+    }
+    if (P->direct.empty())
+        return SSE_OK;  // the spectral kernels have checked their neighbour tables
+    if (clear) {
+        e = launch_clear_status(dstatus, s);
+        if (e != hipSuccess)
+            return hip_fail(e, "clear_status launch");
+    }
     {
         // every instance's neighbour table in one launch
         const int32_t *tabs[kMaxBatch];
@@ -498,28 +531,6 @@ sse_status enqueue_batch(sse_plan_s *P, const sse_args *args, char *ws, uint32_t
         e = launch_validate_neigh_batch(tabs, cnt, na, n, dstatus, s);
         if (e != hipSuccess)
             return hip_fail(e, "validate_neigh launch");
-    }
-    for (const sse_plan_s::Wave &w : P->waves) {
-        if (w.inst.size() == 1) {
-            const int t = w.inst[0];
-            sse_status st = enqueue_spectral(P->inst[t], args[t], dstatus, false, ws + P->spec_off, s);
-            if (st != SSE_OK)
-                return st;
-            continue;
-        }
-        const sse_desc *dp[kMaxBatch];
-        const SpectralGeom *gp[kMaxBatch];
-        const sse_args *ap[kMaxBatch];
-        const int nw = (int)w.inst.size();
-        for (int i = 0; i < nw; ++i) {
-            dp[i] = &P->inst[w.inst[i]].d;
-            gp[i] = &P->inst[w.inst[i]].spec;
-            ap[i] = &args[w.inst[i]];
-        }
-        e = spectral_batch_launch(nw, dp, gp, ap, w.off.data(), w.hp.data(), w.d_params, w.d_redo, w.redo_lds,
-                                  dstatus, ws + P->spec_off, s);
-        if (e != hipSuccess)
-            return hip_fail(e, "spectral batch launch");
     }
     unsigned long long *counters = (unsigned long long *)(ws + kStatusBytes);
     const size_t eb = elem_bytes(d0.prec);
@@ -720,12 +731,12 @@ static void ticket_release(const Ticket &tk)
         g_event_free.push_back(tk.ev);
 }
 
-// Copies the device status (and check sums) to the ticket's pinned block,
-// records its event and registers it.
+// Copies the device status (and check sums) to the ticket's pinned block (bytes = 0:
+// the last kernel does), records its event and registers it.
 static sse_status ticket_finish_enqueue(Ticket &tk, const void *dstatus, size_t bytes,
                                         hipStream_t s, uint64_t *ticket)
 {
-    hipError_t e = hipMemcpyAsync(tk.host_status, dstatus, bytes, hipMemcpyDeviceToHost, s);
+    hipError_t e = bytes ? hipMemcpyAsync(tk.host_status, dstatus, bytes, hipMemcpyDeviceToHost, s) : hipSuccess;
     if (e == hipSuccess)
         e = hipEventRecord(tk.ev, s);
     if (e != hipSuccess) {
@@ -828,7 +839,7 @@ sse_status sse_submit(sse_plan_t plan, const sse_args *args, void *workspace,
         return st;
     uint32_t *dstatus = (uint32_t *)workspace;
     const bool spectral = !plan->batch && plan->inst[0].spec.on && workspace_bytes >= plan->sigma_bytes;
-    hipError_t e = spectral ? hipSuccess : launch_clear_status(dstatus, s);
+    hipError_t e = spectral || plan->batch ? hipSuccess : launch_clear_status(dstatus, s);
     if (e != hipSuccess) {
         ticket_release(tk);
         return hip_fail(e, "clear_status launch");
@@ -836,14 +847,15 @@ sse_status sse_submit(sse_plan_t plan, const sse_args *args, void *workspace,
     if (plan->batch)
         st = enqueue_batch(plan, args, (char *)workspace, dstatus, s);
     else if (spectral)
-        st = enqueue_spectral(plan->inst[0], args[0], dstatus, true, (char *)workspace + kStatusBytes, s);
+        st = enqueue_spectral(plan->inst[0], args[0], dstatus, true, tk.host_status,
+                              (char *)workspace + kStatusBytes, s);
     else
         st = enqueue_instance(plan->inst[0], args[0], dstatus, (char *)workspace + kStatusBytes, s);
     if (st != SSE_OK) {
         ticket_release(tk);
         return st;
     }
-    return ticket_finish_enqueue(tk, dstatus, sizeof(uint32_t), s, ticket);
+    return ticket_finish_enqueue(tk, dstatus, spectral ? 0 : sizeof(uint32_t), s, ticket);
 }
 
 // Status of a finished submission from its device status word.
@@ -975,7 +987,7 @@ sse_status sse_compute_noalloc(sse_plan_t plan, const int32_t *neigh, const doub
     if (e != hipSuccess)
         return hip_fail(e, "clear_status launch");
     sse_args a{neigh, dH, G, Dt, Sigma};
-    st = spectral ? enqueue_spectral(plan->inst[0], a, dstatus, true, (char *)ws + kStatusBytes, s)
+    st = spectral ? enqueue_spectral(plan->inst[0], a, dstatus, true, nullptr, (char *)ws + kStatusBytes, s)
                   : enqueue_instance(plan->inst[0], a, dstatus, (char *)ws + kStatusBytes, s);
     if (st != SSE_OK)
         return st;
@@ -1033,13 +1045,16 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
     const size_t NN = (size_t)d.Norb * d.Norb;
     const size_t g_elems = (size_t)d.Nkz * d.NE * d.NA * NN;
     const size_t pi_elems = (size_t)d.Nqz * d.Nw * d.NA * (d.NB + 1) * kNF;
-    for (int c = 0; c < d.ncomp && e == hipSuccess; ++c) {
+    if (e == hipSuccess) {
         PiParams pp{};
-        pp.X = (const double2 *)G + (size_t)c * g_elems;
-        pp.Y = (const double2 *)G + (size_t)(1 - c) * g_elems;
+        pp.X = (const double2 *)G;
+        pp.Y = (const double2 *)G + g_elems;
+        pp.x_c = (int64_t)g_elems;
+        pp.pi_c = (int64_t)pi_elems;
+        pp.ncomp = d.ncomp;
         pp.dH = dH;
         pp.neigh = neigh;
-        pp.Pi = (double2 *)Pi + (size_t)c * pi_elems;
+        pp.Pi = (double2 *)Pi;
         pp.NA = d.NA;
         pp.NB = d.NB;
         pp.Norb = d.Norb;
@@ -1058,6 +1073,8 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
         memcpy(pp.ts, gm.ts, sizeof pp.ts);
         pp.n_wg = n_wg;
         pp.flag = spectral ? (const uint32_t *)wsfree : nullptr;
+        pp.status = dstatus;
+        pp.host = spectral ? tk.host_status : nullptr;
         pp.beta_re = d.alpha_re;
         pp.beta_im = d.alpha_im;
         e = pi_launch(pp, gm.lds_bytes, s);
@@ -1066,7 +1083,7 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
         ticket_release(tk);
         return hip_fail(e, "phonon kernel launch");
     }
-    return ticket_finish_enqueue(tk, dstatus, sizeof(uint32_t), s, ticket);
+    return ticket_finish_enqueue(tk, dstatus, spectral ? 0 : sizeof(uint32_t), s, ticket);
 }
 
 sse_status sse_pi_compute(sse_plan_t plan, const int32_t *neigh, const double *dH, const void *G,

@@ -37,7 +37,7 @@ struct SpectralGeom {
     // one pass holds nc components, nb energy blocks, and the sandwich's output for na atoms
     int nc = 0, nb = 0, na = 0;
     // Sigma: D^, G^ and S^ at off_d, off_g, off_s; Pi: P^, X^ and Y^ there
-    size_t off_tw = 0, off_dht = 0, off_d = 0, off_g = 0, off_s = 0, bytes = 0;
+    size_t off_dht = 0, off_d = 0, off_g = 0, off_s = 0, bytes = 0;
 };
 
 // Sizes, tables and workspace layout of one instance, as the kernels take them.
@@ -47,14 +47,13 @@ struct SpecParams {
     int32_t na_cap;             // atoms that the sandwich's output has room for
     int32_t antiherm;
     int64_t g_elems, d_elems;   // one component of G and of D~
-    int64_t off_tw, off_dht, off_d, off_g, off_s;
+    int64_t off_dht, off_d, off_g, off_s;
     double alpha_re, alpha_im;
     int32_t shift[kMaxTaps];    // the caller's shifts, in frequency order
 };
 
 // What one call works on: its tensors (of the pass's first component) and workspace.
 // Workspace: the non-finite flag, then
-//   tw   [L] exp(-2 pi i j / L), then [Nkz][Nkz] exp(-2 pi i k k' / Nkz)
 //   dht  [NA][NB][3][n][n'] = dH[a, b, j][n'][n]
 //   Dh   [components][NA][NB][9][npt]
 //   Gh   [components][blocks][NA NN][npt]
@@ -79,23 +78,25 @@ struct SpecPass {
     int64_t dst;          // and the workspace offset of the result
 };
 
+enum SpecJobs { kDht = 1, kDhat = 2, kTransform = 4 };
+
 struct SpecOne {
     SpecParams p;
     SpecPtrs t;
     SpecPass s;
     uint32_t *status;
-    int32_t clear;
+    int32_t jobs;    // of k_spec_prepare
+    int32_t clear;   // the job kDht also clears the status word
 };
 
-// Instances of a batch in one launch: instance i (params[idx[i]]) has workgroups
+// Instances of a batch in one launch: instance i (params[i]) has workgroups
 // [start[i], start[i + 1]); each is done in one pass.
 struct SpecMany {
     const SpecParams *params;
     uint32_t *status;
     int32_t n;
-    int32_t clear;
+    int32_t jobs, clear;
     int32_t start[kMaxBatch + 1];
-    uint8_t idx[kMaxBatch];
     SpecPtrs t[kMaxBatch];
 };
 
@@ -109,24 +110,25 @@ SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift);
 SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32_t *w_shift);
 
 // Sigma of every component (sse_spectral.hip), then the direct kernel (redo: its
-// sizes and taps) where the non-finite flag asks for it.  clear: the call also
-// clears the status word.  Weak: a build of the host runtime alone (its CPU test)
+// sizes and taps) where the non-finite flag asks for it.  clear: the status word
+// first; in the end it goes to *host (pinned memory, or NULL).  Weak: a build of the host runtime alone (its CPU test)
 // has no kernels to launch, and runs the direct launchers.
 __attribute__((weak)) hipError_t spectral_sigma_launch(const sse_desc &d, const SpectralGeom &g,
                                                        const int32_t *w_shift, const sse_args &a,
                                                        uint32_t *status, bool clear,
-                                                       const Fp64Params &redo, size_t redo_lds,
+                                                       uint32_t *host, const Fp64Params &redo, size_t redo_lds,
                                                        void *ws, hipStream_t s);
 
 // The instances of a batch that one pass each can do, together: geom[i], args and
 // workspace offset of each; hp are their parameters, params and redo device tables of
-// the same n instances.
+// the same n instances.  clear: the status word first.
 __attribute__((weak)) hipError_t spectral_batch_launch(int n, const sse_desc *const *d,
                                                        const SpectralGeom *const *g, const sse_args *const *a,
                                                        const size_t *ws_off, const SpecParams *hp,
                                                        const SpecParams *params,
                                                        const Fp64Params *redo, size_t redo_lds,
-                                                       uint32_t *status, char *ws, hipStream_t s);
+                                                       uint32_t *status, bool clear, char *ws,
+                                                       hipStream_t s);
 
 // Pi of every component; the non-finite flag for the direct kernel is at the start of ws.
 __attribute__((weak)) hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g,

@@ -14,11 +14,13 @@
 // kernels and 72 here, next to 24 Norb for the dH products.
 //
 // Passes (each one launch over the pass's components and energy blocks):
-//   k_spec_setup     status word, twiddle tables, dH transposed for scalar reads
-//   k_spec_dhat      D^, and the neighbour-table check
-//   k_spec_forward   G -> G^   (k and e transforms through LDS, one pass over memory)
+//   k_spec_prepare   up to three independent jobs by workgroup: dH transposed for
+//                    scalar reads (and the status word and flag cleared), D^, G -> G^
 //   k_spec_sandwich  G^, D^ -> S^
-//   k_spec_inverse   S^ -> Sigma
+//   k_spec_inverse   S^ -> Sigma, and the neighbour-table check
+//   k_sse_fp64_redo  the direct kernel, if the flag was raised
+// Twiddle factors are computed by each workgroup into LDS, so that nothing has to run
+// before the first launch.
 // G^ and S^ are laid out [atom, orbital pair][kappa][eps], points fastest, so every
 // pass reads and writes whole runs of points.  Rounding is that of binary64
 // transforms: relative to the largest values of a block, as in any sum over them.
@@ -41,7 +43,6 @@ namespace sse {
 namespace {
 
 constexpr int kSB = speck::kSandBlock;
-constexpr int kNkzReg = 8;  // momenta whose values a thread holds in registers
 
 __device__ __forceinline__ int64_t xcd_remap(int64_t bid, int64_t n)
 {
@@ -66,7 +67,6 @@ struct Job {
     int64_t bid, nwg;
 
     __device__ __forceinline__ uint32_t *flag() const { return reinterpret_cast<uint32_t *>(t.ws); }
-    __device__ __forceinline__ double2 *tw() const { return reinterpret_cast<double2 *>(t.ws + p->off_tw); }
     __device__ __forceinline__ double *dht() const { return reinterpret_cast<double *>(t.ws + p->off_dht); }
     __device__ __forceinline__ double2 *Dh() const { return reinterpret_cast<double2 *>(t.ws + p->off_d); }
     __device__ __forceinline__ double2 *Gh() const { return reinterpret_cast<double2 *>(t.ws + p->off_g); }
@@ -88,35 +88,50 @@ __device__ __forceinline__ Job job(const SpecMany &m)
             hi = mid - 1;
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
-    const_ptr<SpecParams> p = ro(m.params) + m.idx[lo];
+    const_ptr<SpecParams> p = ro(m.params) + lo;
     return Job{p, m.t[lo], SpecPass{0, p->nblk, 0, p->NA, -p->smax, p->L, p->g_elems, p->off_g}, x - m.start[lo], m.start[lo + 1] - m.start[lo]};
 }
 
-// Flag and status word, twiddle tables and dH^T; a grid-stride loop over the latter.
-template <typename A>
-__global__ void k_spec_setup(const A arg)
+// tw[j] = exp(-2 pi i j m / n) for j < count.
+__device__ __forceinline__ void fill_twiddles(double2 *tw, int count, int m, int n)
 {
-    const Job J = job(arg);
-    const auto &p = *J.p;
-    const int64_t i0 = J.bid * blockDim.x + threadIdx.x;
-    const int64_t step = J.nwg * blockDim.x;
-    if (i0 == 0) {
-        *J.flag() = 0u;
-        if (arg.clear)
-            *arg.status = 0u;
-    }
-    double2 *tw = J.tw();
-    double *dht = J.dht();
-    for (int64_t i = i0; i < p.L + p.Nkz * p.Nkz; i += step) {
-        // the angle in (-1, 1] half turns
-        const int n = i < p.L ? p.L : p.Nkz;
-        int j = i < p.L ? (int)i : (int)(((i - p.L) / p.Nkz) * ((i - p.L) % p.Nkz) % p.Nkz);
-        if (2 * j > n)
+    for (int i = threadIdx.x; i < count; i += blockDim.x) {
+        int j = (int)((int64_t)i * m % n);
+        if (2 * j > n)  // the angle in (-1, 1] half turns
             j -= n;
         double s, c;
         sincospi(2.0 * j / n, &s, &c);
         tw[i] = make_double2(c, -s);
     }
+}
+
+// Workgroups of one instance in each job.
+__host__ __device__ inline int64_t dht_wgs(const SpecParams &p)
+{
+    const int64_t n = ((int64_t)p.NA * p.NB * kN3D * p.NN + 1023) / 1024;
+    return n < 512 ? n : 512;
+}
+__host__ __device__ inline int64_t dhat_wgs(const SpecParams &p) { return (int64_t)p.NA * p.NB * p.Nkz; }
+__host__ __device__ inline int64_t fft_wgs(const SpecParams &p, int64_t atoms, int nb)
+{
+    return ((atoms * p.NN + p.C - 1) >> p.logC) * nb;
+}
+__host__ __device__ inline int64_t sandwich_wgs(const SpecParams &p, int na, int nb)
+{
+    return (int64_t)((na + 7) / 8 * 8) * p.npg * nb;
+}
+
+// dH^T, and the flag (and the status word) cleared; workgroup bid of nwg.
+__device__ __forceinline__ void dht_job(const Job &J, int64_t bid, int64_t nwg, uint32_t *clear)
+{
+    const auto &p = *J.p;
+    const int64_t i0 = bid * blockDim.x + threadIdx.x, step = nwg * blockDim.x;
+    if (i0 == 0) {
+        *J.flag() = 0u;
+        if (clear)
+            *clear = 0u;
+    }
+    double *dht = J.dht();
     const int NN = p.NN, No = p.Norb;
     const int64_t nd = (int64_t)p.NA * p.NB * kN3D * NN;
     for (int64_t i = i0; i < nd; i += step) {
@@ -126,42 +141,35 @@ __global__ void k_spec_setup(const A arg)
     }
 }
 
-// D^_ij[kappa, eps] of one (a, b) and kappa; the grid's y extent is the components.  The q sum goes
-// into LDS (a few kB), then each thread takes an eps and all nine (i, j).
-template <typename T, typename A>
-__global__ __launch_bounds__(kSB) void k_spec_dhat(const A arg)
+// D^_ij[kappa, eps] of one (a, b) and kappa: the q sum into LDS (a few kB), then each
+// thread takes an eps and all nine (i, j).
+template <typename T>
+__device__ __forceinline__ void dhat_job(const Job &J, double2 *lds, int64_t bid)
 {
-    extern __shared__ double2 lds[];
-    const Job J = job(arg);
     const auto &p = *J.p;
-    const int64_t ab = J.bid / p.Nkz;
-    if (ab >= (int64_t)p.NA * p.NB)
-        return;
-    double2 *Dk = lds;                  // [Nw][9]
-    double2 *tw = lds + p.Nw * kNF;     // [L]
-    const int kap = (int)(J.bid - ab * p.Nkz), tid = threadIdx.x;
+    const int64_t ab = bid / p.Nkz;
+    const int kap = (int)(bid - ab * p.Nkz), tid = threadIdx.x;
+    double2 *tw = lds;               // [L]
+    double2 *tq = tw + p.L;          // [Nqz]
+    double2 *Dk = tq + p.Nqz;        // [Nw][9]
     const T *D = (const T *)J.t.D + (size_t)blockIdx.y * p.d_elems;
     const int64_t slab = (int64_t)p.NA * p.NB * kNF;
-    if (kap == 0 && blockIdx.y == 0 && tid == 0) {
-        const int f = J.t.neigh[ab];
-        if (f < 0 || f >= p.NA)
-            atomicOr(arg.status, kStatusBadNeigh);
-    }
-    for (int i = tid; i < p.L; i += kSB)
-        tw[i] = J.tw()[i];
-    const double2 *twk = J.tw() + p.L + kap * p.Nkz;
-    for (int i = tid; i < p.Nw * kNF; i += kSB) {
+    fill_twiddles(tw, p.L, 1, p.L);
+    fill_twiddles(tq, p.Nqz, kap, p.Nkz);
+    __syncthreads();
+    for (int i = tid; i < p.Nw * kNF; i += blockDim.x) {
         const int w = i / kNF, ij = i - w * kNF;
         // an anti-Hermitian D~ is completed from its entries i < j and Im of the diagonal
         const int ii = ij / kN3D, jj = ij - ii * kN3D;
         const bool low = p.antiherm && ii > jj, dia = p.antiherm && ii == jj;
         const T *src = D + ((int64_t)w * slab + ab * kNF + (low ? jj * kN3D + ii : ij));
         double xr = 0.0, xi = 0.0;
+#pragma unroll 4
         for (int q = 0; q < p.Nqz; ++q) {
             double2 v = to_d2(src[(int64_t)q * p.Nw * slab]);
             if (low || dia)
                 v.x = dia ? 0.0 : -v.x;
-            const double2 t = twk[q];
+            const double2 t = tq[q];
             xr = fma(v.x, t.x, fma(-v.y, t.y, xr));
             xi = fma(v.x, t.y, fma(v.y, t.x, xi));
         }
@@ -169,7 +177,7 @@ __global__ __launch_bounds__(kSB) void k_spec_dhat(const A arg)
     }
     __syncthreads();
     double2 *out = J.Dh() + ((size_t)blockIdx.y * p.NA * p.NB + ab) * kNF * p.npt + (size_t)kap * p.L;
-    for (int e = tid; e < p.L; e += kSB) {
+    for (int e = tid; e < p.L; e += blockDim.x) {
         double ar[kNF], ai[kNF];
 #pragma unroll
         for (int x = 0; x < kNF; ++x)
@@ -207,19 +215,44 @@ __device__ __forceinline__ void second_step(double2 *lds, int rows, int rowp)
     }
 }
 
-// Sum over the Nkz rows of LDS at x (stride row) with the scalar factors w[k], conjugated if S > 0.
-template <int S>
-__device__ __forceinline__ double2 k_sum(const double2 (&v)[kNkzReg], const_ptr<double2> w, int Nkz)
+// The transform over the momenta of the N values at y (stride values apart): put(k, value).
+template <int N, int S, typename Put>
+__device__ __forceinline__ void k_transform_as(const double2 *y, size_t stride, Put put)
 {
-    double xr = 0.0, xi = 0.0;
+    double2 v[N];
 #pragma unroll
-    for (int k = 0; k < kNkzReg; ++k)
-        if (k < Nkz) {
-            const double c = w[k].x, s = -S * w[k].y;
-            xr = fma(v[k].x, c, fma(-v[k].y, s, xr));
-            xi = fma(v[k].x, s, fma(v[k].y, c, xi));
+    for (int k = 0; k < N; ++k)
+        v[k] = y[k * stride];
+    dft::transform<N, S>(v);
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+        put(k, v[k]);
+}
+template <int S, typename Put>
+__device__ __forceinline__ void k_transform(int Nkz, const double2 *y, size_t stride, const double2 *twk, Put put)
+{
+    switch (Nkz) {
+    case 1: return k_transform_as<1, S>(y, stride, put);
+    case 2: return k_transform_as<2, S>(y, stride, put);
+    case 3: return k_transform_as<3, S>(y, stride, put);
+    case 4: return k_transform_as<4, S>(y, stride, put);
+    case 5: return k_transform_as<5, S>(y, stride, put);
+    case 6: return k_transform_as<6, S>(y, stride, put);
+    case 7: return k_transform_as<7, S>(y, stride, put);
+    case 8: return k_transform_as<8, S>(y, stride, put);
+    }
+    for (int kap = 0; kap < Nkz; ++kap) {
+        double xr = 0.0, xi = 0.0;
+        int j = 0;
+        for (int k = 0; k < Nkz; ++k) {
+            const double2 v = y[k * stride], t = twk[j];
+            xr = fma(v.x, t.x, fma(S * v.y, t.y, xr));
+            xi = fma(-S * v.x, t.y, fma(v.y, t.x, xi));
+            j += kap;
+            j -= j >= Nkz ? Nkz : 0;
         }
-    return make_double2(xr, xi);
+        put(kap, make_double2(xr, xi));
+    }
 }
 
 // Transform size L = R1 R2 as n = R2 n1 + n2, eps = k1 + R1 k2: R1-point transforms
@@ -228,22 +261,25 @@ __device__ __forceinline__ double2 k_sum(const double2 (&v)[kNkzReg], const_ptr<
 // consecutive channels (64-byte pieces of each energy row) and all Nkz momenta.
 // S is the sign of the exponents: -1, or +1 for the opposite component of the phonon
 // self-energy, whose transform is wanted at the negated point.
-template <typename T, int R1, int R2, int S, typename A>
-__global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A arg)
+// LDS: [L] and [Nkz] twiddle factors, then the rows [Nkz][C].
+template <typename T, int R1, int R2, int S>
+__device__ __forceinline__ void forward_job(const Job &J, const SpecPass &s, double2 *lds, int64_t bid)
 {
-    extern __shared__ double2 lds[];
     constexpr int L = R1 * R2;
-    const Job J = job(arg);
     const auto &p = *J.p;
     const int C = p.C, NC = p.NA * p.NN, Nkz = p.Nkz, rowp = p.rowp;
     const int ngrp = (NC + C - 1) >> p.logC;
-    if (J.bid >= (int64_t)ngrp * J.s.nb)
+    if (bid >= (int64_t)ngrp * s.nb)
         return;
-    const int64_t x = xcd_remap(J.bid, (int64_t)ngrp * J.s.nb);
+    const int64_t x = xcd_remap(bid, (int64_t)ngrp * s.nb);
     const int blk = (int)(x / ngrp), ch0 = (int)(x - (int64_t)blk * ngrp) << p.logC;
-    const T *src = (const T *)J.t.G + (int64_t)blockIdx.y * J.s.src_c;
-    const double2 *tw = J.tw();
-    const int ebase = (J.s.blk0 + blk) * p.V + J.s.e_off, nrow = J.s.nrow;
+    const T *src = (const T *)J.t.G + (int64_t)blockIdx.y * s.src_c;
+    double2 *tw = lds, *twk = lds + L;
+    lds += L + Nkz;
+    fill_twiddles(tw, L, 1, L);
+    fill_twiddles(twk, Nkz, 1, Nkz);
+    __syncthreads();
+    const int ebase = (s.blk0 + blk) * p.V + s.e_off, nrow = s.nrow;
     for (int it = threadIdx.x; it < Nkz * C * R2; it += blockDim.x) {
         const int ch = it & (C - 1), r = it >> p.logC, k = r / R2, n2 = r - k * R2;
         const bool ok = ch0 + ch < NC;
@@ -251,8 +287,8 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A ar
         double2 v[R1];
 #pragma unroll
         for (int n1 = 0; n1 < R1; ++n1) {
-            const int r = n1 * R2 + n2, e = ebase + r;
-            v[n1] = ok && r < nrow && e >= 0 && e < p.NE ? to_d2(row[(int64_t)e * NC]) : make_double2(0.0, 0.0);
+            const int rr = n1 * R2 + n2, e = ebase + rr;
+            v[n1] = ok && rr < nrow && e >= 0 && e < p.NE ? to_d2(row[(int64_t)e * NC]) : make_double2(0.0, 0.0);
         }
         dft::transform<R1, S>(v);
         double2 *o = lds + (size_t)(k * C + ch) * rowp + n2;
@@ -266,44 +302,24 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_forward(const A ar
     __syncthreads();
     second_step<R1, R2, S>(lds, Nkz * C, rowp);
     __syncthreads();
-    const_ptr<double2> twk = ro(tw + L);
-    double2 *out = reinterpret_cast<double2 *>(J.t.ws + J.s.dst) + (((size_t)blockIdx.y * J.s.nb + blk) * NC + ch0) * p.npt;
+    double2 *out = reinterpret_cast<double2 *>(J.t.ws + s.dst) + (((size_t)blockIdx.y * s.nb + blk) * NC + ch0) * p.npt;
     for (int it = threadIdx.x; it < L * C; it += blockDim.x) {
         const int ch = it / L, eps = it - ch * L;
         if (ch0 + ch >= NC)
             break;
         const double2 *y = lds + (size_t)ch * rowp + (eps % R1) * (R2 + 1) + eps / R1;
         double2 *o = out + (size_t)ch * p.npt + eps;
-        if (Nkz <= kNkzReg) {
-            double2 v[kNkzReg];
-#pragma unroll
-            for (int k = 0; k < kNkzReg; ++k)
-                v[k] = k < Nkz ? y[(size_t)k * C * rowp] : make_double2(0.0, 0.0);
-            for (int kap = 0; kap < Nkz; ++kap)
-                o[(size_t)kap * L] = k_sum<S>(v, twk + kap * Nkz, Nkz);
-        } else {
-            for (int kap = 0; kap < Nkz; ++kap) {
-                double xr = 0.0, xi = 0.0;
-                for (int k = 0; k < Nkz; ++k) {
-                    const double2 v = y[(size_t)k * C * rowp];
-                    const double c = twk[kap * Nkz + k].x, s = -S * twk[kap * Nkz + k].y;
-                    xr = fma(v.x, c, fma(-v.y, s, xr));
-                    xi = fma(v.x, s, fma(v.y, c, xi));
-                }
-                o[(size_t)kap * L] = make_double2(xr, xi);
-            }
-        }
+        k_transform<S>(Nkz, y, (size_t)C * rowp, twk, [&](int kap, double2 v) { o[(size_t)kap * L] = v; });
     }
 }
 
 // The same backwards: energies from points, then k on the way out, alpha and 1 / (Nkz L).
-// An energy that no shift reaches gets an exact zero, as the direct sum gives.
-template <typename T, int R1, int R2, typename A>
-__global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_inverse(const A arg)
+// An energy that no shift reaches gets an exact zero, as the direct sum gives.  Also
+// the neighbour-table check.
+template <typename T, int R1, int R2>
+__device__ __forceinline__ void inverse_job(const Job &J, double2 *lds, uint32_t *status)
 {
-    extern __shared__ double2 lds[];
     constexpr int L = R1 * R2;
-    const Job J = job(arg);
     const auto &p = *J.p;
     const int C = p.C, NC = J.s.na * p.NN, Nkz = p.Nkz, rowp = p.rowp;
     const int64_t strideE = (int64_t)p.NA * p.NN;
@@ -312,8 +328,17 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_inverse(const A ar
         return;
     const int64_t x = xcd_remap(J.bid, (int64_t)ngrp * J.s.nb);
     const int blk = (int)(x / ngrp), ch0 = (int)(x - (int64_t)blk * ngrp) << p.logC;
-    const double2 *tw = J.tw();
+    const int64_t nab = (int64_t)p.NA * p.NB, all = (int64_t)ngrp * J.s.nb * blockDim.x;
+    if (blockIdx.y == 0)
+        for (int64_t i = J.bid * blockDim.x + threadIdx.x; i < nab; i += all)
+            if ((unsigned)J.t.neigh[i] >= (unsigned)p.NA)
+                atomicOr(status, kStatusBadNeigh);
     const double2 *src = J.Sh() + (((size_t)blockIdx.y * J.s.nb + blk) * p.na_cap * p.NN + ch0) * p.npt;
+    double2 *tw = lds, *twk = lds + L;
+    lds += L + Nkz;
+    fill_twiddles(tw, L, 1, L);
+    fill_twiddles(twk, Nkz, 1, Nkz);
+    __syncthreads();
     for (int it = threadIdx.x; it < Nkz * C * R2; it += blockDim.x) {
         const int row = it / R2, n2 = it - row * R2, ch = row & (C - 1), kap = row >> p.logC;
         const bool ok = ch0 + ch < NC;
@@ -334,7 +359,6 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_inverse(const A ar
     __syncthreads();
     second_step<R1, R2, 1>(lds, Nkz * C, rowp);
     __syncthreads();
-    const_ptr<double2> twk = ro(tw + L);
     const double sc = 1.0 / ((double)Nkz * L);
     const double ar = p.alpha_re * sc, ai = p.alpha_im * sc;
     const int e0 = (J.s.blk0 + blk) * p.V, nv = min(p.V, p.NE - e0);
@@ -349,35 +373,109 @@ __global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_inverse(const A ar
             reached = e - p.shift[w] >= 0 && e - p.shift[w] < p.NE;
         const double2 *y = lds + (size_t)ch * rowp + (vv % R1) * (R2 + 1) + vv / R1;
         T *o = dst + (int64_t)e * strideE + ch;
-        auto store = [&](int k, double2 s) {
+        k_transform<1>(Nkz, y, (size_t)C * rowp, twk, [&](int k, double2 s) {
             bad |= !(finite(s.x) && finite(s.y));
             if (reached)
                 put(o + (int64_t)k * p.NE * strideE, ar * s.x - ai * s.y, ar * s.y + ai * s.x);
             else
                 put(o + (int64_t)k * p.NE * strideE, 0.0, 0.0);
-        };
-        if (Nkz <= kNkzReg) {
-            double2 v[kNkzReg];
-#pragma unroll
-            for (int kap = 0; kap < kNkzReg; ++kap)
-                v[kap] = kap < Nkz ? y[(size_t)kap * C * rowp] : make_double2(0.0, 0.0);
-            for (int k = 0; k < Nkz; ++k)
-                store(k, k_sum<1>(v, twk + k * Nkz, Nkz));
-        } else {
-            for (int k = 0; k < Nkz; ++k) {
-                double xr = 0.0, xi = 0.0;
-                for (int kap = 0; kap < Nkz; ++kap) {
-                    const double2 v = y[(size_t)kap * C * rowp];
-                    const double c = twk[k * Nkz + kap].x, s = -twk[k * Nkz + kap].y;
-                    xr = fma(v.x, c, fma(-v.y, s, xr));
-                    xi = fma(v.x, s, fma(v.y, c, xi));
-                }
-                store(k, make_double2(xr, xi));
-            }
-        }
+        });
     }
     if (__any(bad) && (threadIdx.x & 63) == 0)
         atomicOr(J.flag(), 1u);
+}
+
+// Calls f with the integral constants R1, R2 of the transform length L.
+template <typename F>
+__host__ __device__ __forceinline__ void with_length(int L, F f)
+{
+    using std::integral_constant;
+    switch (L) {
+#define SSE_LENGTH(R1, R2)                                                     \
+    case R1 * R2:                                                              \
+        f(integral_constant<int, R1>{}, integral_constant<int, R2>{});         \
+        break;
+        SSE_LENGTH(4, 4)
+        SSE_LENGTH(4, 6)
+        SSE_LENGTH(4, 8)
+        SSE_LENGTH(6, 8)
+        SSE_LENGTH(8, 8)
+        SSE_LENGTH(8, 9)
+        SSE_LENGTH(8, 10)
+        SSE_LENGTH(8, 12)
+        SSE_LENGTH(10, 12)
+        SSE_LENGTH(12, 12)
+        SSE_LENGTH(10, 16)
+        SSE_LENGTH(12, 16)
+        SSE_LENGTH(16, 16)
+#undef SSE_LENGTH
+    }
+}
+
+// The jobs before the sandwich, as many of them as arg.jobs names: in one launch for
+// small problems, which wait for launches; D^ apart from the transforms for others,
+// whose LDS would leave its workgroups alone on a CU (one GPU's energy shard: 2.37 ms
+// together, 1.77 ms apart).  R1 = 0: the length is the instance's own (a batch).
+template <typename T, int R1, int R2, typename A>
+__global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_prepare(const A arg)
+{
+    extern __shared__ double2 lds[];
+    const Job J = job(arg);
+    const SpecParams &p = *(const SpecParams *)J.p;
+    const int64_t n0 = arg.jobs & kDht ? dht_wgs(p) : 0, n1 = n0 + (arg.jobs & kDhat ? dhat_wgs(p) : 0);
+    if (J.bid < n0) {
+        if (blockIdx.y == 0)
+            dht_job(J, J.bid, n0, arg.clear ? arg.status : nullptr);
+    } else if (J.bid < n1) {
+        dhat_job<T>(J, lds, J.bid - n0);
+    } else if constexpr (R1 > 0) {
+        forward_job<T, R1, R2, -1>(J, J.s, lds, J.bid - n1);
+    } else {
+        with_length(p.L, [&](auto r1, auto r2) {
+            forward_job<T, decltype(r1)::value, decltype(r2)::value, -1>(J, J.s, lds, J.bid - n1);
+        });
+    }
+}
+
+template <typename T, int R1, int R2, typename A>
+__global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_inverse(const A arg)
+{
+    extern __shared__ double2 lds[];
+    const Job J = job(arg);
+    if constexpr (R1 > 0)
+        inverse_job<T, R1, R2>(J, lds, arg.status);
+    else
+        with_length(J.p->L, [&](auto r1, auto r2) {
+            inverse_job<T, decltype(r1)::value, decltype(r2)::value>(J, lds, arg.status);
+        });
+}
+
+// The jobs before k_spec_pi: dH^T (first pass), then X^ and Y^ of the pass's energy blocks.
+template <int R1, int R2>
+__global__ __launch_bounds__(speck::kFftBlock, 4) void k_spec_pi_prepare(const SpecOne arg)
+{
+    extern __shared__ double2 lds[];
+    Job J = job(arg);
+    const SpecParams &p = *(const SpecParams *)J.p;
+    const int64_t n0 = arg.jobs & kDht ? dht_wgs(p) : 0, nf = fft_wgs(p, p.NA, J.s.nb);
+    SpecPass s = J.s;
+    if (J.bid < n0) {
+        if (blockIdx.y == 0)
+            dht_job(J, J.bid, n0, arg.status);
+    } else if (J.bid < n0 + nf) {
+        s.e_off = p.smin;
+        s.nrow = p.L;
+        s.src_c = p.g_elems;
+        s.dst = p.off_g;
+        forward_job<double2, R1, R2, -1>(J, s, lds, J.bid - n0);
+    } else {
+        J.t.G = J.t.D;  // the opposite component
+        s.e_off = 0;
+        s.nrow = p.V;
+        s.src_c = -p.g_elems;
+        s.dst = p.off_s;
+        forward_job<double2, R1, R2, 1>(J, s, lds, J.bid - n0 - nf);
+    }
 }
 
 // Keeps a value's computation where it stands: the compiler would otherwise sink the
@@ -763,7 +861,8 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
     const auto &p = *J.p;
     const int L = p.L, Nkz = p.Nkz, Nw = p.Nw, tid = threadIdx.x;
     double2 *tw = lds;                // [L]
-    double2 *ph = tw + L;             // [Nkz][L + 1]
+    double2 *twk = tw + L;            // [Nkz]
+    double2 *ph = twk + Nkz;          // [Nkz][L + 1]
     double2 *A = ph + Nkz * (L + 1);  // [Nkz][Nw]
     const int64_t ab = J.bid / kNF;
     const int ij = (int)(J.bid - ab * kNF);
@@ -773,8 +872,8 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
         if (f < 0 || f >= p.NA)
             atomicOr(arg.status, kStatusBadNeigh);
     }
-    for (int i = tid; i < L; i += kSB)
-        tw[i] = J.tw()[i];
+    fill_twiddles(tw, L, 1, L);
+    fill_twiddles(twk, Nkz, 1, Nkz);
     const double2 *src = J.Dh() + (((size_t)blockIdx.y * p.NA * p.NB + ab) * kNF + ij) * p.npt;
     for (int i = tid; i < p.npt; i += kSB)
         ph[i + i / L] = src[i];
@@ -803,18 +902,19 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
             A[i] = make_double2(xr, xi);
     }
     __syncthreads();
-    const_ptr<double2> twk = ro(J.tw() + L);
     double2 *Pi = (double2 *)J.t.Sigma + (size_t)blockIdx.y * p.Nqz * Nw * p.NA * (p.NB + 1) * kNF;
     const double sc = 1.0 / ((double)Nkz * L), br = p.alpha_re * sc, bi = p.alpha_im * sc;
     bool bad = false;
     for (int i = tid; i < p.Nqz * Nw; i += kSB) {
         const int q = i / Nw, w = i - q * Nw;
         double xr = 0.0, xi = 0.0;
+        int j = 0;
         for (int k = 0; k < Nkz; ++k) {
-            const double2 v = A[k * Nw + w];
-            const double c = twk[q * Nkz + k].x, s = -twk[q * Nkz + k].y;
-            xr = fma(v.x, c, fma(-v.y, s, xr));
-            xi = fma(v.x, s, fma(v.y, c, xi));
+            const double2 v = A[k * Nw + w], t = twk[j];  // t conjugated
+            xr = fma(v.x, t.x, fma(v.y, t.y, xr));
+            xi = fma(v.y, t.x, fma(-v.x, t.y, xi));
+            j += q;
+            j -= j >= Nkz ? Nkz : 0;
         }
         bad |= !(finite(xr) && finite(xi));
         Pi[(((size_t)q * Nw + w) * p.NA + a) * (p.NB + 1) * kNF + b * kNF + ij] =
@@ -841,45 +941,36 @@ struct Shape {
     size_t lds;
 };
 
-// Directions of the transforms: G to points, points to Sigma, and G to negated points.
-enum Direction { kForward, kInverse, kOpposite };
-
-template <Direction D, typename T, int R1, int R2, typename A>
-hipError_t transform_as(const A &arg, const Shape &h, hipStream_t s)
+template <typename K, typename A>
+hipError_t launch(K kernel, const A &arg, const Shape &h, bool &done, hipStream_t s)
 {
-    static bool done = false;
-    auto launch = [&](auto kernel) {
-        const hipError_t e = allow_lds(kernel, speck::kLdsOne, done);
-        if (e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL(kernel, h.grid, dim3(h.threads), h.lds, s, arg);
-        return hipGetLastError();
-    };
-    if constexpr (D == kInverse)
-        return launch(k_spec_inverse<T, R1, R2, A>);
-    else
-        return launch(k_spec_forward<T, R1, R2, D == kForward ? -1 : 1, A>);
+    const hipError_t e = allow_lds(kernel, speck::kLdsOne, done);
+    if (e != hipSuccess)
+        return e;
+    hipLaunchKernelGGL(kernel, h.grid, dim3(h.threads), h.lds, s, arg);
+    return hipGetLastError();
 }
 
-template <Direction D, typename T, typename A>
-hipError_t transform_launch(int L, const A &arg, const Shape &h, hipStream_t s)
+template <typename T>
+hipError_t prepare_launch(int L, const SpecOne &o, const Shape &h, hipStream_t s)
 {
-    switch (L) {
-    case 16: return transform_as<D, T, 4, 4>(arg, h, s);
-    case 24: return transform_as<D, T, 4, 6>(arg, h, s);
-    case 32: return transform_as<D, T, 4, 8>(arg, h, s);
-    case 48: return transform_as<D, T, 6, 8>(arg, h, s);
-    case 64: return transform_as<D, T, 8, 8>(arg, h, s);
-    case 72: return transform_as<D, T, 8, 9>(arg, h, s);
-    case 80: return transform_as<D, T, 8, 10>(arg, h, s);
-    case 96: return transform_as<D, T, 8, 12>(arg, h, s);
-    case 120: return transform_as<D, T, 10, 12>(arg, h, s);
-    case 144: return transform_as<D, T, 12, 12>(arg, h, s);
-    case 160: return transform_as<D, T, 10, 16>(arg, h, s);
-    case 192: return transform_as<D, T, 12, 16>(arg, h, s);
-    case 256: return transform_as<D, T, 16, 16>(arg, h, s);
-    }
-    return hipErrorInvalidValue;
+    hipError_t e = hipErrorInvalidValue;
+    with_length(L, [&](auto r1, auto r2) {
+        static bool done = false;
+        e = launch(k_spec_prepare<T, decltype(r1)::value, decltype(r2)::value, SpecOne>, o, h, done, s);
+    });
+    return e;
+}
+
+template <typename T>
+hipError_t inverse_launch(int L, const SpecOne &o, const Shape &h, hipStream_t s)
+{
+    hipError_t e = hipErrorInvalidValue;
+    with_length(L, [&](auto r1, auto r2) {
+        static bool done = false;
+        e = launch(k_spec_inverse<T, decltype(r1)::value, decltype(r2)::value, SpecOne>, o, h, done, s);
+    });
+    return e;
 }
 
 // Columns per block and waves per SIMD of the sandwich kernel: half the columns keep
@@ -905,16 +996,14 @@ hipError_t sandwich_launch(int norb, const A &arg, const Shape &h, hipStream_t s
     return hipErrorInvalidValue;
 }
 
-// Workgroups of one instance in each pass.
-int64_t setup_wgs(const SpecParams &p)
+size_t dhat_lds(const SpecParams &p) { return ((size_t)p.Nw * kNF + p.L + p.Nqz) * sizeof(double2); }
+int64_t prepare_wgs(const SpecParams &p, int jobs, int nb)
 {
-    const int64_t n = (int64_t)p.NA * p.NB * kN3D * p.NN + p.L + p.Nkz * p.Nkz;
-    return std::min<int64_t>((n + 255) / 256, 1024);
+    return (jobs & kDht ? dht_wgs(p) : 0) + (jobs & kDhat ? dhat_wgs(p) : 0) +
+           (jobs & kTransform ? fft_wgs(p, p.NA, nb) : 0);
 }
-int64_t dhat_wgs(const SpecParams &p) { return (int64_t)p.NA * p.NB * p.Nkz; }
-int64_t fft_wgs(const SpecParams &p, int64_t atoms, int nb) { return ((atoms * p.NN + p.C - 1) >> p.logC) * nb; }
-int64_t sandwich_wgs(const SpecParams &p, int na, int nb) { return (int64_t)((na + 7) / 8 * 8) * p.npg * nb; }
-size_t dhat_lds(const SpecParams &p) { return ((size_t)p.Nw * kNF + p.L) * sizeof(double2); }
+// Up to this many D^ workgroups go with the transforms (four to a compute unit).
+constexpr int64_t kTogether = 1024;
 
 template <typename T>
 hipError_t sigma_passes(SpecOne o, const SpectralGeom &g, hipStream_t s)
@@ -925,99 +1014,96 @@ hipError_t sigma_passes(SpecOne o, const SpectralGeom &g, hipStream_t s)
     o.s.src_c = p.g_elems;
     o.s.dst = p.off_g;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_spec_setup<SpecOne>, dim3((unsigned)setup_wgs(p)), dim3(256), 0, s, o);
-    hipError_t e = hipGetLastError();
+    hipError_t e = hipSuccess;
     const char *G = (const char *)o.t.G, *D = (const char *)o.t.D;
     char *S = (char *)o.t.Sigma;
+    const size_t plus = dhat_lds(p);
     for (int c = 0; c < p.ncomp && e == hipSuccess; c += g.nc) {
         const unsigned nc = (unsigned)std::min(g.nc, p.ncomp - c);
         o.t.G = G + (size_t)c * p.g_elems * sizeof(T);
         o.t.D = D + (size_t)c * p.d_elems * sizeof(T);
         o.t.Sigma = S + (size_t)c * p.g_elems * sizeof(T);
-        hipLaunchKernelGGL((k_spec_dhat<T, SpecOne>), dim3((unsigned)dhat_wgs(p), nc), dim3(kSB), dhat_lds(p), s, o);
-        e = hipGetLastError();
+        o.jobs = kDhat | (c == 0 ? kDht : 0);
+        if (dhat_wgs(p) * nc > kTogether) {
+            e = prepare_launch<T>(g.L, o, Shape{dim3((unsigned)prepare_wgs(p, o.jobs, 0), nc), kSB, plus}, s);
+            o.jobs = 0;
+        }
         for (o.s.blk0 = 0; o.s.blk0 < g.nblk && e == hipSuccess; o.s.blk0 += g.nb) {
             o.s.nb = std::min(g.nb, g.nblk - o.s.blk0);
-            Shape h{dim3((unsigned)fft_wgs(p, p.NA, o.s.nb), nc), (unsigned)g.fft_threads, g.fft_lds};
-            e = transform_launch<kForward, T>(g.L, o, h, s);
+            o.jobs |= kTransform;
+            const bool with = o.jobs & kDhat;
+            Shape h{dim3((unsigned)prepare_wgs(p, o.jobs, o.s.nb), nc),
+                    (unsigned)(with ? std::max(g.fft_threads, kSB) : g.fft_threads),
+                    with ? std::max(g.fft_lds, plus) : g.fft_lds};
+            e = prepare_launch<T>(g.L, o, h, s);
+            o.jobs = 0;
             for (o.s.a0 = 0; o.s.a0 < p.NA && e == hipSuccess; o.s.a0 += g.na) {
                 o.s.na = std::min(g.na, p.NA - o.s.a0);
                 e = sandwich_launch<1>(p.Norb, o, Shape{dim3((unsigned)sandwich_wgs(p, o.s.na, o.s.nb), nc), kSB,
                                                         g.sand_lds}, s);
-                h.grid.x = (unsigned)fft_wgs(p, o.s.na, o.s.nb);
                 if (e == hipSuccess)
-                    e = transform_launch<kInverse, T>(g.L, o, h, s);
+                    e = inverse_launch<T>(g.L, o, Shape{dim3((unsigned)fft_wgs(p, o.s.na, o.s.nb), nc),
+                                                        (unsigned)g.fft_threads, g.fft_lds}, s);
             }
         }
     }
     return e;
 }
 
-// A launch over the instances of m that want() takes, count() workgroups each (rounded
-// up to the eight XCDs); *any is whether there were some.
-template <typename Want, typename Count>
-unsigned lay_out(SpecMany *m, const SpecMany &all, Want want, Count count)
+// Lays out count(i) workgroups of each instance (rounded up to the eight XCDs).
+template <typename Count>
+unsigned lay_out(SpecMany *m, Count count)
 {
-    m->n = 0;
     m->start[0] = 0;
-    for (int i = 0; i < all.n; ++i)
-        if (want(i)) {
-            m->idx[m->n] = (uint8_t)i;
-            m->t[m->n] = all.t[i];
-            m->start[m->n + 1] = m->start[m->n] + (int32_t)((count(i) + 7) / 8 * 8);
-            ++m->n;
-        }
+    for (int i = 0; i < m->n; ++i)
+        m->start[i + 1] = m->start[i] + (int32_t)((count(i) + 7) / 8 * 8);
     return (unsigned)m->start[m->n];
 }
 
 template <typename T>
-hipError_t sigma_batch(const SpecMany &all, const SpecParams *hp, const SpectralGeom *const *g, hipStream_t s)
+hipError_t sigma_batch(SpecMany m, const SpecParams *hp, const SpectralGeom *const *g, hipStream_t s)
 {
     const unsigned nc = (unsigned)hp[0].ncomp;
-    auto every = [](int) { return true; };
-    SpecMany m = all;
-    (void)hipGetLastError();
-    unsigned x = lay_out(&m, all, every, [&](int i) { return setup_wgs(hp[i]); });
-    hipLaunchKernelGGL(k_spec_setup<SpecMany>, dim3(x), dim3(256), 0, s, m);
+    Shape h{dim3(0, nc), kSB, 0};
     size_t lds = 0;
-    for (int i = 0; i < all.n; ++i)
+    for (int i = 0; i < m.n; ++i) {
+        h.threads = std::max(h.threads, (unsigned)g[i]->fft_threads);
+        h.lds = std::max(h.lds, g[i]->fft_lds);
         lds = std::max(lds, dhat_lds(hp[i]));
-    x = lay_out(&m, all, every, [&](int i) { return dhat_wgs(hp[i]); });
-    hipLaunchKernelGGL((k_spec_dhat<T, SpecMany>), dim3(x, nc), dim3(kSB), lds, s, m);
-    hipError_t e = hipGetLastError();
-    auto transforms = [&](bool fwd) {
-        bool done[kMaxBatch] = {};
-        for (int i = 0; i < all.n && e == hipSuccess; ++i) {
-            if (done[i])
-                continue;
-            Shape h{dim3(0, nc), 0, 0};
-            h.grid.x = lay_out(&m, all,
-                               [&](int j) {
-                                   if (g[j]->L != g[i]->L)
-                                       return false;
-                                   done[j] = true;
-                                   h.threads = std::max(h.threads, (unsigned)g[j]->fft_threads);
-                                   h.lds = std::max(h.lds, g[j]->fft_lds);
-                                   return true;
-                               },
-                               [&](int j) { return fft_wgs(hp[j], hp[j].NA, hp[j].nblk); });
-            e = fwd ? transform_launch<kForward, T>(g[i]->L, m, h, s) : transform_launch<kInverse, T>(g[i]->L, m, h, s);
-        }
+    }
+    static bool d0 = false, d1 = false;
+    int64_t dhat = 0;
+    for (int i = 0; i < m.n; ++i)
+        dhat += dhat_wgs(hp[i]);
+    auto prepare = [&](int jobs, unsigned threads, size_t bytes) {
+        m.jobs = jobs;
+        const unsigned x = lay_out(&m, [&](int i) { return prepare_wgs(hp[i], jobs, hp[i].nblk); });
+        return launch(k_spec_prepare<T, 0, 0, SpecMany>, m, Shape{dim3(x, nc), threads, bytes}, d0, s);
     };
-    transforms(true);
+    (void)hipGetLastError();
+    hipError_t e;
+    if (dhat * nc > kTogether) {
+        e = prepare(kDht | kDhat, kSB, lds);
+        if (e == hipSuccess)
+            e = prepare(kTransform, h.threads, h.lds);
+    } else {
+        e = prepare(kDht | kDhat | kTransform, h.threads, std::max(h.lds, lds));
+    }
     if (e != hipSuccess)
         return e;
-    x = lay_out(&m, all, every, [&](int i) { return sandwich_wgs(hp[i], hp[i].NA, hp[i].nblk); });
-    e = sandwich_launch<1>(hp[0].Norb, m, Shape{dim3(x, nc), kSB, g[0]->sand_lds}, s);
-    transforms(false);
-    return e;
+    h.grid.x = lay_out(&m, [&](int i) { return sandwich_wgs(hp[i], hp[i].NA, hp[i].nblk); });
+    e = sandwich_launch<1>(hp[0].Norb, m, Shape{h.grid, kSB, g[0]->sand_lds}, s);
+    if (e != hipSuccess)
+        return e;
+    h.grid.x = lay_out(&m, [&](int i) { return fft_wgs(hp[i], hp[i].NA, hp[i].nblk); });
+    return launch(k_spec_inverse<T, 0, 0, SpecMany>, m, h, d1, s);
 }
 
 }  // namespace
 
 hipError_t spectral_sigma_launch(const sse_desc &d, const SpectralGeom &g, const int32_t *w_shift,
-                                 const sse_args &a, uint32_t *status, bool clear, const Fp64Params &redo,
-                                 size_t redo_lds, void *ws, hipStream_t s)
+                                 const sse_args &a, uint32_t *status, bool clear, uint32_t *host,
+                                 const Fp64Params &redo, size_t redo_lds, void *ws, hipStream_t s)
 {
     SpecOne o{};
     o.p = spectral_params(d, g, w_shift);
@@ -1025,49 +1111,40 @@ hipError_t spectral_sigma_launch(const sse_desc &d, const SpectralGeom &g, const
     o.status = status;
     o.clear = clear;
     const bool c64 = d.prec != SSE_FP64;
-    const size_t eb = c64 ? 8 : 16;
     hipError_t e = c64 ? sigma_passes<float2>(o, g, s) : sigma_passes<double2>(o, g, s);
-    for (int c = 0; c < d.ncomp && e == hipSuccess; ++c) {
-        Fp64Params r = redo;
-        r.neigh = a.neigh;
-        r.dH = a.dH;
-        r.G = (const char *)a.G + (size_t)c * o.p.g_elems * eb;
-        r.D = (const char *)a.Dt + (size_t)c * o.p.d_elems * eb;
-        r.Sigma = (char *)a.Sigma + (size_t)c * o.p.g_elems * eb;
-        e = fp64_redo_launch(r, c64, d.dt_antiherm != 0, redo_lds, (const uint32_t *)ws, s);
-    }
-    return e;
+    if (e != hipSuccess)
+        return e;
+    Fp64Params r = redo;
+    r.neigh = a.neigh;
+    r.dH = a.dH;
+    r.G = a.G;
+    r.D = a.Dt;
+    r.Sigma = a.Sigma;
+    return fp64_redo_launch(r, c64, d.dt_antiherm != 0, redo_lds, d.ncomp, (const uint32_t *)ws, status, host, s);
 }
 
 hipError_t spectral_batch_launch(int n, const sse_desc *const *d, const SpectralGeom *const *g,
                                  const sse_args *const *a, const size_t *ws_off, const SpecParams *hp,
                                  const SpecParams *params, const Fp64Params *redo, size_t redo_lds,
-                                 uint32_t *status, char *ws, hipStream_t s)
+                                 uint32_t *status, bool clear, char *ws, hipStream_t s)
 {
     if (n < 1 || n > kMaxBatch)
         return hipErrorInvalidValue;
     SpecMany m{};
     m.params = params;
     m.status = status;
+    m.clear = clear;
     m.n = n;
-    for (int i = 0; i < n; ++i)
-        m.t[i] = SpecPtrs{a[i]->neigh, a[i]->dH, a[i]->G, a[i]->Dt, a[i]->Sigma, ws + ws_off[i]};
-    const bool c64 = d[0]->prec != SSE_FP64;
-    hipError_t e = c64 ? sigma_batch<float2>(m, hp, g, s) : sigma_batch<double2>(m, hp, g, s);
-    if (e != hipSuccess)
-        return e;
     BatchLaunch bl{};
     bl.params = redo;
     bl.n = n;
-    const size_t eb = c64 ? 8 : 16;
-    for (int c = 0; c < d[0]->ncomp && e == hipSuccess; ++c) {
-        for (int i = 0; i < n; ++i)
-            bl.ptr[i] = TensorPtrs{a[i]->neigh, a[i]->dH, (const char *)a[i]->G + (size_t)c * hp[i].g_elems * eb,
-                                   (const char *)a[i]->Dt + (size_t)c * hp[i].d_elems * eb,
-                                   (char *)a[i]->Sigma + (size_t)c * hp[i].g_elems * eb, m.t[i].ws};
-        e = fp64_redo_batch_launch(bl, c64, d[0]->dt_antiherm != 0, redo_lds, s);
+    for (int i = 0; i < n; ++i) {
+        m.t[i] = SpecPtrs{a[i]->neigh, a[i]->dH, a[i]->G, a[i]->Dt, a[i]->Sigma, ws + ws_off[i]};
+        bl.ptr[i] = TensorPtrs{a[i]->neigh, a[i]->dH, a[i]->G, a[i]->Dt, a[i]->Sigma, m.t[i].ws};
     }
-    return e;
+    const bool c64 = d[0]->prec != SSE_FP64;
+    hipError_t e = c64 ? sigma_batch<float2>(m, hp, g, s) : sigma_batch<double2>(m, hp, g, s);
+    return e != hipSuccess ? e : fp64_redo_batch_launch(bl, c64, d[0]->dt_antiherm != 0, redo_lds, d[0]->ncomp, s);
 }
 
 namespace {
@@ -1101,45 +1178,36 @@ hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g, const in
     o.p = spectral_params(d, g, w_shift);
     o.t = SpecPtrs{neigh, dH, nullptr, nullptr, nullptr, (char *)ws};
     o.status = status;
+    o.jobs = kDht;
     o.clear = 1;
     const SpecParams &p = o.p;
     const size_t pi_elems = (size_t)d.Nqz * d.Nw * d.NA * (d.NB + 1) * kNF;
-    const size_t out_lds = ((size_t)g.L + (size_t)d.Nkz * (g.L + 1) + (size_t)d.Nkz * d.Nw) * sizeof(double2);
-    static bool done = false;
-    hipError_t e = allow_lds(k_spec_pi_out, speck::kLdsOne, done);
-    if (e != hipSuccess)
-        return e;
+    const size_t out_lds = ((size_t)g.L + d.Nkz + (size_t)d.Nkz * (g.L + 1) + (size_t)d.Nkz * d.Nw) * sizeof(double2);
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_spec_setup<SpecOne>, dim3((unsigned)setup_wgs(p)), dim3(256), 0, s, o);
-    e = hipGetLastError();
+    hipError_t e = hipSuccess;
     const double2 *Gc = (const double2 *)G;
     for (int c = 0; c < d.ncomp && e == hipSuccess; c += g.nc) {
         const unsigned nc = (unsigned)std::min(g.nc, d.ncomp - c);
+        o.t.G = Gc + (size_t)c * p.g_elems;
+        o.t.D = Gc + (size_t)(1 - c) * p.g_elems;
         for (o.s.blk0 = 0; o.s.blk0 < g.nblk && e == hipSuccess; o.s.blk0 += g.nb) {
             o.s.nb = std::min(g.nb, g.nblk - o.s.blk0);
-            const Shape h{dim3((unsigned)fft_wgs(p, p.NA, o.s.nb), nc), (unsigned)g.fft_threads, g.fft_lds};
-            o.t.G = Gc + (size_t)c * p.g_elems;
-            o.s.e_off = p.smin;
-            o.s.nrow = p.L;
-            o.s.src_c = p.g_elems;
-            o.s.dst = p.off_g;
-            e = transform_launch<kForward, double2>(g.L, o, h, s);
-            if (e != hipSuccess)
-                break;
-            o.t.G = Gc + (size_t)(1 - c) * p.g_elems;
-            o.s.e_off = 0;
-            o.s.nrow = p.V;
-            o.s.src_c = -p.g_elems;
-            o.s.dst = p.off_s;
-            e = transform_launch<kOpposite, double2>(g.L, o, h, s);
+            const int64_t n = (o.jobs & kDht ? dht_wgs(p) : 0) + 2 * fft_wgs(p, p.NA, o.s.nb);
+            const Shape h{dim3((unsigned)n, nc), (unsigned)g.fft_threads, g.fft_lds};
+            e = hipErrorInvalidValue;
+            with_length(g.L, [&](auto r1, auto r2) {
+                static bool done = false;
+                e = launch(k_spec_pi_prepare<decltype(r1)::value, decltype(r2)::value>, o, h, done, s);
+            });
             if (e == hipSuccess)
                 e = pi_sandwich_launch<1>(o, Shape{dim3((unsigned)sandwich_wgs(p, p.NA, 1), nc), kSB, g.sand_lds}, s);
+            o.jobs = 0;
         }
         if (e != hipSuccess)
             break;
         o.t.Sigma = (double2 *)Pi + (size_t)c * pi_elems;
-        hipLaunchKernelGGL(k_spec_pi_out, dim3((unsigned)(d.NA * d.NB * kNF), nc), dim3(kSB), out_lds, s, o);
-        e = hipGetLastError();
+        static bool done = false;
+        e = launch(k_spec_pi_out, o, Shape{dim3((unsigned)(d.NA * d.NB * kNF), nc), kSB, out_lds}, done, s);
     }
     return e;
 }

@@ -42,23 +42,23 @@ int main()
         for (int w = 0; w < Nw; ++w)
             NEED(g.smax - s[w] >= 0 && g.smax - s[w] + g.V <= g.L);
         NEED(g.C == 1 << g.logC && g.rowp >= (g.r1 - 1) * (g.r2 + 1) + g.r2);
-        NEED((size_t)Nkz * g.C * g.rowp * 16 == g.fft_lds && g.fft_lds <= speck::kLdsOne);
+        NEED(((size_t)g.L + Nkz + (size_t)Nkz * g.C * g.rowp) * 16 == g.fft_lds && g.fft_lds <= speck::kLdsOne);
         NEED(g.fft_threads % 64 == 0 && g.fft_threads >= 64 && g.fft_threads <= speck::kFftBlock);
         NEED(g.P == speck::kSandBlock / Norb && g.P * g.npg >= g.npt && g.P * (g.npg - 1) < g.npt);
         NEED(g.sand_lds == NN * g.P * 16 + 3 * NN * 8 && g.sand_lds <= speck::kLdsOne);
         NEED(g.nc >= 1 && g.nc <= ncomp && g.nb >= 1 && g.nb <= g.nblk && g.na >= 1 && g.na <= NA);
-        NEED(g.off_tw >= 256 && g.off_dht >= g.off_tw + (g.L + (size_t)Nkz * Nkz) * 16);
+        NEED(g.off_dht >= 256 && ((size_t)Nw * 9 + g.L + d.Nqz) * 16 <= speck::kLdsOne);
         NEED(g.off_d >= g.off_dht + NA * NB * 3 * NN * 8);
         NEED(g.off_g >= g.off_d + g.nc * ((size_t)NA * NB * 9 * row));
         NEED(g.off_s >= g.off_g + (size_t)g.nc * g.nb * NA * NN * row);
         NEED(g.bytes >= g.off_s + (size_t)g.nc * g.nb * g.na * NN * row);
-        NEED(g.bytes <= speck::kHardBytes && ((g.off_tw | g.off_dht | g.off_d | g.off_g | g.off_s) & 15) == 0);
+        NEED(g.bytes <= speck::kHardBytes && ((g.off_dht | g.off_d | g.off_g | g.off_s) & 15) == 0);
         if (SpectralGeom h = spectral_pi_geometry(d, s.data()); h.on) {
             ++pi;
             const size_t hrow = (size_t)h.npt * 16;
             NEED(prec == 0 && h.V * h.nblk >= NE && h.npt == Nkz * h.L && h.na == NA);
             NEED(h.sand_lds >= (size_t)std::max(Norb, 9) * Norb * h.P * 16 + 3 * NN * 8 && h.sand_lds <= speck::kLdsOne);
-            NEED(((size_t)h.L + (size_t)Nkz * (h.L + 1 + Nw)) * 16 <= speck::kLdsOne);
+            NEED(((size_t)h.L + (size_t)Nkz * (h.L + 2 + Nw)) * 16 <= speck::kLdsOne);
             NEED(h.off_g >= h.off_d + h.nc * ((size_t)NA * NB * 9 * hrow));
             NEED(h.off_s >= h.off_g + (size_t)h.nc * h.nb * NA * NN * hrow);
             NEED(h.bytes >= h.off_s + (size_t)h.nc * h.nb * NA * NN * hrow && h.bytes <= speck::kHardBytes);
