@@ -269,12 +269,16 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 }
 
 // The cheapest transform length whose pass fits: points computed, weighted by what
-// pieces of under 64 bytes and one workgroup per CU cost the transforms.
+// the transforms lose.  Of the whole call at Nkz 7, Norb 10, NB 4, complex128, L 256 and
+// 288 against 160: one workgroup per CU (64-byte pieces, 115 kB of LDS) 4 % per point,
+// 32-byte pieces (two workgroups, 57 kB) 11 %.  Device scale: L 288 in 4 blocks 81.4 ms,
+// L 160 in 8 (a ninth more points) 85.0 ms.
 template <typename Layout>
 SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, Layout layout)
 {
-    static const int kSizes[][2] = {{4, 4}, {4, 6}, {4, 8}, {6, 8}, {8, 8}, {8, 9}, {8, 10},
-                                    {8, 12}, {10, 12}, {12, 12}, {10, 16}, {12, 16}, {16, 16}};
+#define SSE_LENGTH(R1, R2) {R1, R2},
+    static const int kSizes[][2] = {SSE_SPECTRAL_LENGTHS(SSE_LENGTH)};
+#undef SSE_LENGTH
     SpectralGeom best;
     if (d.Norb > speck::kMaxNorb || d.Nkz > 64)
         return best;
@@ -318,8 +322,8 @@ SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, Layout lay
             if (!layout(d, speck::kSoftBytes, &g) && !layout(d, speck::kHardBytes, &g))
                 continue;
             const int piece = g.C * (c64 ? 8 : 16);
-            const double cost = (double)g.nblk * g.L * (1.0 + (piece < 64 ? 0.15 : 0.0) + (piece < 32 ? 0.3 : 0.0) +
-                                                        (g.fft_lds > speck::kLdsTwo ? 0.1 : 0.0));
+            const double cost = (double)g.nblk * g.L * (1.0 + (piece < 64 ? 0.11 : 0.0) + (piece < 32 ? 0.3 : 0.0) +
+                                                        (g.fft_lds > speck::kLdsTwo ? 0.04 : 0.0));
             if (best_cost == 0.0 || cost < best_cost) {
                 best_cost = cost;
                 best = g;

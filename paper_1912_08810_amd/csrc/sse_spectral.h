@@ -15,6 +15,12 @@ constexpr size_t kLdsTwo = 79 * 1024;   // LDS of a workgroup when two share a C
 constexpr size_t kLdsOne = 158 * 1024;  // LDS of a workgroup alone on a CU
 constexpr int kMaxNorb = 16;        // orbitals that the sandwich kernel is built for
 constexpr size_t kAlign = 256;
+// Transform lengths R1 R2 that the kernels are built for: X(R1, R2).  Close enough that
+// the last energy block is rarely much larger than its energies; up to two factors that
+// fit a thread's registers (18 complex values).
+#define SSE_SPECTRAL_LENGTHS(X)                                                          \
+    X(4, 4) X(4, 6) X(4, 8) X(6, 8) X(8, 8) X(8, 9) X(8, 10) X(8, 12) X(10, 12)          \
+    X(12, 12) X(10, 16) X(12, 15) X(12, 16) X(14, 16) X(15, 16) X(16, 16) X(16, 18)
 // Workspace: what a pass may hold beside its D~ and one energy block of G (soft),
 // and the most a plan asks for (hard; above it the direct kernels run).
 constexpr size_t kSoftBytes = (size_t)5 << 30;

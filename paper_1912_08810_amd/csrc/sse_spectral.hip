@@ -395,19 +395,7 @@ __host__ __device__ __forceinline__ void with_length(int L, F f)
     case R1 * R2:                                                              \
         f(integral_constant<int, R1>{}, integral_constant<int, R2>{});         \
         break;
-        SSE_LENGTH(4, 4)
-        SSE_LENGTH(4, 6)
-        SSE_LENGTH(4, 8)
-        SSE_LENGTH(6, 8)
-        SSE_LENGTH(8, 8)
-        SSE_LENGTH(8, 9)
-        SSE_LENGTH(8, 10)
-        SSE_LENGTH(8, 12)
-        SSE_LENGTH(10, 12)
-        SSE_LENGTH(12, 12)
-        SSE_LENGTH(10, 16)
-        SSE_LENGTH(12, 16)
-        SSE_LENGTH(16, 16)
+        SSE_SPECTRAL_LENGTHS(SSE_LENGTH)
 #undef SSE_LENGTH
     }
 }

@@ -36,7 +36,7 @@ int main()
             continue;
         ++on;
         const size_t NN = (size_t)Norb * Norb, row = (size_t)g.npt * 16;
-        NEED(Norb <= speck::kMaxNorb && g.L == g.r1 * g.r2 && g.L <= 256 && g.npt == Nkz * g.L);
+        NEED(Norb <= speck::kMaxNorb && g.L == g.r1 * g.r2 && g.L <= 288 && g.npt == Nkz * g.L);
         NEED(g.V == g.L - (g.smax - g.smin) && g.V >= 1);
         NEED(g.V * g.nblk >= NE && g.V * (g.nblk - 1) < NE);
         for (int w = 0; w < Nw; ++w)

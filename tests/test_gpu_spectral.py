@@ -50,6 +50,11 @@ CASES = {
                       shift=(17, -9, 4, 4, 31, -20, 0, 11)), 0),
     "complex64": (P(NA=9, NB=4, Norb=10, Nkz=5, Nqz=5, NE=205, Nw=25), 3),
     "complex64_odd": (P(NA=9, NB=3, Norb=5, Nkz=3, Nqz=3, NE=83, Nw=11), 3),
+    "length_180": (P(NA=6, NB=3, Norb=4, Nkz=3, Nqz=3, NE=178, Nw=3), 0),
+    "length_224": (P(NA=6, NB=3, Norb=4, Nkz=3, Nqz=3, NE=222, Nw=3), 0),
+    "length_240": (P(NA=6, NB=3, Norb=4, Nkz=3, Nqz=3, NE=238, Nw=3), 0),
+    "length_288": (P(NA=6, NB=3, Norb=4, Nkz=3, Nqz=3, NE=286, Nw=3), 0),
+    "length_288_alone_on_cu": (P(NA=6, NB=3, Norb=5, Nkz=7, Nqz=7, NE=286, Nw=3), 0),
     "bf16x3_large": (P(NA=100, NB=4, Norb=10, Nkz=5, Nqz=5, NE=200, Nw=20), 2),
 }
 
@@ -164,6 +169,8 @@ PI_CASES = {
     "norb_13_ragged_columns": P(NA=7, NB=4, Norb=13, Nkz=3, Nqz=3, NE=61, Nw=9),
     "norb_16": P(NA=7, NB=4, Norb=16, Nkz=3, Nqz=3, NE=61, Nw=9),
     "signed_gaps": P(NA=8, NB=4, Norb=10, Nkz=5, Nqz=5, NE=66, Nw=8, shift=(17, -9, 4, 4, 31, -20, 0, 11)),
+    "length_180": P(NA=6, NB=3, Norb=4, Nkz=3, Nqz=3, NE=178, Nw=3),
+    "length_288": P(NA=6, NB=3, Norb=4, Nkz=7, Nqz=7, NE=286, Nw=3),
 }
 
 
