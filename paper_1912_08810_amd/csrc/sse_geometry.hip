@@ -199,6 +199,7 @@ SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32
     p.nblk = g.nblk;
     p.na_cap = g.na;
     p.antiherm = d.dt_antiherm;
+    p.matrix = g.matrix;
     p.g_elems = (int64_t)d.Nkz * d.NE * d.NA * p.NN;
     p.d_elems = (int64_t)d.Nqz * d.Nw * d.NA * d.NB * kNF;
     p.off_dht = (int64_t)g.off_dht;
@@ -274,7 +275,7 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 // 32-byte pieces (two workgroups, 57 kB) 11 %.  Device scale: L 288 in 4 blocks 81.4 ms,
 // L 160 in 8 (a ninth more points) 85.0 ms.
 template <typename Layout>
-SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, Layout layout)
+SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, bool matrix, Layout layout)
 {
 #define SSE_LENGTH(R1, R2) {R1, R2},
     static const int kSizes[][2] = {SSE_SPECTRAL_LENGTHS(SSE_LENGTH)};
@@ -304,9 +305,17 @@ SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, Layout lay
             continue;
         g.nblk = (d.NE + g.V - 1) / g.V;
         g.npt = d.Nkz * g.L;
-        g.P = speck::kSandBlock / d.Norb;
+        // the matrix form walks its points in rounds of 16, so that a workgroup's start is
+        // paid once; rounds as long as 2048 workgroups remain (one GPU's energy shard:
+        // 4.53, 4.11 and 4.03 ms per component with 16, 32 and 64 points)
+        g.matrix = matrix;
+        g.P = matrix ? 16 : speck::kSandBlock / d.Norb;
+        while (matrix && g.P < 64 && 2 * g.P <= g.npt && d.NB * speck::matrix_bytes(d.Norb, 2 * g.P) <= speck::kLdsTwo &&
+               (int64_t)d.NA * d.ncomp * g.nblk * (g.npt / (2 * g.P)) >= 2048)
+            g.P *= 2;
         g.npg = (g.npt + g.P - 1) / g.P;
-        g.sand_lds = (size_t)NN * g.P * 16 + kN3D * NN * 8;
+        g.sand_lds = matrix ? speck::matrix_bytes(d.Norb, g.P) * std::min(d.NB, speck::matrix_neighbours(d.Norb))
+                            : (size_t)NN * g.P * 16 + kN3D * NN * 8;
         for (g.logC = 1; g.logC <= 3; ++g.logC) {
             g.C = 1 << g.logC;
             // the rows of a momentum's C channels start 16 / C sixteen-byte banks apart
@@ -354,7 +363,7 @@ SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift)
     // an explicit tile shape asks for the direct kernel that has tiles
     if (d.tile_e > 0 || d.chunk_taps > 0)
         return SpectralGeom();
-    const SpectralGeom g = best_geometry(d, w_shift, spectral_layout);
+    const SpectralGeom g = best_geometry(d, w_shift, speck::matrix_form(d.Norb), spectral_layout);
     if (!g.on)
         return g;
     const double flops = direct_flops(d);
@@ -368,7 +377,7 @@ SpectralGeom spectral_pi_geometry(const sse_desc &d, const int32_t *w_shift)
 {
     if (d.prec != SSE_FP64)
         return SpectralGeom();
-    SpectralGeom g = best_geometry(d, w_shift, spectral_pi_layout);
+    SpectralGeom g = best_geometry(d, w_shift, false, spectral_pi_layout);
     if (!g.on)
         return g;
     // the sum over a point's rows reuses the Y^ region for nine values per lane

@@ -25,6 +25,21 @@ constexpr size_t kAlign = 256;
 // and the most a plan asks for (hard; above it the direct kernels run).
 constexpr size_t kSoftBytes = (size_t)5 << 30;
 constexpr size_t kHardBytes = (size_t)8 << 30;
+// The matrix form of the sandwich works in tiles of four orbitals, the row form on one
+// row per lane.  Measured at NA 256, NB 4, NE 270, Nkz 3 (NA 12, NE 60), us per call,
+// row / matrix form: Norb 4 179 / 185 (48 / 43), 5 269 / 399, 6 374 / 403 (55 / 43),
+// 7 531 / 497, 8 650 / 547, 9 892 / 1002, 10 1070 / 996 (77 / 56), 11 1485 / 1163,
+// 12 1741 / 1278 (86 / 59).  Above 12 its registers spill (16: 3285 / 5011).
+constexpr bool matrix_form(int No) { return No == 4 || No == 7 || No == 8 || (No >= 10 && No <= 12); }
+// Tiles of 4 x 4 values of dH per neighbour in LDS; bytes per neighbour with the D^ of P
+// points; the most neighbours that are staged at once.
+constexpr int matrix_tiles(int No)
+{
+    const int T = (No + 3) / 4;
+    return kN3D * T * T + (No % 4 == 2 ? 2 * T : 0);
+}
+constexpr size_t matrix_bytes(int No, int P) { return (size_t)matrix_tiles(No) * 128 + (size_t)kNF * P * 16; }
+constexpr int matrix_neighbours(int No) { return (int)(kLdsTwo / matrix_bytes(No, 16)); }
 }  // namespace speck
 
 // Geometry and workspace layout of the spectral form of one instance.
@@ -38,6 +53,7 @@ struct SpectralGeom {
     size_t fft_lds = 0;
     int smin = 0, smax = 0;
     int npt = 0;                 // transform points per block: Nkz L
+    bool matrix = false;         // which form of the sandwich
     int P = 0, npg = 0;          // points per sandwich workgroup, groups of them
     size_t sand_lds = 0;
     // one pass holds nc components, nb energy blocks, and the sandwich's output for na atoms
@@ -51,7 +67,7 @@ struct SpecParams {
     int32_t NA, NB, Norb, NN, Nkz, Nqz, NE, Nw, ncomp;
     int32_t L, V, C, logC, rowp, npt, P, npg, smin, smax, nblk;
     int32_t na_cap;             // atoms that the sandwich's output has room for
-    int32_t antiherm;
+    int32_t antiherm, matrix;
     int64_t g_elems, d_elems;   // one component of G and of D~
     int64_t off_dht, off_d, off_g, off_s;
     double alpha_re, alpha_im;
@@ -60,7 +76,7 @@ struct SpecParams {
 
 // What one call works on: its tensors (of the pass's first component) and workspace.
 // Workspace: the non-finite flag, then
-//   dht  [NA][NB][3][n][n'] = dH[a, b, j][n'][n]
+//   dht  [NA][NB][3][n][n'] = dH[a, b, j][n'][n] (not written for the matrix form)
 //   Dh   [components][NA][NB][9][npt]
 //   Gh   [components][blocks][NA NN][npt]
 //   Sh   [components][blocks][na_cap NN][npt]

@@ -16,7 +16,7 @@
 // Passes (each one launch over the pass's components and energy blocks):
 //   k_spec_prepare   up to three independent jobs by workgroup: dH transposed for
 //                    scalar reads (and the status word and flag cleared), D^, G -> G^
-//   k_spec_sandwich  G^, D^ -> S^
+//   k_spec_sandwich  G^, D^ -> S^ (k_spec_matrix for the Norb that speck::matrix_form names)
 //   k_spec_inverse   S^ -> Sigma, and the neighbour-table check
 //   k_sse_fp64_redo  the direct kernel, if the flag was raised
 // Twiddle factors are computed by each workgroup into LDS, so that nothing has to run
@@ -25,8 +25,8 @@
 // pass reads and writes whole runs of points.  Rounding is that of binary64
 // transforms: relative to the largest values of a block, as in any sum over them.
 // Device scale (NA = 1024, NB = 4, Norb = 10, Nkz = Nqz = 7, NE = 1000, Nw = 30, both
-// components, complex128): 1609 ms per call in the direct kernel, 84 ms here, of
-// which the transforms (at the rate of a copy, 4.4 TB/s) 26 ms, the sandwich 57 ms.
+// components, complex128): 1609 ms per call in the direct kernel, 73 ms here, of
+// which the transforms (at the rate of a copy, 4.4 TB/s) 26 ms, the sandwich 48 ms.
 // Inputs that are not finite, or so large that a transform overflows, raise a flag;
 // the direct kernel then recomputes Sigma (its sums meet fewer elements).
 #include <hip/hip_runtime.h>
@@ -109,7 +109,7 @@ __device__ __forceinline__ void fill_twiddles(double2 *tw, int count, int m, int
 __host__ __device__ inline int64_t dht_wgs(const SpecParams &p)
 {
     const int64_t n = ((int64_t)p.NA * p.NB * kN3D * p.NN + 1023) / 1024;
-    return n < 512 ? n : 512;
+    return p.matrix ? 1 : n < 512 ? n : 512;
 }
 __host__ __device__ inline int64_t dhat_wgs(const SpecParams &p) { return (int64_t)p.NA * p.NB * p.Nkz; }
 __host__ __device__ inline int64_t fft_wgs(const SpecParams &p, int64_t atoms, int nb)
@@ -131,6 +131,8 @@ __device__ __forceinline__ void dht_job(const Job &J, int64_t bid, int64_t nwg, 
         if (clear)
             *clear = 0u;
     }
+    if (p.matrix)
+        return;
     double *dht = J.dht();
     const int NN = p.NN, No = p.Norb;
     const int64_t nd = (int64_t)p.NA * p.NB * kN3D * NN;
@@ -658,6 +660,236 @@ __global__ __launch_bounds__(kSB, W) void k_spec_sandwich(const A arg)
         atomicOr(J.flag(), 1u);
 }
 
+__device__ __forceinline__ double mfma(double a, double b, double c)
+{
+    return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+// x of the lane that CTRL names within each four
+template <int CTRL>
+__device__ __forceinline__ double quad_perm(double x)
+{
+    const int2 v = __builtin_bit_cast(int2, x);
+    return __builtin_bit_cast(double, make_int2(__builtin_amdgcn_mov_dpp(v.x, CTRL, 0xf, 0xf, true),
+                                                __builtin_amdgcn_mov_dpp(v.y, CTRL, 0xf, 0xf, true)));
+}
+// the lower 32 lanes of x in both halves, and its upper 32
+__device__ __forceinline__ void halves(double x, double *lower, double *upper)
+{
+    const uint2 v = __builtin_bit_cast(uint2, x);
+    const auto a = __builtin_amdgcn_permlane32_swap(v.x, v.x, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(v.y, v.y, false, false);
+    *lower = __builtin_bit_cast(double, make_uint2(a[0], b[0]));
+    *upper = __builtin_bit_cast(double, make_uint2(a[1], b[1]));
+}
+
+// The sandwich in the matrix form, v_mfma_f64_4x4x4: four products of 4 x 4 matrices, one
+// per point, so that nothing is padded but the orbitals.  With M_i^T = G^T dH_i^T and
+// S^T = sum_j dH_j T_j^T the instruction's result layout is that of its second operand:
+// T_j, mixed from the M_i in the lanes that hold them, goes into the second product
+// without leaving the registers, and dH in 4 x 4 tiles (LDS) serves both products.
+// A wave has four points and all orbitals; per neighbour it reads G^ once, a tile
+// column ahead, and D^ from LDS, where the workgroup's are staged with dH.
+// Norb = 4 t + 2 would waste half of the last tile in each direction.  There the
+// 2 columns take two directions i (first product) or re and im (second), the 2 rows of
+// M re and im, and the contraction over them j = 0 and 1 at once: 240 of the 324
+// matrix instructions at Norb 10 remain.
+// Per four points and neighbour 240 matrix (16 cycles) and 290 vector fp64 instructions
+// (4 cycles); they share the units (alone 75 and 61 TFLOP/s, interleaved no more).  One
+// GPU's energy shard: 4.03 ms per component, the units busy 80 % at 2.2 GHz (row form:
+// 4.53 ms); 97 atoms with 12 orbitals and six neighbours 0.56 ms, row form 0.79 ms.
+// A third wave per SIMD spills (8.3 ms); dH held in registers 4.25 ms.
+template <int No, typename A>
+__global__ __launch_bounds__(kSB, No <= 8 ? 3 : 2) void k_spec_matrix(const A arg)
+{
+    extern __shared__ double2 lds[];
+    const Job J = job(arg);
+    const auto &p = *J.p;
+    constexpr int NN = No * No, T = (No + 3) / 4;
+    constexpr bool kHalf = No % 4 == 2;       // the last tile is a half one,
+    constexpr int Tf = kHalf ? T - 1 : T;     // the first Tf are handled alike
+    constexpr int F = speck::matrix_tiles(No);
+    const int na8 = (J.s.na + 7) >> 3, per = na8 * 8;
+    int64_t x = J.bid;
+    const int in = (int)(x % per);
+    x /= per;
+    const int al = (in & 7) * na8 + (in >> 3);
+    if (al >= J.s.na || x >= (int64_t)p.npg * J.s.nb)
+        return;
+    const int pg = (int)(x % p.npg), blk = (int)(x / p.npg);
+    const int a = J.s.a0 + al, npt = p.npt, P = p.P;
+    const int cap = min(p.NB, speck::matrix_neighbours(No));
+    double *hs = reinterpret_cast<double *>(lds + cap * kNF * P);
+    const int lane = threadIdx.x & 63, lo = lane & 3, hi = lane >> 4;
+    const int pl = (threadIdx.x >> 6) * 4 + ((lane >> 2) & 3), p0 = pg * P;  // the lane's point, the first one
+    const int rounds = min(P, npt - p0 + 15) >> 4;
+    const double2 *Gh = J.Gh() + ((size_t)blockIdx.y * J.s.nb + blk) * p.NA * NN * npt;
+    const double2 *Dh = J.Dh() + ((size_t)blockIdx.y * p.NA + a) * p.NB * kNF * npt;
+    const_ptr<int32_t> neigh = ro(J.t.neigh) + (size_t)a * p.NB;
+    unsigned go[T], co[T];  // element offsets of rows n' and columns m' (past the last: it again)
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        go[t] = (unsigned)(min(4 * t + hi, No - 1) * No * npt);
+        co[t] = (unsigned)(min(4 * t + (kHalf && t == Tf ? lo & 1 : lo), No - 1) * npt);
+    }
+    auto next_valid = [&](int b, int end) {
+        while (b < end && (unsigned)neigh[b] >= (unsigned)p.NA)
+            ++b;
+        return b;
+    };
+    auto rows = [&](int b) { return Gh + (size_t)neigh[b] * NN * npt; };
+    double2 g[T];  // the next tile column of G^; of a half one re or im alone
+    auto read_g = [&](const double2 *gb, unsigned pt, int mu) {
+#pragma unroll
+        for (int k = 0; k < T; ++k)
+            if (kHalf && mu == Tf)
+                g[k].x = reinterpret_cast<const double *>(gb)[2 * (go[k] + co[mu] + pt) + (lo >> 1)];
+            else
+                g[k] = gb[go[k] + co[mu] + pt];
+    };
+    double sr[T][T], si[T][T];
+    bool bad = false;
+    for (int b0 = 0; b0 < p.NB; b0 += cap) {
+        const int b1 = min(p.NB, b0 + cap), first = next_valid(b0, b1);
+        if (first < b1)
+            read_g(rows(first), min(p0 + pl, npt - 1), 0);
+        __syncthreads();
+        for (int i = threadIdx.x; i < (b1 - b0) * kNF * P; i += kSB) {
+            const int r = i / P;
+            lds[i] = (Dh + ((size_t)b0 * kNF + r) * npt)[min(p0 + i - r * P, npt - 1)];
+        }
+        const double *dH = J.t.dH + ((size_t)a * p.NB + b0) * kN3D * NN;
+        for (int i = threadIdx.x; i < (b1 - b0) * F * 16; i += kSB) {
+            const int fb = i >> 4, b = fb / F, f = fb - b * F, l = i & 3, h = i >> 2 & 3;
+            int d = f / (T * T), r = 4 * (f / T % T) + l, c = 4 * (f % T) + h;
+            if (kHalf && f >= kN3D * T * T) {
+                const int e = f - kN3D * T * T;
+                if (e < T) {  // rows of the half tile, directions 0 and 1
+                    d = l >> 1;
+                    r = 4 * Tf + (l & 1);
+                    c = 4 * e + h;
+                } else {      // columns of the half tile, directions 0 and 1
+                    d = h >> 1;
+                    r = 4 * (e - T) + l;
+                    c = 4 * Tf + (h & 1);
+                }
+            }
+            hs[i] = r < No && c < No ? dH[(b * kN3D + d) * NN + r * No + c] : 0.0;
+        }
+        __syncthreads();
+        for (int rd = 0; rd < rounds; ++rd) {
+            if (b0 == 0)
+#pragma unroll
+                for (int u = 0; u < T; ++u)
+#pragma unroll
+                    for (int v = 0; v < T; ++v)
+                        sr[u][v] = si[u][v] = 0.0;
+            for (int b = first; b < b1;) {
+                const int bn = next_valid(b + 1, b1);
+                const double2 *gb = rows(b), *gn = rows(bn < b1 ? bn : first);
+                const unsigned pt = min(p0 + rd * 16 + pl, npt - 1);
+                const unsigned ptn = bn < b1 || rd + 1 == rounds ? pt : (unsigned)min(p0 + rd * 16 + 16 + pl, npt - 1);
+                const double *hb = hs + (b - b0) * F * 16 + (hi * 4 + lo);
+                const double2 *db = lds + (b - b0) * kNF * P + rd * 16 + pl;
+                auto h = [&](int i, int u, int v) { return hb[((i * T + u) * T + v) * 16]; };
+                auto hx = [&](int k) { return hb[(kN3D * T * T + k) * 16]; };
+                auto kx = [&](int u) { return hb[(kN3D * T * T + T + u) * 16]; };
+#pragma unroll
+                for (int mu = 0; mu < T; ++mu) {
+                    double2 c[T];
+#pragma unroll
+                    for (int k = 0; k < T; ++k)
+                        c[k] = g[k];
+                    if (mu + 1 < T)
+                        read_g(gb, pt, mu + 1);
+                    else
+                        read_g(gn, ptn, 0);
+                    double mr[kN3D][T], mi[kN3D][T];
+                    const bool half = kHalf && mu == Tf;
+#pragma unroll
+                    for (int k = 0; k < T; ++k) {
+                        auto both = [&](int i, int v, double w) {
+                            mr[i][v] = mfma(c[k].x, w, k ? mr[i][v] : 0.0);
+                            if (!half)
+                                mi[i][v] = mfma(c[k].y, w, k ? mi[i][v] : 0.0);
+                        };
+#pragma unroll
+                        for (int i = 0; i < kN3D; ++i)
+#pragma unroll
+                            for (int v = 0; v < Tf; ++v)
+                                both(i, v, h(i, v, k));
+                        if (kHalf) {
+                            both(0, T - 1, hx(k));
+                            both(2, T - 1, h(2, T - 1, k));
+                        }
+                    }
+                    if (kHalf) {
+                        mr[1][T - 1] = quad_perm<0xEE>(mr[0][T - 1]);
+                        if (!half)
+                            mi[1][T - 1] = quad_perm<0xEE>(mi[0][T - 1]);
+                    }
+                    if (half)
+#pragma unroll
+                        for (int i = 0; i < kN3D; ++i)
+#pragma unroll
+                            for (int v = 0; v < T; ++v)
+                                halves(mr[i][v], &mr[i][v], &mi[i][v]);
+#pragma unroll
+                    for (int jj = 0; jj < (half ? 2 : kN3D); ++jj) {
+                        // of a half tile the lanes' halves take j = 0 and 1, then all j = 2
+                        double2 d[kN3D];
+#pragma unroll
+                        for (int i = 0; i < kN3D; ++i)
+                            d[i] = db[(i * kN3D + (half ? jj ? 2 : lane >> 5 : jj)) * P];
+                        auto w = [&](int u) { return half ? jj ? h(2, u, mu) : kx(u) : h(jj, u, mu); };
+#pragma unroll
+                        for (int v = 0; v < T; ++v) {
+                            double tr = 0.0, ti = 0.0;
+#pragma unroll
+                            for (int i = 0; i < kN3D; ++i) {
+                                tr = fma(d[i].x, mr[i][v], fma(-d[i].y, mi[i][v], tr));
+                                ti = fma(d[i].x, mi[i][v], fma(d[i].y, mr[i][v], ti));
+                            }
+                            if (kHalf && v == Tf) {
+                                const double o = quad_perm<0x44>(ti);
+                                tr = lo < 2 ? tr : o;
+                            }
+#pragma unroll
+                            for (int u = 0; u < T; ++u) {
+                                sr[u][v] = mfma(w(u), tr, sr[u][v]);
+                                if (!(kHalf && v == Tf))
+                                    si[u][v] = mfma(w(u), ti, si[u][v]);
+                            }
+                        }
+                    }
+                }
+                b = bn;
+            }
+            const int pt = p0 + rd * 16 + pl;
+            if (b1 < p.NB || pt >= npt)
+                continue;
+            double2 *o = J.Sh() + (((size_t)blockIdx.y * J.s.nb + blk) * p.na_cap * NN + (size_t)al * NN) * npt + pt;
+#pragma unroll
+            for (int u = 0; u < T; ++u)
+#pragma unroll
+                for (int v = 0; v < T; ++v) {
+                    const int m = 4 * u + hi, n = 4 * v + (kHalf && v == Tf ? lo & 1 : lo);
+                    if (m >= No || n >= No)
+                        continue;
+                    double2 *to = o + (unsigned)((n * No + m) * npt);
+                    if (kHalf && v == Tf) {
+                        bad |= !finite(sr[u][v]);
+                        reinterpret_cast<double *>(to)[lo >> 1] = sr[u][v];
+                    } else {
+                        bad |= !(finite(sr[u][v]) && finite(si[u][v]));
+                        *to = make_double2(sr[u][v], si[u][v]);
+                    }
+                }
+        }
+    }
+    if (__any(bad) && (threadIdx.x & 63) == 0)
+        atomicOr(J.flag(), 1u);
+}
+
 // The phonon self-energy (Eqs. (4)-(5)): P_ij[q, w] = sum_k sum_e tr(dH_i^T X[k + q, e + s_w, a]
 // dH_j Y[k, e, f]) is a correlation over (k, e), so with X^ the transform of the shifted
 // component and Y^ that of the opposite one at the negated point,
@@ -973,11 +1205,10 @@ hipError_t sandwich_launch(int norb, const A &arg, const Shape &h, hipStream_t s
 {
     if (norb == No) {
         static bool done = false;
-        const hipError_t e = allow_lds(k_spec_sandwich<No, col_block(No), waves(No), A>, speck::kLdsOne, done);
-        if (e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((k_spec_sandwich<No, col_block(No), waves(No), A>), h.grid, dim3(h.threads), h.lds, s, arg);
-        return hipGetLastError();
+        if constexpr (speck::matrix_form(No))
+            return launch(k_spec_matrix<No, A>, arg, h, done, s);
+        else
+            return launch(k_spec_sandwich<No, col_block(No), waves(No), A>, arg, h, done, s);
     }
     if constexpr (No < speck::kMaxNorb)
         return sandwich_launch<No + 1>(norb, arg, h, s);
@@ -1080,7 +1311,10 @@ hipError_t sigma_batch(SpecMany m, const SpecParams *hp, const SpectralGeom *con
     if (e != hipSuccess)
         return e;
     h.grid.x = lay_out(&m, [&](int i) { return sandwich_wgs(hp[i], hp[i].NA, hp[i].nblk); });
-    e = sandwich_launch<1>(hp[0].Norb, m, Shape{h.grid, kSB, g[0]->sand_lds}, s);
+    size_t sand = 0;
+    for (int i = 0; i < m.n; ++i)
+        sand = std::max(sand, g[i]->sand_lds);
+    e = sandwich_launch<1>(hp[0].Norb, m, Shape{h.grid, kSB, sand}, s);
     if (e != hipSuccess)
         return e;
     h.grid.x = lay_out(&m, [&](int i) { return fft_wgs(hp[i], hp[i].NA, hp[i].nblk); });

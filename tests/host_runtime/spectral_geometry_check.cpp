@@ -44,8 +44,15 @@ int main()
         NEED(g.C == 1 << g.logC && g.rowp >= (g.r1 - 1) * (g.r2 + 1) + g.r2);
         NEED(((size_t)g.L + Nkz + (size_t)Nkz * g.C * g.rowp) * 16 == g.fft_lds && g.fft_lds <= speck::kLdsOne);
         NEED(g.fft_threads % 64 == 0 && g.fft_threads >= 64 && g.fft_threads <= speck::kFftBlock);
-        NEED(g.P == speck::kSandBlock / Norb && g.P * g.npg >= g.npt && g.P * (g.npg - 1) < g.npt);
-        NEED(g.sand_lds == NN * g.P * 16 + 3 * NN * 8 && g.sand_lds <= speck::kLdsOne);
+        NEED(g.P * g.npg >= g.npt && g.P * (g.npg - 1) < g.npt && g.matrix == speck::matrix_form(Norb));
+        if (g.matrix) {
+            const int cap = std::min(d.NB, speck::matrix_neighbours(Norb));
+            NEED(cap >= 1 && g.P % 16 == 0 && (g.P == 16 || cap == d.NB));  // rounds only with every neighbour staged
+            NEED(g.sand_lds == cap * speck::matrix_bytes(Norb, g.P) && g.sand_lds <= speck::kLdsTwo);
+        } else {
+            NEED(g.P == speck::kSandBlock / Norb);
+            NEED(g.sand_lds == NN * g.P * 16 + 3 * NN * 8 && g.sand_lds <= speck::kLdsOne);
+        }
         NEED(g.nc >= 1 && g.nc <= ncomp && g.nb >= 1 && g.nb <= g.nblk && g.na >= 1 && g.na <= NA);
         NEED(g.off_dht >= 256 && ((size_t)Nw * 9 + g.L + d.Nqz) * 16 <= speck::kLdsOne);
         NEED(g.off_d >= g.off_dht + NA * NB * 3 * NN * 8);

@@ -59,6 +59,31 @@ CASES = {
 }
 
 
+# Norb of the matrix form: whole tiles, three and two orbitals in the last one, more
+# neighbours than are staged at once, an invalid one; 864 points are 13 groups of four
+# rounds and one of two.
+MATRIX = {f"norb_{n}": P(NA=120, NB=4, Norb=n, Nkz=3, Nqz=3, NE=280, Nw=5) for n in (4, 7, 8, 10, 11, 12)}
+MATRIX.update({
+    "norb_10_13_neighbours": P(NA=16, NB=13, Norb=10, Nkz=3, Nqz=3, NE=41, Nw=5),
+    "norb_12_15_neighbours": P(NA=17, NB=15, Norb=12, Nkz=2, Nqz=2, NE=41, Nw=5),
+    "norb_4_one_point_group": P(NA=5, NB=2, Norb=4, Nkz=1, Nqz=1, NE=12, Nw=3),
+})
+
+
+@pytest.mark.parametrize("name", MATRIX)
+def test_matrix_form_matches_oracle(name):
+    prob = MATRIX[name]
+    assert _is_spectral(prob, 0, 2)
+    dp = gu.DeviceProblem(prob, 40 + len(name), ncomp=2)
+    assert gu.run_sse(dp, prec=0, alpha=0.5 - 1.5j) == 0
+    for c in range(2):
+        blocks = gu.sample_blocks(prob, 3, n_e=8, n_a=4)
+        got, want = dp.device_blocks(c, blocks), gu.oracle_blocks(dp, c, blocks, alpha=0.5 - 1.5j)
+        e = gu.rel_fro(got, want)
+        print(f"  {name} comp {c}: rel_fro={e:.3e}", flush=True)
+        assert e <= 1e-12
+
+
 @pytest.mark.parametrize("name", CASES)
 def test_matches_oracle(name):
     prob, prec = CASES[name]
