@@ -24,7 +24,6 @@ result is the same alone and in a mix.
 from __future__ import annotations
 
 import dataclasses
-import math
 import time
 
 import numpy as np
@@ -63,10 +62,12 @@ def job_bytes(prob: configs.Problem, ncomp: int = 2, nsample: int = 64) -> int:
     g = prob.g_elems() * 8 * ncomp
     d = prob.d_elems() * 8 * ncomp
     dh = prob.NA * prob.NB * prob.N3D * prob.NN * 8
-    groups = sum(math.ceil(n / 8) for n in [prob.Nw])  # one chunk at these sizes
-    afrag = prob.NA * prob.NB * prob.Nqz * groups * 64 * 32
-    split = prob.g_elems() * 8  # bf16 (hi, lo) copy of one component's G
-    return 2 * g + d + dh + afrag + split + 512 + sse.check_workspace_bytes(nsample, ncomp) + \
+    # the larger workspace of the job's plan (whichever fast form) and its binary64 fallback's
+    ws = max(sse.sse_plan(sse.make_desc(prob.NA, prob.NB, prob.Norb, prob.Nkz, prob.Nqz, prob.NE,
+                                        prob.Nw, ncomp=ncomp, prec=pr),
+                          prob.shifts()).workspace_bytes
+             for pr in (sse.FP32, sse.BF16X3, sse.FP64C64))
+    return 2 * g + d + dh + max(ws, 256) + sse.check_workspace_bytes(nsample, ncomp) + \
         prob.NA * prob.NB * 4
 
 
