@@ -377,11 +377,18 @@ SpectralGeom spectral_pi_geometry(const sse_desc &d, const int32_t *w_shift)
 {
     if (d.prec != SSE_FP64)
         return SpectralGeom();
-    SpectralGeom g = best_geometry(d, w_shift, false, spectral_pi_layout);
+    SpectralGeom g = best_geometry(d, w_shift, speck::matrix_form(d.Norb), spectral_pi_layout);
     if (!g.on)
         return g;
-    // the sum over a point's rows reuses the Y^ region for nine values per lane
-    g.sand_lds = std::max((size_t)d.Norb * d.Norb, (size_t)kNF * d.Norb) * g.P * 16 +
+    if (g.matrix) {
+        // rounds of 16 points as for Sigma
+        while (g.P < 64 && 2 * g.P <= g.npt && (int64_t)d.NA * g.nc * (g.npt / (2 * g.P)) >= 2048)
+            g.P *= 2;
+        g.npg = (g.npt + g.P - 1) / g.P;
+        g.sand_lds = (size_t)speck::matrix_tiles(d.Norb) * 128 * std::min(d.NB, speck::pi_matrix_neighbours(d.Norb));
+    } else
+        // the sum over a point's rows reuses the Y^ region for nine values per lane
+        g.sand_lds = std::max((size_t)d.Norb * d.Norb, (size_t)kNF * d.Norb) * g.P * 16 +
                  (size_t)kN3D * d.Norb * d.Norb * 8;
     // the direct kernel walks all energies of all momenta in steps of 3.2 us
     const double direct = 10.0 + d.ncomp * std::max(direct_flops(d) / 30e6, 3.2 * d.Nkz * d.NE);

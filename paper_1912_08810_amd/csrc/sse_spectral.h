@@ -30,9 +30,12 @@ constexpr size_t kHardBytes = (size_t)8 << 30;
 // row / matrix form: Norb 4 179 / 185 (48 / 43), 5 269 / 399, 6 374 / 403 (55 / 43),
 // 7 531 / 497, 8 650 / 547, 9 892 / 1002, 10 1070 / 996 (77 / 56), 11 1485 / 1163,
 // 12 1741 / 1278 (86 / 59).  Above 12 its registers spill (16: 3285 / 5011).
+// Pi, both components: Norb 4 371 / 417 (50 / 45), 5 536 / 785, 6 740 / 827 (64 / 54),
+// 7 1004 / 986, 8 1237 / 1101, 9 1711 / 1962, 10 2122 / 1942 (89 / 71), 11 2853 / 2262,
+// 12 3386 / 2457 (95 / 78).
 constexpr bool matrix_form(int No) { return No == 4 || No == 7 || No == 8 || (No >= 10 && No <= 12); }
 // Tiles of 4 x 4 values of dH per neighbour in LDS; bytes per neighbour with the D^ of P
-// points; the most neighbours that are staged at once.
+// points (Pi: without); the most neighbours that are staged at once.
 constexpr int matrix_tiles(int No)
 {
     const int T = (No + 3) / 4;
@@ -40,6 +43,7 @@ constexpr int matrix_tiles(int No)
 }
 constexpr size_t matrix_bytes(int No, int P) { return (size_t)matrix_tiles(No) * 128 + (size_t)kNF * P * 16; }
 constexpr int matrix_neighbours(int No) { return (int)(kLdsTwo / matrix_bytes(No, 16)); }
+constexpr int pi_matrix_neighbours(int No) { return (int)(kLdsTwo / (matrix_tiles(No) * 128)); }
 }  // namespace speck
 
 // Geometry and workspace layout of the spectral form of one instance.

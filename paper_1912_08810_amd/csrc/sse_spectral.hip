@@ -16,7 +16,8 @@
 // Passes (each one launch over the pass's components and energy blocks):
 //   k_spec_prepare   up to three independent jobs by workgroup: dH transposed for
 //                    scalar reads (and the status word and flag cleared), D^, G -> G^
-//   k_spec_sandwich  G^, D^ -> S^ (k_spec_matrix for the Norb that speck::matrix_form names)
+//   k_spec_sandwich  G^, D^ -> S^ (for the Norb that speck::matrix_form names
+//                    k_spec_matrix, and k_spec_pi_matrix in place of k_spec_pi)
 //   k_spec_inverse   S^ -> Sigma, and the neighbour-table check
 //   k_sse_fp64_redo  the direct kernel, if the flag was raised
 // Twiddle factors are computed by each workgroup into LDS, so that nothing has to run
@@ -682,6 +683,53 @@ __device__ __forceinline__ void halves(double x, double *lower, double *upper)
     *upper = __builtin_bit_cast(double, make_uint2(a[1], b[1]));
 }
 
+// dH of nb neighbours as 4 x 4 tiles, zero past the last orbital; of a half tile also its
+// rows and its columns of the directions 0 and 1 side by side.
+template <int No>
+__device__ __forceinline__ void stage_tiles(double *hs, const double *dH, int nb)
+{
+    constexpr int T = (No + 3) / 4, Tf = No / 4, F = speck::matrix_tiles(No);
+    for (int i = threadIdx.x; i < nb * F * 16; i += kSB) {
+        const int fb = i >> 4, b = fb / F, f = fb - b * F, l = i & 3, h = i >> 2 & 3;
+        int d = f / (T * T), r = 4 * (f / T % T) + l, c = 4 * (f % T) + h;
+        if (No % 4 == 2 && f >= kN3D * T * T) {
+            const int e = f - kN3D * T * T;
+            if (e < T) {
+                d = l >> 1;
+                r = 4 * Tf + (l & 1);
+                c = 4 * e + h;
+            } else {
+                d = h >> 1;
+                r = 4 * (e - T) + l;
+                c = 4 * Tf + (h & 1);
+            }
+        }
+        hs[i] = r < No && c < No ? dH[(b * kN3D + d) * No * No + r * No + c] : 0.0;
+    }
+}
+// Element offsets of a lane's rows and columns of G^ in tile t (past the last: it again),
+// and a tile column at a point (of a half one re or im alone).
+template <int No, int T>
+__device__ __forceinline__ void matrix_offsets(int npt, int lo, int hi, unsigned (&go)[T], unsigned (&co)[T])
+{
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        go[t] = (unsigned)(min(4 * t + hi, No - 1) * No * npt);
+        co[t] = (unsigned)(min(4 * t + (No % 4 == 2 && t == No / 4 ? lo & 1 : lo), No - 1) * npt);
+    }
+}
+template <int No, int T>
+__device__ __forceinline__ void matrix_read(const double2 *gb, unsigned pt, int col, int lo, const unsigned (&go)[T],
+                                            const unsigned (&co)[T], double2 (&g)[T])
+{
+#pragma unroll
+    for (int k = 0; k < T; ++k)
+        if (No % 4 == 2 && col == No / 4)
+            g[k].x = reinterpret_cast<const double *>(gb)[2 * (go[k] + co[col] + pt) + (lo >> 1)];
+        else
+            g[k] = gb[go[k] + co[col] + pt];
+}
+
 // The sandwich in the matrix form, v_mfma_f64_4x4x4: four products of 4 x 4 matrices, one
 // per point, so that nothing is padded but the orbitals.  With M_i^T = G^T dH_i^T and
 // S^T = sum_j dH_j T_j^T the instruction's result layout is that of its second operand:
@@ -725,27 +773,16 @@ __global__ __launch_bounds__(kSB, No <= 8 ? 3 : 2) void k_spec_matrix(const A ar
     const double2 *Gh = J.Gh() + ((size_t)blockIdx.y * J.s.nb + blk) * p.NA * NN * npt;
     const double2 *Dh = J.Dh() + ((size_t)blockIdx.y * p.NA + a) * p.NB * kNF * npt;
     const_ptr<int32_t> neigh = ro(J.t.neigh) + (size_t)a * p.NB;
-    unsigned go[T], co[T];  // element offsets of rows n' and columns m' (past the last: it again)
-#pragma unroll
-    for (int t = 0; t < T; ++t) {
-        go[t] = (unsigned)(min(4 * t + hi, No - 1) * No * npt);
-        co[t] = (unsigned)(min(4 * t + (kHalf && t == Tf ? lo & 1 : lo), No - 1) * npt);
-    }
+    unsigned go[T], co[T];
+    matrix_offsets<No>(npt, lo, hi, go, co);
     auto next_valid = [&](int b, int end) {
         while (b < end && (unsigned)neigh[b] >= (unsigned)p.NA)
             ++b;
         return b;
     };
     auto rows = [&](int b) { return Gh + (size_t)neigh[b] * NN * npt; };
-    double2 g[T];  // the next tile column of G^; of a half one re or im alone
-    auto read_g = [&](const double2 *gb, unsigned pt, int mu) {
-#pragma unroll
-        for (int k = 0; k < T; ++k)
-            if (kHalf && mu == Tf)
-                g[k].x = reinterpret_cast<const double *>(gb)[2 * (go[k] + co[mu] + pt) + (lo >> 1)];
-            else
-                g[k] = gb[go[k] + co[mu] + pt];
-    };
+    double2 g[T];  // the next tile column of G^
+    auto read_g = [&](const double2 *gb, unsigned pt, int mu) { matrix_read<No>(gb, pt, mu, lo, go, co, g); };
     double sr[T][T], si[T][T];
     bool bad = false;
     for (int b0 = 0; b0 < p.NB; b0 += cap) {
@@ -757,24 +794,7 @@ __global__ __launch_bounds__(kSB, No <= 8 ? 3 : 2) void k_spec_matrix(const A ar
             const int r = i / P;
             lds[i] = (Dh + ((size_t)b0 * kNF + r) * npt)[min(p0 + i - r * P, npt - 1)];
         }
-        const double *dH = J.t.dH + ((size_t)a * p.NB + b0) * kN3D * NN;
-        for (int i = threadIdx.x; i < (b1 - b0) * F * 16; i += kSB) {
-            const int fb = i >> 4, b = fb / F, f = fb - b * F, l = i & 3, h = i >> 2 & 3;
-            int d = f / (T * T), r = 4 * (f / T % T) + l, c = 4 * (f % T) + h;
-            if (kHalf && f >= kN3D * T * T) {
-                const int e = f - kN3D * T * T;
-                if (e < T) {  // rows of the half tile, directions 0 and 1
-                    d = l >> 1;
-                    r = 4 * Tf + (l & 1);
-                    c = 4 * e + h;
-                } else {      // columns of the half tile, directions 0 and 1
-                    d = h >> 1;
-                    r = 4 * (e - T) + l;
-                    c = 4 * Tf + (h & 1);
-                }
-            }
-            hs[i] = r < No && c < No ? dH[(b * kN3D + d) * NN + r * No + c] : 0.0;
-        }
+        stage_tiles<No>(hs, J.t.dH + ((size_t)a * p.NB + b0) * kN3D * NN, b1 - b0);
         __syncthreads();
         for (int rd = 0; rd < rounds; ++rd) {
             if (b0 == 0)
@@ -900,9 +920,9 @@ __global__ __launch_bounds__(kSB, No <= 8 ? 3 : 2) void k_spec_matrix(const A ar
 // one point and row m: W_j[m, :] comes from LDS, U_i[n, m] from the lane's column m of X^
 // with wave-uniform dH_i, and the sum over m goes through LDS once per neighbour.
 // The same pipelining, and the same bound.  NA = 128, NE = 500, otherwise as the device-
-// scale problem, both components: 204.6 ms per call in the direct kernel, 5.6 ms here, of
-// which this kernel 3.9 ms and the four transforms 1.8 ms (the CPU-scale configuration:
-// 1270 and 63 us).
+// scale problem, both components: 204.6 ms per call in the direct kernel, 5.4 ms here, of
+// which this kernel 3.7 ms and the four transforms 1.7 ms (Norb 10, which has a matrix
+// form by now).
 template <int No, int CB, int W>
 __global__ __launch_bounds__(kSB, W) void k_spec_pi(const SpecOne arg)
 {
@@ -1070,6 +1090,183 @@ __global__ __launch_bounds__(kSB, W) void k_spec_pi(const SpecOne arg)
     }
 }
 
+// The same in the matrix form (see k_spec_matrix): with A = dH_j, B = Y^ and A = X^T,
+// B = dH_i the results W_j[m, n] and U_i[n, m] of one tile (m, n) lie in the same lanes, so
+// the nine traces are lane-local products; per neighbour their sums over a point's 16 lanes
+// are two more matrix products, with columns and rows of ones.  Of a half tile the rows m
+// hold j = 0 and 1 (W) or re and im (U), the columns n re and im (W) or i = 0 and 1 (U);
+// such sums are kept apart until the end: px by i (lanes' halves j = 0, 1), py by j
+// (halves of each four i = 0, 1), pz both.  240 matrix and 256 vector fp64 instructions
+// per four points and neighbour at Norb 10, and 40 matrix instructions for the sums.
+// NA = 128, NE = 500, otherwise as the device-scale problem: 5.08 ms per call, row form
+// 5.41 ms; the CPU-scale configuration 40 us, row form 49 us.
+template <int No>
+__global__ __launch_bounds__(kSB, 2) void k_spec_pi_matrix(const SpecOne arg)
+{
+    extern __shared__ double2 lds[];
+    const Job J = job(arg);
+    const auto &p = *J.p;
+    constexpr int NN = No * No, T = (No + 3) / 4;
+    constexpr bool kHalf = No % 4 == 2;
+    constexpr int Tf = kHalf ? T - 1 : T, F = speck::matrix_tiles(No);
+    double *hs = reinterpret_cast<double *>(lds);
+    const int na8 = (p.NA + 7) >> 3, per = na8 * 8;
+    const int in = (int)(J.bid % per), pg = (int)(J.bid / per);
+    const int a = (in & 7) * na8 + (in >> 3);
+    if (a >= p.NA || pg >= p.npg)
+        return;
+    const int npt = p.npt, P = p.P;
+    const int cap = min(p.NB, speck::pi_matrix_neighbours(No));
+    const int lane = threadIdx.x & 63, lo = lane & 3, hi = lane >> 4;
+    const int pl = (threadIdx.x >> 6) * 4 + ((lane >> 2) & 3), p0 = pg * P;
+    const int rounds = min(P, npt - p0 + 15) >> 4;
+    const size_t comp = (size_t)blockIdx.y * J.s.nb * p.NA * NN * npt;
+    double2 *Ph = J.Dh() + ((size_t)blockIdx.y * p.NA + a) * p.NB * kNF * npt;
+    const_ptr<int32_t> neigh = ro(J.t.neigh) + (size_t)a * p.NB;
+    unsigned go[T], co[T];
+    matrix_offsets<No>(npt, lo, hi, go, co);
+    auto read = [&](const double2 *gb, unsigned pt, int col, double2 (&g)[T]) {
+        matrix_read<No>(gb, pt, col, lo, go, co, g);
+    };
+    const double e[kN3D] = {lo == 0 ? 1.0 : 0.0, lo == 1 ? 1.0 : 0.0, lo == 2 ? 1.0 : 0.0};
+    const double e01 = hi < 2 ? e[0] : e[1];
+    for (int blk = 0; blk < J.s.nb; ++blk) {
+        const bool add = J.s.blk0 + blk > 0;  // the first block's sums overwrite
+        const double2 *X = J.Gh() + comp + ((size_t)blk * p.NA + a) * NN * npt;
+        const double2 *Y = J.Sh() + comp + (size_t)blk * p.NA * NN * npt;
+        for (int b0 = 0; b0 < p.NB; b0 += cap) {
+            const int b1 = min(p.NB, b0 + cap);
+            if (blk == 0 || cap < p.NB) {
+                __syncthreads();
+                stage_tiles<No>(hs, J.t.dH + ((size_t)a * p.NB + b0) * kN3D * NN, b1 - b0);
+                __syncthreads();
+            }
+            auto next_valid = [&](int b) {
+                while (b < b1 && (unsigned)neigh[b] >= (unsigned)p.NA)
+                    ++b;
+                return b;
+            };
+            const int first = next_valid(b0);
+            for (int rd = 0; rd < rounds; ++rd) {
+                const int at = p0 + rd * 16 + pl;
+                const unsigned pt = min(at, npt - 1);
+                double2 x[T][T], g[T];
+#pragma unroll
+                for (int u = 0; u < T; ++u)
+                    read(X, pt, u, x[u]);
+                if (first < b1)
+                    read(Y + (size_t)neigh[first] * NN * npt, pt, 0, g);
+                for (int b = first; b < b1;) {
+                    const int bn = next_valid(b + 1);
+                    const double2 *yb = Y + (size_t)neigh[b] * NN * npt;
+                    const double2 *yn = Y + (size_t)neigh[bn < b1 ? bn : b] * NN * npt;
+                    const double *hb = hs + (b - b0) * F * 16, *hr = hb + hi * 4 + lo, *hc = hb + lo * 4 + hi;
+                    double pr[kNF], pi[kNF], pxr[kN3D], pxi[kN3D], pyr[kN3D], pyi[kN3D], pzr = 0.0, pzi = 0.0;
+#pragma unroll
+                    for (int i = 0; i < kNF; ++i)
+                        pr[i] = pi[i] = 0.0;
+#pragma unroll
+                    for (int i = 0; i < kN3D; ++i)
+                        pxr[i] = pxi[i] = pyr[i] = pyi[i] = 0.0;
+#pragma unroll
+                    for (int v = 0; v < T; ++v) {
+                        const bool hn = kHalf && v == Tf;
+                        double2 y[T];
+#pragma unroll
+                        for (int k = 0; k < T; ++k)
+                            y[k] = g[k];
+                        if (v + 1 < T)
+                            read(yb, pt, v + 1, g);
+                        else
+                            read(yn, pt, 0, g);
+#pragma unroll
+                        for (int u = 0; u < T; ++u) {
+                            const bool hm = kHalf && u == Tf;
+                            const int nj = hm ? 2 : kN3D, ni = hn ? 2 : kN3D;
+                            double wr[kN3D], wi[kN3D], ur[kN3D], ui[kN3D];
+#pragma unroll
+                            for (int k = 0; k < T; ++k) {
+#pragma unroll
+                                for (int j = 0; j < nj; ++j) {
+                                    const double h = hm && j == 0 ? hr[(kN3D * T * T + k) * 16]
+                                                                  : hr[(((hm ? 2 : j) * T + u) * T + k) * 16];
+                                    wr[j] = mfma(h, y[k].x, k ? wr[j] : 0.0);
+                                    if (!hn)
+                                        wi[j] = mfma(h, y[k].y, k ? wi[j] : 0.0);
+                                }
+#pragma unroll
+                                for (int i = 0; i < ni; ++i) {
+                                    const double h = hn && i == 0 ? hc[(kN3D * T * T + T + k) * 16]
+                                                                  : hc[(((hn ? 2 : i) * T + k) * T + v) * 16];
+                                    ur[i] = mfma(x[u][k].x, h, k ? ur[i] : 0.0);
+                                    if (!hm)
+                                        ui[i] = mfma(x[u][k].y, h, k ? ui[i] : 0.0);
+                                }
+                            }
+#pragma unroll
+                            for (int j = 0; j < nj; ++j)
+                                if (hn) {
+                                    wi[j] = quad_perm<0xEE>(wr[j]);
+                                    wr[j] = quad_perm<0x44>(wr[j]);
+                                }
+#pragma unroll
+                            for (int i = 0; i < ni; ++i)
+                                if (hm)
+                                    halves(ur[i], &ur[i], &ui[i]);
+#pragma unroll
+                            for (int i = 0; i < ni; ++i)
+#pragma unroll
+                                for (int j = 0; j < nj; ++j) {
+                                    const bool si = hn && i == 0, sj = hm && j == 0;  // two at once
+                                    const int ii = hn ? 2 : i, jj = hm ? 2 : j;
+                                    double &zr = si && sj ? pzr : si ? pyr[jj] : sj ? pxr[ii] : pr[ii * kN3D + jj];
+                                    double &zi = si && sj ? pzi : si ? pyi[jj] : sj ? pxi[ii] : pi[ii * kN3D + jj];
+                                    zr = fma(ur[i], wr[j], fma(-ui[i], wi[j], zr));
+                                    zi = fma(ur[i], wi[j], fma(ui[i], wr[j], zi));
+                                }
+                        }
+                    }
+                    // over the lanes' hi: column j of i's tile; then over their lo: row i
+                    double2 s = make_double2(0.0, 0.0), q = s;
+#pragma unroll
+                    for (int i = 0; i < kN3D; ++i) {
+                        double2 r = make_double2(0.0, 0.0);
+#pragma unroll
+                        for (int j = 0; j < kN3D; ++j) {
+                            r.x = mfma(pr[i * kN3D + j], e[j], r.x);
+                            r.y = mfma(pi[i * kN3D + j], e[j], r.y);
+                        }
+                        if (kHalf) {
+                            r.x = mfma(pxr[i], e01, r.x);
+                            r.y = mfma(pxi[i], e01, r.y);
+                            q.x = mfma(pyr[i], e[i], q.x);
+                            q.y = mfma(pyi[i], e[i], q.y);
+                        }
+                        s.x = mfma(e[i], r.x, s.x);
+                        s.y = mfma(e[i], r.y, s.y);
+                    }
+                    if (kHalf) {
+                        q.x = mfma(pzr, e01, q.x);
+                        q.y = mfma(pzi, e01, q.y);
+                        s.x = mfma(e01, q.x, s.x);
+                        s.y = mfma(e01, q.y, s.y);
+                    }
+                    if (hi < kN3D && lo < kN3D && at < npt) {
+                        double2 *o = Ph + ((size_t)b * kNF + hi * kN3D + lo) * npt + at;
+                        const double2 old = add ? *o : make_double2(0.0, 0.0);
+                        *o = make_double2(old.x + s.x, old.y + s.y);
+                    }
+                    b = bn;
+                }
+                if (!add)
+                    for (int b = b0; b < b1; ++b)
+                        if ((unsigned)neigh[b] >= (unsigned)p.NA && hi < kN3D && lo < kN3D && at < npt)
+                            Ph[((size_t)b * kNF + hi * kN3D + lo) * npt + at] = make_double2(0.0, 0.0);
+            }
+        }
+    }
+}
+
 // Pi[q, w, a, b, i, j] = beta / (Nkz L) sum_kappa sum_eps P^_ij[kappa, eps]
 // exp(2 pi i (kappa q / Nkz + eps (s_w - smin) / L)), one workgroup per (a, b, i, j): the
 // eps sum per (kappa, w), split over 2^lg neighbouring lanes where there are few of them,
@@ -1193,10 +1390,11 @@ hipError_t inverse_launch(int L, const SpecOne &o, const Shape &h, hipStream_t s
     return e;
 }
 
-// Columns per block and waves per SIMD of the sandwich kernel: half the columns keep
-// M, S^ and D^ of a lane within 168 registers up to 10 orbitals, so that three waves
-// share a SIMD.  At device scale 3.6 ms per energy block against 4.2 with all ten
-// columns at two waves (a Norb of 12: 1.01 ms per call at two waves, 1.07 at three).
+// Columns per block and waves per SIMD of the sandwich kernel's row form: half the
+// columns keep M, S^ and D^ of a lane within 168 registers up to 10 orbitals, so that
+// three waves share a SIMD.  At Norb 10 (device scale) 3.6 ms per energy block against
+// 4.2 with all ten columns at two waves; at Norb 12 1.01 ms per call at two waves, 1.07
+// at three.
 constexpr int col_block(int No) { return No <= 5 ? No : (No + 1) / 2; }
 constexpr int waves(int No) { return No <= 10 ? 3 : 2; }
 
@@ -1379,11 +1577,10 @@ hipError_t pi_sandwich_launch(const SpecOne &o, const Shape &h, hipStream_t s)
 {
     if (o.p.Norb == No) {
         static bool done = false;
-        const hipError_t e = allow_lds(k_spec_pi<No, pi_col_block(No), pi_waves(No)>, speck::kLdsOne, done);
-        if (e != hipSuccess)
-            return e;
-        hipLaunchKernelGGL((k_spec_pi<No, pi_col_block(No), pi_waves(No)>), h.grid, dim3(h.threads), h.lds, s, o);
-        return hipGetLastError();
+        if constexpr (speck::matrix_form(No))
+            return launch(k_spec_pi_matrix<No>, o, h, done, s);
+        else
+            return launch(k_spec_pi<No, pi_col_block(No), pi_waves(No)>, o, h, done, s);
     }
     if constexpr (No < speck::kMaxNorb)
         return pi_sandwich_launch<No + 1>(o, h, s);

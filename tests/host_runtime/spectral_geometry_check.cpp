@@ -64,7 +64,12 @@ int main()
             ++pi;
             const size_t hrow = (size_t)h.npt * 16;
             NEED(prec == 0 && h.V * h.nblk >= NE && h.npt == Nkz * h.L && h.na == NA);
-            NEED(h.sand_lds >= (size_t)std::max(Norb, 9) * Norb * h.P * 16 + 3 * NN * 8 && h.sand_lds <= speck::kLdsOne);
+            NEED(h.P * h.npg >= h.npt && h.P * (h.npg - 1) < h.npt && h.matrix == speck::matrix_form(Norb));
+            if (h.matrix)
+                NEED(h.P % 16 == 0 && h.sand_lds <= speck::kLdsTwo &&
+                     h.sand_lds == speck::matrix_tiles(Norb) * 128 * (size_t)std::min(d.NB, speck::pi_matrix_neighbours(Norb)));
+            else
+                NEED(h.sand_lds >= (size_t)std::max(Norb, 9) * Norb * h.P * 16 + 3 * NN * 8 && h.sand_lds <= speck::kLdsOne);
             NEED(((size_t)h.L + (size_t)Nkz * (h.L + 2 + Nw)) * 16 <= speck::kLdsOne);
             NEED(h.off_g >= h.off_d + h.nc * ((size_t)NA * NB * 9 * hrow));
             NEED(h.off_s >= h.off_g + (size_t)h.nc * h.nb * NA * NN * hrow);

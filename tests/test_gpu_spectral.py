@@ -211,6 +211,20 @@ def _run_pi_in(dp, nbytes, ncomp=2):
     return st, Pi
 
 
+@pytest.mark.parametrize("name", [*MATRIX, "norb_10_20_neighbours", "norb_12_24_neighbours"])
+def test_pi_matrix_form_is_the_direct_kernel(name):
+    """Several energy blocks, rounds and stagings of the neighbours.  Both round sums of some
+    1e6 terms: 1e-13 is a thousand rounding errors, a wrong term is above 1e-7."""
+    prob = MATRIX.get(name) or P(NA=26, NB=int(name.split("_")[2]), Norb=int(name.split("_")[1]), Nkz=2, Nqz=2,
+                                 NE=600, Nw=5)
+    dp = gu.DeviceProblem(prob, 60 + len(name), ncomp=2)
+    (st, got), (st2, want) = _run_pi_in(dp, 0), _run_pi_in(dp, 256)
+    assert st == st2 == 0
+    e = gu.rel_fro(got.cpu().numpy(), want.cpu().numpy())
+    print(f"  {name}: rel_fro={e:.3e}", flush=True)
+    assert e <= 1e-13
+
+
 @pytest.mark.parametrize("name", PI_CASES)
 def test_pi_matches_oracle(name):
     prob = PI_CASES[name]
