@@ -5,6 +5,7 @@ import glob
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -26,18 +27,18 @@ def sources():
 
 
 def build(verbose: bool = False, extra=()) -> str:
-    """Compile each source to an object in _build/, link libsse.so in the package."""
+    """Compile the sources side by side to objects in _build/, link libsse.so in the package."""
     bdir = os.path.join(ROOT, "_build")
     os.makedirs(bdir, exist_ok=True)
-    objs = []
+    cmds, objs = [], []
     for src in sources():
-        obj = os.path.join(bdir, os.path.basename(src) + ".o")
-        cmd = [HIPCC, *HIP_FLAGS, *extra, "-I", os.path.join(ROOT, "include"),
-               "-I", os.path.join(PKG, "csrc"), "-c", src, "-o", obj]
+        objs.append(os.path.join(bdir, os.path.basename(src) + ".o"))
+        cmds.append([HIPCC, *HIP_FLAGS, *extra, "-I", os.path.join(ROOT, "include"),
+                     "-I", os.path.join(PKG, "csrc"), "-c", src, "-o", objs[-1]])
         if verbose:
-            print(" ".join(cmd), flush=True)
-        subprocess.run(cmd, check=True)
-        objs.append(obj)
+            print(" ".join(cmds[-1]), flush=True)
+    with ThreadPoolExecutor(min(8, len(cmds))) as pool:
+        list(pool.map(lambda c: subprocess.run(c, check=True), cmds))
     tmp = LIB + ".tmp"
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", tmp, *objs]
     subprocess.run(cmd, check=True)
