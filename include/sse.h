@@ -134,9 +134,9 @@ typedef struct sse_plan_s *sse_plan_t;
  * Validate a problem and build a plan.  w_shift: host array [Nw] of energy
  * index shifts, |s_w| < NE (may be negative; need not be sorted).
  * *workspace_bytes receives the device workspace size for every call with this
- * plan, at most 8 GiB beyond what the direct form needs; a single-instance plan
- * also takes a smaller one that holds the direct form's (256 bytes in binary64
- * arithmetic).  SSE_ERR_SHAPE if NA, Nkz, NE < 1, NB outside 1..50, Norb outside
+ * plan, at most 8 GiB beyond what the direct form needs; a smaller one that holds
+ * the direct form's (256 bytes in binary64 arithmetic) is taken too, and runs that
+ * form.  SSE_ERR_SHAPE if NA, Nkz, NE < 1, NB outside 1..50, Norb outside
  * 1..30, N3D != 3, Nqz outside 1..Nkz, Nw outside 1..128, ncomp not 1 or 2, a
  * shift out of range, or a tensor larger than 2^62 elements.
  */

@@ -84,6 +84,7 @@ struct sse_plan_s {
     };
     std::vector<Wave> waves;
     size_t spec_off = 0;
+    sse_plan_s *plain = nullptr;  // with waves: the same batch, every instance direct
     // ---- batch plans: device tables, built at the first submission
     std::once_flag tables_once;
     hipError_t tables_err = hipSuccess;
@@ -97,6 +98,7 @@ struct sse_plan_s {
     int grid = 0;
     ~sse_plan_s()
     {
+        delete plain;
         // nothing useful can be done with a failure while destroying a plan
         (void)hipFree(d_params);
         (void)hipFree(d_chunk_inst);
@@ -191,7 +193,8 @@ TapTable sorted_taps(const sse_desc &d, const int32_t *w_shift)
     return t;
 }
 
-sse_status build_instance(const sse_desc *d, const int32_t *w_shift, Instance *out)
+// spectral: the spectral form may be chosen.
+sse_status build_instance(const sse_desc *d, const int32_t *w_shift, bool spectral, Instance *out)
 {
     const int te_request = d ? d->tile_e : 0;
     sse_status st = check_desc(d, w_shift);
@@ -216,7 +219,7 @@ sse_status build_instance(const sse_desc *d, const int32_t *w_shift, Instance *o
     const int64_t nwg = (int64_t)out->geom.n_etiles * d->Nkz * d->NA;
     if (nwg > 0x7fffffffLL)
         return fail(SSE_ERR_SHAPE, "sse_plan: %lld tiles exceed one launch", (long long)nwg);
-    if (spectral_sigma_launch)
+    if (spectral && spectral_sigma_launch)
         out->spec = spectral_geometry(*d, w_shift);
     if (out->spec.on)
         out->redo_geom = fp64_geometry(d->Norb, d->NE, t, 0, 0, &out->redo_taps);
@@ -615,7 +618,7 @@ sse_status sse_plan(const sse_desc *desc, const int32_t *w_shift, sse_plan_t *pl
     if (!p)
         return fail(SSE_ERR_NOMEM, "sse_plan: out of host memory");
     p->inst.resize(1);
-    sse_status st = build_instance(desc, w_shift, &p->inst[0]);
+    sse_status st = build_instance(desc, w_shift, true, &p->inst[0]);
     if (st != SSE_OK) {
         delete p;
         return st;
@@ -634,14 +637,9 @@ sse_status sse_plan(const sse_desc *desc, const int32_t *w_shift, sse_plan_t *pl
 // Most workspace of an instance that shares its launches with others of its batch.
 static constexpr size_t kSharedBytes = (size_t)128 << 20;
 
-sse_status sse_plan_batch(const sse_desc *descs, const int32_t *const *w_shift, int32_t n,
-                          sse_plan_t *plan, size_t *workspace_bytes)
+static sse_status make_batch(const sse_desc *descs, const int32_t *const *w_shift, int32_t n, bool spectral,
+                             sse_plan_s **plan)
 {
-    if (!plan || !descs || !w_shift || n < 1)
-        return fail(SSE_ERR_ARG, "sse_plan_batch: NULL argument or n < 1");
-    if (n > kMaxBatch)
-        return fail(SSE_ERR_ARG, "sse_plan_batch: n=%d above %d instances", n, kMaxBatch);
-    *plan = nullptr;
     sse_plan_s *p = new (std::nothrow) sse_plan_s;
     if (!p)
         return fail(SSE_ERR_NOMEM, "sse_plan_batch: out of host memory");
@@ -659,7 +657,7 @@ sse_status sse_plan_batch(const sse_desc *descs, const int32_t *const *w_shift, 
             return fail(SSE_ERR_ARG, "sse_plan_batch: instance %d differs in Norb/ncomp/prec/alpha/dt_antiherm",
                         t);
         }
-        sse_status st = build_instance(&descs[t], w_shift[t], &p->inst[t]);
+        sse_status st = build_instance(&descs[t], w_shift[t], spectral, &p->inst[t]);
         if (st != SSE_OK) {
             delete p;
             return st;
@@ -691,10 +689,29 @@ sse_status sse_plan_batch(const sse_desc *descs, const int32_t *const *w_shift, 
     }
     p->spec_off = ws;
     p->ws_bytes = ws + spec;
+    if (!p->waves.empty()) {
+        const sse_status st = make_batch(descs, w_shift, n, false, &p->plain);
+        if (st != SSE_OK) {
+            delete p;
+            return st;
+        }
+    }
     *plan = p;
-    if (workspace_bytes)
-        *workspace_bytes = p->ws_bytes;
     return SSE_OK;
+}
+
+sse_status sse_plan_batch(const sse_desc *descs, const int32_t *const *w_shift, int32_t n,
+                          sse_plan_t *plan, size_t *workspace_bytes)
+{
+    if (!plan || !descs || !w_shift || n < 1)
+        return fail(SSE_ERR_ARG, "sse_plan_batch: NULL argument or n < 1");
+    if (n > kMaxBatch)
+        return fail(SSE_ERR_ARG, "sse_plan_batch: n=%d above %d instances", n, kMaxBatch);
+    *plan = nullptr;
+    const sse_status st = make_batch(descs, w_shift, n, true, plan);
+    if (st == SSE_OK && workspace_bytes)
+        *workspace_bytes = (*plan)->ws_bytes;
+    return st;
 }
 
 void sse_plan_destroy(sse_plan_t plan) { delete plan; }
@@ -830,10 +847,13 @@ sse_status sse_submit(sse_plan_t plan, const sse_args *args, void *workspace,
 {
     if (!plan || !args || !ticket)
         return fail(SSE_ERR_ARG, "sse_submit: NULL plan, args or ticket");
-    // a single plan's workspace may be the direct kernels' alone: then they run
+    // the workspace may be the direct kernels' alone: then they run
+    const size_t full = plan->ws_bytes;
+    if (plan->plain && workspace_bytes < full)
+        plan = plan->plain;
     const size_t least = plan->batch ? plan->ws_bytes : plan->direct_bytes;
     if (!workspace || workspace_bytes < least)
-        return fail(SSE_ERR_ARG, "sse_submit: workspace of %zu bytes needed", plan->ws_bytes);
+        return fail(SSE_ERR_ARG, "sse_submit: workspace of %zu bytes needed", full);
     for (size_t t = 0; t < plan->inst.size(); ++t) {
         const sse_args &a = args[t];
         if (!a.neigh || !a.dH || !a.G || !a.Dt || !a.Sigma)
