@@ -135,7 +135,8 @@ def make_desc(NA, NB, Norb, Nkz, Nqz, NE, Nw, ncomp=1, prec=FP64, alpha=1j, N3D=
 
 
 class Plan:
-    """Owns an sse_plan_t; ``workspace_bytes`` is the device workspace each call needs."""
+    """Owns an sse_plan_t; ``workspace_bytes`` is the device workspace of a call in the plan's
+    form, ``direct_bytes`` the least that Sigma takes, in the direct form."""
 
     def __init__(self, desc, w_shift=None, descs=None, w_shifts=None):
         self.handle = ctypes.c_void_p()
@@ -143,6 +144,7 @@ class Plan:
         if descs is None:
             import numpy as np
             self._shift = np.ascontiguousarray(w_shift, dtype=np.int32)
+            self._shifts = [self._shift]
             st = lib.sse_plan(ctypes.byref(desc), self._shift.ctypes.data_as(ctypes.c_void_p),
                               ctypes.byref(self.handle), ctypes.byref(ws))
             _check(st, "sse_plan")
@@ -159,12 +161,34 @@ class Plan:
             self.n = n
             self.descs = list(descs)
         self.workspace_bytes = ws.value
+        self.batch = descs is not None
+        self._direct = None
+
+    @property
+    def direct_bytes(self) -> int:
+        if self._direct is None:
+            # a chunk cap that cuts nothing asks for the direct form; a batch of one adds 256 bytes
+            descs = []
+            for d in self.descs:
+                c = sse_desc.from_buffer_copy(d)
+                c.chunk_taps = c.chunk_taps or 128
+                descs.append(c)
+            p = Plan(None, descs=descs, w_shifts=self._shifts)
+            self._direct = p.workspace_bytes - (0 if self.batch else 256)
+        return self._direct
 
     def __del__(self):
         h = getattr(self, "handle", None)
         if h is not None and h.value and lib is not None:
             lib.sse_plan_destroy(h)
             self.handle = None
+
+
+def _nbytes(workspace, of_pointer) -> int:
+    """A workspace's size; that of a bare pointer is not known and taken to be of_pointer()."""
+    if hasattr(workspace, "numel"):
+        return workspace.numel() * workspace.element_size()
+    return of_pointer()
 
 
 def sse_plan(desc, w_shift) -> Plan:
@@ -176,8 +200,11 @@ def sse_plan_batch(descs, w_shifts) -> Plan:
 
 
 def sse_compute(plan: Plan, neigh, dH, G, Dt, Sigma, workspace, stream=None, check=True) -> int:
+    """workspace: a tensor of plan.workspace_bytes; one of fewer bytes, or a bare pointer (to at
+    least plan.direct_bytes), runs the direct form.  The same for sse_submit."""
     st = lib.sse_compute(plan.handle, _ptr(neigh), _ptr(dH), _ptr(G), _ptr(Dt), _ptr(Sigma),
-                         _ptr(workspace), plan.workspace_bytes, _stream(stream))
+                         _ptr(workspace), _nbytes(workspace, lambda: plan.direct_bytes),
+                         _stream(stream))
     return _check(st, "sse_compute") if check else st
 
 
@@ -194,9 +221,10 @@ def pi_elems(desc) -> int:
 
 
 def sse_pi_compute(plan: Plan, neigh, dH, G, Pi, workspace, stream=None, check=True) -> int:
-    """Phonon self-energy (Eqs. (4)-(5)); G holds both components, Pi ncomp."""
-    nbytes = workspace.numel() * workspace.element_size() if hasattr(workspace, "numel") \
-        else plan.workspace_bytes
+    """Phonon self-energy (Eqs. (4)-(5)); G holds both components, Pi ncomp.  workspace: a tensor
+    of plan.workspace_bytes; one of fewer bytes, or a bare pointer (to at least 256), runs the
+    direct form."""
+    nbytes = _nbytes(workspace, lambda: 256)
     st = lib.sse_pi_compute(plan.handle, _ptr(neigh), _ptr(dH), _ptr(G), _ptr(Pi),
                             _ptr(workspace), nbytes, _stream(stream))
     return _check(st, "sse_pi_compute") if check else st
@@ -204,8 +232,7 @@ def sse_pi_compute(plan: Plan, neigh, dH, G, Pi, workspace, stream=None, check=T
 
 def sse_pi_submit(plan: Plan, neigh, dH, G, Pi, workspace, stream=None) -> int:
     t = ctypes.c_uint64()
-    nbytes = workspace.numel() * workspace.element_size() if hasattr(workspace, "numel") \
-        else plan.workspace_bytes
+    nbytes = _nbytes(workspace, lambda: 256)
     _check(lib.sse_pi_submit(plan.handle, _ptr(neigh), _ptr(dH), _ptr(G), _ptr(Pi),
                              _ptr(workspace), nbytes, _stream(stream), ctypes.byref(t)),
            "sse_pi_submit")
@@ -256,7 +283,8 @@ def sse_submit(plan: Plan, items, workspace, stream=None) -> int:
     """items: one (neigh, dH, G, Dt, Sigma) tuple per instance; returns a ticket."""
     t = ctypes.c_uint64()
     arr = _args(items)
-    _check(lib.sse_submit(plan.handle, arr, _ptr(workspace), plan.workspace_bytes,
+    _check(lib.sse_submit(plan.handle, arr, _ptr(workspace),
+                          _nbytes(workspace, lambda: plan.direct_bytes),
                           _stream(stream), ctypes.byref(t)), "sse_submit")
     return t.value
 

@@ -1,0 +1,42 @@
+"""Workspaces of the direct kernels' size, through the Python binding: accepted, and the
+result is the direct form's, bit for bit; the bytes behind the buffer stay as they were."""
+import pytest
+
+from paper_1912_08810_amd import configs
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+P = configs.Problem
+PROBS = [P(NA=11, NB=4, Norb=10, Nkz=3, Nqz=3, NE=41, Nw=6), P(NA=7, NB=4, Norb=10, Nkz=3, Nqz=3, NE=60, Nw=10)]
+
+
+def _desc(p, prec, **kw):
+    from paper_1912_08810_amd import sse
+    return sse.make_desc(p.NA, p.NB, p.Norb, p.Nkz, p.Nqz, p.NE, p.Nw, prec=prec, **kw)
+
+
+@pytest.mark.parametrize("prec", [0, 3])
+@pytest.mark.parametrize("batch", [False, True], ids=["single", "batch"])
+def test_small_workspace_runs_the_direct_form(prec, batch):
+    import torch
+    from paper_1912_08810_amd import sse
+    probs = PROBS if batch else PROBS[:1]
+    dps = [gu.DeviceProblem(p, 300 + i, fp32=prec != 0) for i, p in enumerate(probs)]
+    items = [(d.neigh, d.dH, d.G, d.D, d.Sigma) for d in dps]
+    shifts = [p.shifts() for p in probs]
+
+    def run(nbytes, **kw):
+        descs = [_desc(p, prec, **kw) for p in probs]
+        plan = sse.sse_plan_batch(descs, shifts) if batch else sse.sse_plan(descs[0], shifts[0])
+        assert nbytes is None or nbytes < plan.workspace_bytes
+        guard = torch.full(((nbytes or plan.workspace_bytes) + 65536,), 7, dtype=torch.uint8, device="cuda")
+        ws = guard[:nbytes or plan.workspace_bytes]
+        sse.sse_wait(sse.sse_submit(plan, items, ws, torch.cuda.current_stream()))
+        assert bool((guard[ws.numel():] == 7).all())
+        return plan, [d.Sigma.clone() for d in dps]
+
+    direct, want = run(None, chunk_taps=128)
+    plan, got = run(direct.direct_bytes)
+    assert plan.direct_bytes == direct.direct_bytes
+    for g, w in zip(got, want):
+        assert torch.equal(g.view(torch.int32), w.view(torch.int32))
