@@ -216,6 +216,8 @@ SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32
 namespace {
 
 size_t up(size_t x) { return (x + speck::kAlign - 1) & ~(speck::kAlign - 1); }
+// At the end of a layout: room for its start to move to a multiple of kAlign, and more.
+constexpr size_t kSlack = 4096;
 
 // Workspace layout for the most components, then energy blocks, then sandwich
 // atoms per pass that fit budget; false if an eighth of the atoms does not fit.
@@ -223,7 +225,7 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 {
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
-    const size_t fixed = up((size_t)d.NA * d.NB * kN3D * NN * 8) + 4 * speck::kAlign + 4096;
+    const size_t fixed = up((size_t)d.NA * d.NB * kN3D * NN * 8) + 4 * speck::kAlign + kSlack;
     for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
         const size_t base = fixed + g->nc * db, per = 2 * g->nc * gb;
         if (budget < base + (g->nc > 1 ? per : gb + gb / 8))
@@ -236,7 +238,7 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
         g->off_d = g->off_dht + up((size_t)d.NA * d.NB * kN3D * NN * 8);
         g->off_g = g->off_d + up(g->nc * db);
         g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
-        g->bytes = g->off_s + up((size_t)g->nc * g->nb * g->na * NN * row) + 4096;
+        g->bytes = g->off_s + up((size_t)g->nc * g->nb * g->na * NN * row) + kSlack;
         return true;
     }
     return false;
@@ -249,7 +251,7 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
     const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
-    const size_t fixed = dht + 4 * speck::kAlign + 4096;
+    const size_t fixed = dht + 4 * speck::kAlign + kSlack;
     // the output pass holds a transform row per momentum and its sums per frequency
     if (((size_t)g->L + (size_t)d.Nkz * (g->L + 2 + d.Nw)) * 16 > speck::kLdsOne)
         return false;
@@ -263,7 +265,7 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
         g->off_d = g->off_dht + dht;
         g->off_g = g->off_d + up(g->nc * db);
         g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
-        g->bytes = g->off_s + up((size_t)g->nc * g->nb * gb) + 4096;
+        g->bytes = g->off_s + up((size_t)g->nc * g->nb * gb) + kSlack;
         return true;
     }
     return false;

@@ -5,6 +5,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdint>
 #include <cstring>
 #include <cstdarg>
 #include <cstdio>
@@ -231,6 +232,11 @@ bool fp64_arith(int prec) { return prec == SSE_FP64 || prec == SSE_FP64C64; }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
+// The workspace of the spectral kernels, which read and write whole complex values and
+// move 16 bytes per lane into LDS: the caller's, wherever that starts, from the next
+// multiple of 256 on (a SpectralGeom's bytes have room for that at their end).
+char *spectral_ws(void *p) { return (char *)(((uintptr_t)p + 255) & ~(uintptr_t)255); }
+
 Fp64Params fp64_params(const sse_desc &d, const TileGeom &geom, const TapTable &taps);
 
 // The spectral form of one instance, every component, then the direct binary64
@@ -241,7 +247,7 @@ sse_status enqueue_spectral(const Instance &I, const sse_args &a, uint32_t *dsta
 {
     hipError_t e = spectral_sigma_launch(I.d, I.spec, I.shift, a, dstatus, clear, host,
                                          fp64_params(I.d, I.redo_geom, I.redo_taps), I.redo_geom.lds_bytes,
-                                         wsfree, s);
+                                         spectral_ws(wsfree), s);
     return e == hipSuccess ? SSE_OK : hip_fail(e, "spectral kernel launch");
 }
 
@@ -509,7 +515,7 @@ sse_status enqueue_batch(sse_plan_s *P, const sse_args *args, char *ws, uint32_t
             ap[i] = &args[w.inst[i]];
         }
         e = spectral_batch_launch(nw, dp, gp, ap, w.off.data(), w.hp.data(), w.d_params, w.d_redo, w.redo_lds,
-                                  dstatus, clear, ws + P->spec_off, s);
+                                  dstatus, clear, spectral_ws(ws + P->spec_off), s);
         if (e != hipSuccess)
             return hip_fail(e, "spectral batch launch");
         clear = false;
@@ -1059,7 +1065,7 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
     if (st != SSE_OK)
         return st;
     uint32_t *dstatus = (uint32_t *)workspace;
-    char *wsfree = (char *)workspace + kStatusBytes;
+    char *wsfree = spectral_ws((char *)workspace + kStatusBytes);
     const bool spectral = I.pi_spec.on && workspace_bytes >= kStatusBytes + I.pi_spec.bytes;
     hipError_t e;
     if (spectral) {

@@ -20,6 +20,9 @@ static void touch(const SpectralGeom &g, const sse_desc &d, char *ws)
 {
     const size_t row = (size_t)g.npt * 16 * d.Norb * d.Norb;
     const size_t end = g.off_s + (size_t)g.nc * g.nb * g.na * row;
+    // complex values lie on their own size, 16 bytes
+    if (((uintptr_t)ws | g.off_dht | g.off_d | g.off_g | g.off_s) & 15)
+        g_bad = true;
     if (ws < g_ws + 4 || ws + end > g_ws + g_ws_bytes)
         g_bad = true;
 }
@@ -103,11 +106,48 @@ static int batch_in_a_direct_workspace()
     return 0;
 }
 
+// Workspaces that start 4, 8 and 252 bytes behind a multiple of 256 (the status word alone
+// wants four): single plans, a batch and Pi, in the plan's own size.
+static int workspace_at_any_word()
+{
+    for (int off : {0, 4, 8, 252}) {
+        const int32_t *sh[2] = {kShift, kShift};
+        sse_desc d = desc(SSE_FP64, 0), d2[2] = {d, d};
+        sse_plan_t p, pb;
+        size_t n, nb;
+        if (sse_plan(&d, kShift, &p, &n) || sse_plan_batch(d2, sh, 2, &pb, &nb))
+            return 1;
+        const size_t most = n > nb ? n : nb;
+        std::vector<char> w(most + 512);
+        char *base = (char *)(((uintptr_t)w.data() + 255) & ~(uintptr_t)255) + off;
+        sse_args a[2] = {{kNeigh, one, one, one, one}, {kNeigh, one, one, one, one}};
+        uint64_t t[3];
+        n_spectral = 0;
+        g_ws = base;
+        g_ws_bytes = n;
+        if (sse_submit(p, a, base, n, nullptr, &t[0]) || sse_wait(t[0]))
+            return 2;
+        if (sse_pi_submit(p, kNeigh, one, one, one, base, n, nullptr, &t[1]))
+            return 3;
+        sse_wait(t[1]);  // the stand-in of the last kernel delivers no status
+        g_ws_bytes = nb;
+        if (sse_submit(pb, a, base, nb, nullptr, &t[2]) || sse_wait(t[2]))
+            return 4;
+        if (n_spectral != 3)
+            return 5;
+        sse_plan_destroy(p);
+        sse_plan_destroy(pb);
+    }
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     int r = -1;
     if (argc > 1 && !strcmp(argv[1], "batch_in_a_direct_workspace"))
         r = batch_in_a_direct_workspace();
+    if (argc > 1 && !strcmp(argv[1], "workspace_at_any_word"))
+        r = workspace_at_any_word();
     if (r == 0 && !g_bad)
         printf("OK\n");
     else

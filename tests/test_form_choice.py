@@ -31,3 +31,7 @@ def _run(exe, check):
 
 def test_batch_takes_a_workspace_of_the_direct_size(driver):
     _run(driver, "batch_in_a_direct_workspace")
+
+
+def test_workspace_may_start_at_any_word(driver):
+    _run(driver, "workspace_at_any_word")

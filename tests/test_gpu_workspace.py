@@ -40,3 +40,22 @@ def test_small_workspace_runs_the_direct_form(prec, batch):
     assert plan.direct_bytes == direct.direct_bytes
     for g, w in zip(got, want):
         assert torch.equal(g.view(torch.int32), w.view(torch.int32))
+
+
+def test_workspace_behind_a_word_gives_the_same_bits():
+    """A workspace that starts four bytes behind an aligned one: Sigma and Pi."""
+    import torch
+    from paper_1912_08810_amd import sse
+    p = PROBS[0]
+    dp = gu.DeviceProblem(p, 310, ncomp=2)
+    plan = sse.sse_plan(_desc(p, 0, ncomp=2), p.shifts())
+    assert plan.workspace_bytes > plan.direct_bytes
+    got = []
+    for off in (0, 4):
+        ws = torch.empty(plan.workspace_bytes + 4, dtype=torch.uint8, device="cuda")[off:off + plan.workspace_bytes]
+        Pi = torch.zeros(2, sse.pi_elems(plan.descs[0]) * 2, dtype=torch.float64, device="cuda")
+        sse.sse_compute(plan, dp.neigh, dp.dH, dp.G, dp.D, dp.Sigma, ws, torch.cuda.current_stream())
+        sse.sse_pi_compute(plan, dp.neigh, dp.dH, dp.G, Pi, ws, torch.cuda.current_stream())
+        got.append((dp.Sigma.clone(), Pi))
+    for x, y in zip(*got):
+        assert torch.equal(x.view(torch.int64), y.view(torch.int64))
