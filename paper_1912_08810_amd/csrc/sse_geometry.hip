@@ -252,7 +252,10 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
     const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
     const size_t fixed = dht + 4 * speck::kAlign + kSlack;
-    // the output pass holds a transform row per momentum and its sums per frequency
+    // the output pass has a workgroup per (atom, neighbour, i, j), and a launch fewer than 2^32 threads
+    if ((int64_t)d.NA * d.NB * kNF * speck::kSandBlock > 0xffffffffLL)
+        return false;
+    // it holds a transform row per momentum and its sums per frequency
     if (((size_t)g->L + (size_t)d.Nkz * (g->L + 2 + d.Nw)) * 16 > speck::kLdsOne)
         return false;
     for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
