@@ -57,18 +57,26 @@ class JobResult:
         return self.done - self.arrival
 
 
-def job_bytes(prob: configs.Problem, ncomp: int = 2, nsample: int = 64) -> int:
-    """Device bytes a job holds while admitted (complex64 storage)."""
+def _desc(prob: configs.Problem, prec: int, ncomp: int, **kw):
+    return sse.make_desc(prob.NA, prob.NB, prob.Norb, prob.Nkz, prob.Nqz, prob.NE, prob.Nw,
+                         ncomp=ncomp, prec=prec, **kw)
+
+
+def _tensor_bytes(prob: configs.Problem, ncomp: int, nsample: int) -> int:
     g = prob.g_elems() * 8 * ncomp
     d = prob.d_elems() * 8 * ncomp
     dh = prob.NA * prob.NB * prob.N3D * prob.NN * 8
-    # the larger workspace of the job's plan (whichever fast form) and its binary64 fallback's
-    ws = max(sse.sse_plan(sse.make_desc(prob.NA, prob.NB, prob.Norb, prob.Nkz, prob.Nqz, prob.NE,
-                                        prob.Nw, ncomp=ncomp, prec=pr),
-                          prob.shifts()).workspace_bytes
-             for pr in (sse.FP32, sse.BF16X3, sse.FP64C64))
-    return 2 * g + d + dh + max(ws, 256) + sse.check_workspace_bytes(nsample, ncomp) + \
-        prob.NA * prob.NB * 4
+    return 2 * g + d + dh + sse.check_workspace_bytes(nsample, ncomp) + prob.NA * prob.NB * 4
+
+
+def job_bytes(prob: configs.Problem, ncomp: int = 2, nsample: int = 64) -> int:
+    """Least device bytes a job holds while admitted (complex64 storage): its tensors and the
+    workspace of the direct kernels, whichever the form."""
+    ws = 256
+    for prec in (sse.FP32, sse.BF16X3):
+        if prob.Norb <= 22:  # the complex64 matrix forms' most
+            ws = max(ws, sse.sse_plan(_desc(prob, prec, ncomp), prob.shifts()).direct_bytes)
+    return _tensor_bytes(prob, ncomp, nsample) + ws
 
 
 def poisson_arrivals(n: int, rate: float, seed: int) -> np.ndarray:
@@ -85,25 +93,22 @@ def make_jobs(probs, rate: float, seed: int, iterations: int = 10):
 class _Active:
     """An admitted job: resident tensors, plans, its stream and iteration state."""
 
-    def __init__(self, spec: JobSpec, prec: int, stream, nsample: int, now: float):
+    def __init__(self, spec: JobSpec, prec: int, stream, nsample: int, now: float, ws_bytes: int):
         import torch
         from ssegen.device_problem import DeviceProblem
         self.spec = spec
         self.admitted = now
         p = spec.prob
         self.stream = stream
-        mk = lambda pr: sse.make_desc(p.NA, p.NB, p.Norb, p.Nkz, p.Nqz, p.NE, p.Nw, ncomp=2,
-                                      prec=pr)
-        self.plan = sse.sse_plan(mk(prec), p.shifts())
-        self.plan_fb = sse.sse_plan(mk(sse.FP64C64), p.shifts())
-        nbytes = max(self.plan.workspace_bytes, self.plan_fb.workspace_bytes, 256)
+        self.plan = sse.sse_plan(_desc(p, prec, 2), p.shifts())
+        self.plan_fb = sse.sse_plan(_desc(p, sse.FP64C64, 2), p.shifts())
         rng = np.random.default_rng(spec.seed + 17)
         blocks = np.stack([rng.integers(0, p.Nkz, nsample), rng.integers(0, p.NE, nsample),
                            rng.integers(0, p.NA, nsample)], axis=1).astype(np.int32)
         # every allocation and the input generation are ordered on the job's stream
         with torch.cuda.stream(stream):
             self.dp = DeviceProblem(p, spec.seed, ncomp=2, fp32=True, sync=False)
-            self.ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+            self.ws = torch.empty(ws_bytes, dtype=torch.uint8, device="cuda")
             self.blocks = torch.from_numpy(blocks).cuda()
             self.cws = torch.empty(sse.check_workspace_bytes(nsample, 2), dtype=torch.uint8,
                                    device="cuda")
@@ -190,6 +195,17 @@ class Server:
         self.keep = keep_results
         self.sigma = {}
 
+    def _need(self, prob):
+        """(bytes reserved, bytes of workspace) of a job: the workspace that its plans ask for if
+        the budget has room for such a job, else the direct kernels'.  What else is in flight
+        does not matter, so that a job's result is the same alone and in a mix."""
+        least = job_bytes(prob, nsample=self.nsample)
+        tensors = _tensor_bytes(prob, 2, self.nsample)
+        full = max([256] + [sse.sse_plan(_desc(prob, pr, 2), prob.shifts()).workspace_bytes
+                            for pr in {self.prec, sse.FP64C64}])
+        full = max(full, least - tensors)
+        return (tensors + full, full) if tensors + full <= self.budget else (least, least - tensors)
+
     def run(self, jobs, log=None):
         import torch
         streams = [torch.cuda.Stream() for _ in range(self.slots)]
@@ -211,17 +227,18 @@ class Server:
     def _loop(self, pending, active, results, streams, free_streams, log):
         import torch
         used = 0
+        needs = {j.jid: self._need(j.prob) for j in pending}
         t0 = time.perf_counter()
         while pending or active:
             now = time.perf_counter() - t0
             # admission: first come first served, by budget and free slot
             while pending and free_streams and pending[0].arrival <= now:
-                need = job_bytes(pending[0].prob, nsample=self.nsample)
+                need, ws_bytes = needs[pending[0].jid]
                 if used + need > self.budget:
                     break
                 spec = pending.pop(0)
                 si = free_streams.pop(0)
-                a = _Active(spec, self.prec, streams[si], self.nsample, now)
+                a = _Active(spec, self.prec, streams[si], self.nsample, now, ws_bytes)
                 a.si, a.need = si, need
                 used += need
                 a.start_iteration()

@@ -59,3 +59,15 @@ def test_workspace_behind_a_word_gives_the_same_bits():
         got.append((dp.Sigma.clone(), Pi))
     for x, y in zip(*got):
         assert torch.equal(x.view(torch.int64), y.view(torch.int64))
+
+
+def test_served_job_with_room_for_the_direct_workspace_alone():
+    """A budget between a job's least and what its plans ask for: admitted, and checked."""
+    from paper_1912_08810_amd import serving, sse
+    prob = P(NA=100, NB=4, Norb=10, Nkz=5, Nqz=5, NE=200, Nw=20)
+    job = serving.make_jobs([prob], rate=1e6, seed=33, iterations=2)[0]
+    least = serving.job_bytes(prob)
+    assert serving.Server()._need(prob)[0] > 1.01 * least
+    srv = serving.Server(slots=1, budget_bytes=1.01 * least)
+    res = srv.run([job])
+    assert res[0].status == sse.OK and 0 < res[0].max_check_err <= 1e-5
