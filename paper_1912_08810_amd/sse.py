@@ -134,6 +134,13 @@ def make_desc(NA, NB, Norb, Nkz, Nqz, NE, Nw, ncomp=1, prec=FP64, alpha=1j, N3D=
                     int(dt_antiherm), alpha.real, alpha.imag)
 
 
+def direct_desc(desc):
+    """The same problem in the direct form: a chunk cap that cuts nothing asks for it."""
+    d = sse_desc.from_buffer_copy(desc)
+    d.chunk_taps = d.chunk_taps or 128
+    return d
+
+
 class Plan:
     """Owns an sse_plan_t; ``workspace_bytes`` is the device workspace of a call in the plan's
     form, ``direct_bytes`` the least that Sigma takes, in the direct form."""
@@ -167,15 +174,14 @@ class Plan:
     @property
     def direct_bytes(self) -> int:
         if self._direct is None:
-            # a chunk cap that cuts nothing asks for the direct form; a batch of one adds 256 bytes
-            descs = []
-            for d in self.descs:
-                c = sse_desc.from_buffer_copy(d)
-                c.chunk_taps = c.chunk_taps or 128
-                descs.append(c)
-            p = Plan(None, descs=descs, w_shifts=self._shifts)
-            self._direct = p.workspace_bytes - (0 if self.batch else 256)
+            p = Plan(None, descs=[direct_desc(d) for d in self.descs], w_shifts=self._shifts)
+            self._direct = p.workspace_bytes - (0 if self.batch else 256)  # a batch of one adds 256
         return self._direct
+
+    @property
+    def spectral(self) -> bool:
+        """Whether Sigma (of a single plan) takes the spectral form in workspace_bytes."""
+        return Plan(None, descs=self.descs, w_shifts=self._shifts).workspace_bytes != self.direct_bytes + 256
 
     def __del__(self):
         h = getattr(self, "handle", None)

@@ -71,3 +71,22 @@ def test_served_job_with_room_for_the_direct_workspace_alone():
     srv = serving.Server(slots=1, budget_bytes=1.01 * least)
     res = srv.run([job])
     assert res[0].status == sse.OK and 0 < res[0].max_check_err <= 1e-5
+
+
+def test_a_miss_of_the_spectral_form_is_recomputed_by_the_direct_kernel():
+    """Sigma of the fallback against the same job's direct binary64 result, bit for bit."""
+    import torch
+    from paper_1912_08810_amd import serving, sse
+    prob = P(NA=100, NB=4, Norb=10, Nkz=5, Nqz=5, NE=200, Nw=20)
+    assert sse.sse_plan(serving._desc(prob, sse.BF16X3, 2), prob.shifts()).spectral
+    job = serving.make_jobs([prob], rate=1e6, seed=35, iterations=1)[0]
+    srv = serving.Server(slots=1, tol=1e-12, keep_results=True)   # below the storage's rounding
+    res = srv.run([job])
+    assert res[0].status == sse.ERR_TOLERANCE and res[0].fallbacks == 1
+    dp = gu.DeviceProblem(prob, job.seed, ncomp=2, fp32=True)
+    for direct in (True, False):
+        desc = serving._desc(prob, sse.FP64C64, 2)
+        plan = sse.sse_plan(sse.direct_desc(desc) if direct else desc, prob.shifts())
+        ws = torch.empty(plan.workspace_bytes, dtype=torch.uint8, device="cuda")
+        sse.sse_compute(plan, dp.neigh, dp.dH, dp.G, dp.D, dp.Sigma, ws, torch.cuda.current_stream())
+        assert torch.equal(srv.sigma[job.jid].view(torch.int32), dp.Sigma.cpu().view(torch.int32)) == direct

@@ -31,3 +31,16 @@ def test_a_budget_below_the_spectral_workspace_gets_the_direct_one(prec):
     need, ws = serving.Server(prec=prec, budget_bytes=1.01 * least)._need(prob)
     assert need == least and ws >= sse.sse_plan(serving._desc(prob, prec, 2), prob.shifts()).direct_bytes
     assert ws < sse.sse_plan(serving._desc(prob, sse.FP64C64, 2), prob.shifts()).workspace_bytes
+
+
+def test_fallback_is_another_kernel_than_the_form_that_missed():
+    large, small = PROBS[0], PROBS[2]
+    for prec in (sse.FP32, sse.BF16X3, sse.FP64C64):
+        plan = sse.sse_plan(serving._desc(large, prec, 2), large.shifts())
+        assert plan.spectral
+        fb = serving._fallback_desc(large, plan, plan.workspace_bytes)
+        assert fb.prec == sse.FP64C64 and not sse.sse_plan(fb, large.shifts()).spectral
+        # in the direct form's workspace the fast plan runs that form, and the fallback is free
+        assert serving._fallback_desc(large, plan, plan.direct_bytes).chunk_taps == 0
+    plan = sse.sse_plan(serving._desc(small, sse.BF16X3, 2), small.shifts())
+    assert not plan.spectral and serving._fallback_desc(small, plan, plan.workspace_bytes).chunk_taps == 0
