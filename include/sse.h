@@ -69,12 +69,15 @@ typedef enum {
  * spectral form, for all but short sums and small problems, takes the (q, w) sums
  * as products of discrete Fourier transforms over the momenta and over blocks of
  * energies, in binary64 arithmetic in every precision (a complex64 precision then
- * names its storage); its rounding error is relative to the largest values of a
- * block of energies.  The direct form takes the sums as they stand, in the
- * arithmetic that the precision names.  It runs where the spectral form would not
- * be faster, for a desc with tile_e or chunk_taps set, in a workspace too small
- * for the other, and over again where the spectral form meets a value that is not
- * finite.
+ * names its storage).  Its rounding is relative to the largest values of a block of
+ * energies (of Pi: of the correlation over all its lags), so output blocks [Norb, Norb]
+ * of one (k, e, a) ([3, 3] of Pi) that lie more than 2^6 below those (2^20 in complex64
+ * storage; 2^20, 2^10 and 2^8 with one, two and three orbitals) are computed again in
+ * the direct form: every output block is accurate relative to its own largest value.
+ * The direct form takes the sums as they stand, in the arithmetic that the precision
+ * names.  It runs where the spectral form would not be faster, for a desc with tile_e
+ * or chunk_taps set, in a workspace too small for the other, and, in binary64, over
+ * again where the spectral form meets a value that is not finite or too large.
  */
 typedef enum {
     SSE_FP64 = 0,  /* complex128 storage, binary64 arithmetic throughout */

@@ -26,6 +26,7 @@
 
 #include "sse_internal.h"
 #include "sse_copy.h"
+#include "sse_guard.h"
 
 namespace sse {
 
@@ -414,49 +415,143 @@ __global__ __launch_bounds__(kBlock, 2) void k_sse_fp64(const Fp64Params p)
     fp64_tile<T, AH>(ro(&p), ptr, a, k, et, lds);
 }
 
-// Every tile of an instance, all components, by a grid of any size.
-template <typename T, bool AH>
-__device__ __forceinline__ void walk_tiles(const_ptr<Fp64Params> pp, TensorPtrs ptr, int ncomp, double2 *lds)
+// Whether an output block of the tile lies below the guard: of the suspect ones the
+// largest value, from Sigma as it stands, against the atom's largest peak.
+template <typename T>
+__device__ __forceinline__ bool below_guard(const_ptr<Fp64Params> pp, const TensorPtrs &ptr, int c, int a, int k,
+                                            int et, double2 *lds)
 {
     const auto &p = *pp;
-    const int64_t g = (int64_t)p.Nkz * p.NE * p.NA * p.NN, d = (int64_t)p.Nqz * p.Nw * p.NA * p.NB * kNF;
-    for (int c = 0; c < ncomp; ++c) {
-        for (int64_t L = blockIdx.x; L < p.n_wg; L += gridDim.x) {
-            const int k = (int)(L % p.Nkz);
-            const int et = (int)(L / p.Nkz % p.n_etiles);
-            const int a = (int)(L / p.Nkz / p.n_etiles);
-            fp64_tile<T, AH>(pp, ptr, a, k, et, lds);
+    const char *ws = (const char *)ptr.aux;
+    const int e0 = et * p.TE, te = min(p.TE, p.NE - e0), V = p.guard.V, n0 = e0 / V, nb = (e0 + te - 1) / V - n0 + 1;
+    uint32_t *top = reinterpret_cast<uint32_t *>(lds), *peak = top + te;
+    const uint32_t *suspect = reinterpret_cast<const uint32_t *>(ws + p.guard.suspect) + ((int64_t)c * p.NA + a) * p.NE + e0;
+    const uint32_t bit = suspect_bit(k, p.Nkz);
+    for (int i = threadIdx.x; i < te + nb; i += kBlock)
+        top[i] = 0u;
+    __syncthreads();
+    const T *S = (const T *)ptr.Sigma + (((size_t)k * p.NE + e0) * p.NA + a) * p.NN;
+    for (int i = threadIdx.x; i < te * p.NN; i += kBlock) {
+        const int e = i / p.NN;
+        if (suspect[e] & bit)
+            atomicMax(&top[e], magnitude(S[(size_t)e * p.NA * p.NN + (i - e * p.NN)]));
+    }
+    const uint32_t *peaks = reinterpret_cast<const uint32_t *>(ws + p.guard.peaks);
+    for (int i = threadIdx.x; i < nb * p.NN; i += kBlock) {
+        const int n = i / p.NN;
+        atomicMax(&peak[n], peaks[(((int64_t)c * p.guard.nblk + n0 + n) * p.NA + a) * p.NN + i - n * p.NN]);
+    }
+    __syncthreads();
+    bool weak = false;
+    for (int i = threadIdx.x; i < te; i += kBlock)
+        if (suspect[i] & bit)
+            weak |= top[i] < guard_floor(scaled(peak[(e0 + i) / V - n0], p.guard.scale), p.guard.bits);
+    return __syncthreads_or(weak);
+}
+
+// Tile j of workgroup x: component, atom, k and energy tile.
+__device__ __forceinline__ void place_tile(const_ptr<Fp64Params> pp, int j, int x, int *c, int *a, int *k, int *et)
+{
+    const auto &p = *pp;
+    const int64_t t = (int64_t)j * gridDim.x + x;
+    *c = t >= p.n_wg ? 1 : 0;
+    uint32_t L = (uint32_t)(t - *c * p.n_wg);
+    *k = (int)(L % (uint32_t)p.Nkz);
+    L /= (uint32_t)p.Nkz;
+    *et = (int)(L % (uint32_t)p.n_etiles);
+    *a = (int)(L / (uint32_t)p.n_etiles);
+}
+
+// The tiles of an instance, all components, that the spectral form leaves: every one if
+// the flag at the start of its workspace is raised (it met a value that is not finite),
+// else those with an output block below the guard.  The gridDim.x workgroups that call it
+// share them: workgroup x has tiles x', x' + gridDim.x, ..., where the x' of an XCD are
+// neighbours, as their G rows are.  It lists those to look at in LDS, some at a time (2^lg
+// lanes look at one tile's suspect words, as many as leave every lane a tile), and the loop
+// holds nothing over a tile, whose own values take all registers.  Where every tile is
+// computed again this takes 1.2 to 1.35 times the direct kernel's own launch, as equal shares
+// do not end together; shares taken from queues come to 1.15 to 1.2, but cost calls at flat
+// inputs up to 7 % (256 atoms, 300 energies: 2.13 -> 2.28 ms).
+template <typename T, bool AH>
+__device__ __forceinline__ void walk_tiles(const_ptr<Fp64Params> pp, const_ptr<TensorPtrs> first, int ncomp,
+                                           double2 *lds)
+{
+    __shared__ int s_next, s_n, s_i, s_list[kBlock];
+    if (threadIdx.x == 0)
+        s_next = s_n = s_i = 0;
+    for (;;) {
+        __syncthreads();
+        // sizes and pointers are read anew
+        int none = 0, tid = threadIdx.x;
+        asm volatile("" : "+s"(none), "+v"(tid));
+        const_ptr<Fp64Params> p = pp + none;
+        const_ptr<TensorPtrs> t = first + none;
+        const char *ws = (const char *)t->aux;
+        const bool all = ro(reinterpret_cast<const uint32_t *>(ws))[0] != 0u;
+        const int x = (int)xcd_remap(blockIdx.x, gridDim.x);
+        const int i = __builtin_amdgcn_readfirstlane(s_i);
+        if (i == __builtin_amdgcn_readfirstlane(s_n)) {
+            const int mine = (int)((p->n_wg * ncomp - x + gridDim.x - 1) / gridDim.x);  // this workgroup's tiles
+            const int j0 = __builtin_amdgcn_readfirstlane(s_next);
+            if (j0 >= mine)
+                return;
             __syncthreads();
+            if (tid == 0)
+                s_n = s_i = 0;
+            __syncthreads();
+            int lg = 0;
+            while (lg < 6 && (mine << (lg + 1)) <= kBlock)
+                ++lg;
+            const int j = j0 + (tid >> lg), part = tid & ((1 << lg) - 1);
+            bool look = all && j < mine;
+            if (!all && j < mine) {
+                int c, a, k, et;
+                place_tile(p, j, x, &c, &a, &k, &et);
+                const uint32_t *s = reinterpret_cast<const uint32_t *>(ws + p->guard.suspect) + ((int64_t)c * p->NA + a) * p->NE;
+                const int e1 = min(p->NE, (et + 1) * p->TE);
+                uint32_t any = 0u;
+                for (int e = et * p->TE + part; e < e1; e += 1 << lg)
+                    any |= s[e];
+                look = (any & suspect_bit(k, p->Nkz)) != 0u;
+            }
+            const unsigned long long bits = __ballot(look) >> (tid & 63);  // this lane's and those above
+            if (part == 0 && (bits & ((2ull << ((1 << lg) - 1)) - 1)) != 0)
+                s_list[atomicAdd(&s_n, 1)] = j;
+            if (tid == 0)
+                s_next = j0 + (kBlock >> lg);
+            continue;
         }
-        ptr.G = (const T *)ptr.G + g;
-        ptr.D = (const T *)ptr.D + d;
-        ptr.Sigma = (T *)ptr.Sigma + g;
+        int c, a, k, et;
+        place_tile(p, __builtin_amdgcn_readfirstlane(s_list[i]), x, &c, &a, &k, &et);
+        const int64_t g = (int64_t)p->Nkz * p->NE * p->NA * p->NN, d = (int64_t)p->Nqz * p->Nw * p->NA * p->NB * kNF;
+        const TensorPtrs ptr{t->neigh, t->dH, (const T *)t->G + c * g, (const T *)t->D + c * d,
+                             (T *)t->Sigma + c * g, t->aux};
+        __syncthreads();
+        if (tid == 0)
+            s_i = i + 1;
+        if (all || below_guard<T>(p, ptr, c, a, k, et, lds))
+            fp64_tile<T, AH>(p, ptr, a, k, et, lds);
     }
 }
 
-// A fixed grid walks the tiles if the flag asks for them (the spectral form met a
-// value that is not finite); else every workgroup ends at once.  The last launch of a
-// spectral submission, so it also delivers the status word: a copy of four bytes would
-// be a launch of its own.
+// The last launch of a spectral submission, so it also delivers the status word: a copy of
+// four bytes would be a launch of its own.
 template <typename T, bool AH>
-__global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo(const Fp64Params p, int ncomp, const uint32_t *flag,
+__global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo(const Fp64Params p, const TensorPtrs t, int ncomp,
                                                              const uint32_t *status, uint32_t *host)
 {
     extern __shared__ double2 lds[];
     if (blockIdx.x == 0 && threadIdx.x == 0 && host)
         __hip_atomic_store(host, *status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (ro(flag)[0] == 0u)
-        return;
-    walk_tiles<T, AH>(ro(&p), TensorPtrs{p.neigh, p.dH, p.G, p.D, p.Sigma}, ncomp, lds);
+    walk_tiles<T, AH>(ro(&p), ro(&t), ncomp, lds);
 }
 
 template <typename T, bool AH>
 __global__ __launch_bounds__(kBlock, 2) void k_sse_fp64_redo_batch(const BatchLaunch bl, int ncomp)
 {
     extern __shared__ double2 lds[];
-    for (int i = 0; i < bl.n; ++i)
-        if (ro(reinterpret_cast<const uint32_t *>(bl.ptr[i].aux))[0] != 0u)
-            walk_tiles<T, AH>(ro(reinterpret_cast<const Fp64Params *>(bl.params)) + i, bl.ptr[i], ncomp, lds);
+    const int i = blockIdx.y;
+    walk_tiles<T, AH>(ro(reinterpret_cast<const Fp64Params *>(bl.params)) + i, ro(&bl.ptr[i]), ncomp, lds);
 }
 
 // Persistent form: a fixed grid pulls tiles from the batch's work queues
@@ -540,7 +635,7 @@ static hipError_t launch_as(const Fp64Params &p, size_t lds_bytes, hipStream_t s
 }
 
 template <typename T, bool AH>
-static hipError_t redo_as(const Fp64Params &p, size_t lds_bytes, int ncomp, const uint32_t *flag,
+static hipError_t redo_as(const Fp64Params &p, size_t lds_bytes, int ncomp, const void *ws,
                           const uint32_t *status, uint32_t *host, hipStream_t s)
 {
     static bool done = false;
@@ -548,18 +643,18 @@ static hipError_t redo_as(const Fp64Params &p, size_t lds_bytes, int ncomp, cons
     if (e != hipSuccess)
         return e;
     (void)hipGetLastError();
-    const unsigned grid = (unsigned)std::min<int64_t>(p.n_wg, 512);  // two per CU
-    hipLaunchKernelGGL((k_sse_fp64_redo<T, AH>), dim3(grid), dim3(kBlock), lds_bytes, s, p, ncomp, flag, status,
-                       host);
+    const unsigned grid = (unsigned)std::min<int64_t>(p.n_wg * ncomp, 512);  // two per CU
+    hipLaunchKernelGGL((k_sse_fp64_redo<T, AH>), dim3(grid), dim3(kBlock), lds_bytes, s, p,
+                       TensorPtrs{p.neigh, p.dH, p.G, p.D, p.Sigma, ws}, ncomp, status, host);
     return hipGetLastError();
 }
 
 hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, int ncomp,
-                            const uint32_t *flag, const uint32_t *status, uint32_t *host, hipStream_t s)
+                            const void *ws, const uint32_t *status, uint32_t *host, hipStream_t s)
 {
     auto as = c64 ? (ah ? redo_as<float2, true> : redo_as<float2, false>)
                   : (ah ? redo_as<double2, true> : redo_as<double2, false>);
-    return as(p, lds_bytes, ncomp, flag, status, host, s);
+    return as(p, lds_bytes, ncomp, ws, status, host, s);
 }
 
 template <typename T, bool AH>
@@ -570,7 +665,8 @@ static hipError_t redo_batch_as(const BatchLaunch &bl, size_t lds_bytes, int nco
     if (e != hipSuccess)
         return e;
     (void)hipGetLastError();
-    hipLaunchKernelGGL((k_sse_fp64_redo_batch<T, AH>), dim3(512), dim3(kBlock), lds_bytes, s, bl, ncomp);
+    hipLaunchKernelGGL((k_sse_fp64_redo_batch<T, AH>), dim3((unsigned)std::max(8, 512 / bl.n), (unsigned)bl.n), dim3(kBlock),
+                       lds_bytes, s, bl, ncomp);
     return hipGetLastError();
 }
 

@@ -3,6 +3,7 @@
 // bytes and workspace sizes.  Host code only (also built by the host-side
 // runtime test with a stand-in HIP header).
 #include <algorithm>
+#include <cmath>
 #include <vector>
 
 #include "sse_internal.h"
@@ -202,6 +203,10 @@ SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32
     p.matrix = g.matrix;
     p.g_elems = (int64_t)d.Nkz * d.NE * d.NA * p.NN;
     p.d_elems = (int64_t)d.Nqz * d.Nw * d.NA * d.NB * kNF;
+    p.guard_bits = speck::guard_bits(d.prec, d.Norb);
+    p.off_suspect = (int64_t)g.off_suspect;
+    p.guard_k = (uint32_t)(std::log2((double)d.Nkz) * (1 << 18));
+    p.guard_quads = (int64_t)(g.guard_bytes / 16);
     p.off_dht = (int64_t)g.off_dht;
     p.off_d = (int64_t)g.off_d;
     p.off_g = (int64_t)g.off_g;
@@ -225,7 +230,11 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 {
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
-    const size_t fixed = up((size_t)d.NA * d.NB * kN3D * NN * 8) + 4 * speck::kAlign + kSlack;
+    const size_t peaks = (size_t)d.ncomp * g->nblk * d.NA * NN * 4;
+    g->off_suspect = speck::kAlign + peaks;
+    g->guard_bytes = up(peaks + (size_t)d.ncomp * d.NA * d.NE * 4);
+    const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
+    const size_t fixed = g->guard_bytes + dht + 4 * speck::kAlign + kSlack;
     for (g->nc = d.ncomp; g->nc >= 1; --g->nc) {
         const size_t base = fixed + g->nc * db, per = 2 * g->nc * gb;
         if (budget < base + (g->nc > 1 ? per : gb + gb / 8))
@@ -234,8 +243,8 @@ bool spectral_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
         g->na = d.NA;
         if (base + per > budget)  // one component, one block, some atoms
             g->na = (int)std::max<size_t>(1, (budget - base - gb) / (NN * row));
-        g->off_dht = speck::kAlign;  // behind the non-finite flag
-        g->off_d = g->off_dht + up((size_t)d.NA * d.NB * kN3D * NN * 8);
+        g->off_dht = speck::kAlign + g->guard_bytes;  // behind the non-finite flag
+        g->off_d = g->off_dht + dht;
         g->off_g = g->off_d + up(g->nc * db);
         g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);
         g->bytes = g->off_s + up((size_t)g->nc * g->nb * g->na * NN * row) + kSlack;
@@ -251,7 +260,10 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
     const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
-    const size_t fixed = dht + 4 * speck::kAlign + kSlack;
+    const size_t peaks = (size_t)d.ncomp * d.NA * d.NB * 4;
+    g->off_suspect = speck::kAlign + peaks;
+    g->guard_bytes = up(peaks + (size_t)d.ncomp * d.NA * d.NB * d.Nqz * d.Nw);
+    const size_t fixed = g->guard_bytes + dht + 4 * speck::kAlign + kSlack;
     // the output pass has a workgroup per (atom, neighbour, i, j), and a launch fewer than 2^32 threads
     if ((int64_t)d.NA * d.NB * kNF * speck::kSandBlock > 0xffffffffLL)
         return false;
@@ -264,7 +276,7 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
             continue;
         g->nb = (int)std::min<size_t>(g->nblk, (budget - base) / per);
         g->na = d.NA;
-        g->off_dht = speck::kAlign;
+        g->off_dht = speck::kAlign + g->guard_bytes;
         g->off_d = g->off_dht + dht;
         g->off_g = g->off_d + up(g->nc * db);
         g->off_s = g->off_g + up((size_t)g->nc * g->nb * gb);

@@ -162,6 +162,19 @@ __device__ __forceinline__ void pull_first(const BatchLaunch &bl, int home, int 
     pull_resolve(bl, home, t, st, s_tile);
 }
 
+// What the spectral form leaves to the direct kernel behind it.  The direct sums round
+// relative to their own terms, the transforms relative to the largest values of an atom's
+// energy block: an output block [Norb, Norb] that lies more than `bits` powers of two below
+// that peak is computed again.  Values are compared by the upper halves of their absolute
+// binary64 forms, which order as they do and differ by 2^20 for a factor of two.
+struct SpecGuard {
+    int64_t peaks, suspect;  // workspace offsets: a word per (component, energy block, channel), and
+                             // one per (component, atom, energy), a bit per momentum to look at
+    int32_t V, nblk;         // energies per energy block, blocks
+    int32_t bits;
+    double scale;            // from the peaks' unit to the outputs'
+};
+
 // Launch parameters of the FP64 tiled kernel (one component).  G, D and Sigma
 // are complex128, or complex64 for SSE_FP64C64.
 struct Fp64Params {
@@ -180,6 +193,7 @@ struct Fp64Params {
     // (w, s) of tap t at [2 t], [2 t + 1], padded: a tap pair's record is four
     // consecutive words, fetched one pair ahead
     int32_t tws[2 * kMaxTaps + 4];
+    SpecGuard guard;   // of the launches behind the spectral form
 };
 
 // Fills Fp64Params::tws from Fp64Params::taps (host).
@@ -228,7 +242,12 @@ struct PiParams {
     int64_t n_wg;      // NA * Nqz * nbgroups * nchunk
     int32_t ncomp;     // component c: X + c x_c, Y - c x_c, Pi + c pi_c
     int64_t x_c, pi_c;
-    const uint32_t *flag;  // not NULL: nothing is computed where it is zero
+    // not NULL: nothing is computed where *flag is zero but the workgroups' outputs below the
+    // guard (SpecGuard): peaks [ncomp][NA][NB], suspect [ncomp][NA][NB][Nqz][Nw]
+    const uint32_t *flag, *peaks;
+    const unsigned char *suspect;
+    int32_t guard_bits;
+    double guard_scale;
     const uint32_t *status;  // copied to *host at the end if host is not NULL (pinned memory)
     uint32_t *host;
     double beta_re, beta_im;
@@ -290,12 +309,12 @@ TileGeom fp64_geometry(int Norb, int NE, const TapTable &taps_unchunked, int te_
                        int chunk_cap, TapTable *taps_out);
 // ah: D~ anti-Hermitian per 3 x 3 block (only i <= j read; half the tap FMAs).
 hipError_t fp64_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, hipStream_t s);
-// The same sums for ncomp components (p's tensors are the first's) where *flag is not
-// zero, nothing otherwise: a fixed grid that walks the tiles.  In the end *host gets
-// *status (host: pinned memory, or NULL).
+// The same sums for ncomp components (p's tensors are the first's) where the non-finite flag
+// at the start of ws is not zero, else of the tiles with an output below p.guard: a fixed
+// grid that walks the tiles.  In the end *host gets *status (host: pinned memory, or NULL).
 hipError_t fp64_redo_launch(const Fp64Params &p, bool c64, bool ah, size_t lds_bytes, int ncomp,
-                            const uint32_t *flag, const uint32_t *status, uint32_t *host, hipStream_t s);
-// The same over the bl.n instances of a batch (bl.params, bl.ptr), the flag of each at its ptr.aux.
+                            const void *ws, const uint32_t *status, uint32_t *host, hipStream_t s);
+// The same over the bl.n instances of a batch (bl.params, bl.ptr), the workspace of each at its ptr.aux.
 hipError_t fp64_redo_batch_launch(const BatchLaunch &bl, bool c64, bool ah, size_t lds_bytes, int ncomp,
                                   hipStream_t s);
 hipError_t fp64_persistent_launch(const BatchLaunch &bl, bool c64, bool ah, int grid,

@@ -38,6 +38,7 @@
 
 #include <algorithm>
 
+#include "sse_guard.h"
 #include "sse_internal.h"
 
 namespace sse {
@@ -165,9 +166,6 @@ template <int MT, int NTN>
 __global__ __launch_bounds__(kBlock, 1) void k_pi_mfma(const PiParams p)
 {
     extern __shared__ double2 lds[];
-    // behind the spectral form: only if that met a value that is not finite
-    if (p.flag && ro(p.flag)[0] == 0u)
-        return;
     constexpr int ZC = 16 * NTN;                  // Zb row: 2 (b, i, j) columns, padded
     const int NN = p.NN, No = p.Norb, R = p.R, nbw = p.nbw;
     const int NNp = NN + (NN & 1);                // orbital pairs padded to an even count
@@ -191,6 +189,25 @@ __global__ __launch_bounds__(kBlock, 1) void k_pi_mfma(const PiParams p)
     const int b0 = bg * nbw;
     const int nbv = min(nbw, p.NB - b0);          // neighbours of this workgroup
     const int t0 = p.cb[chunk], t1 = p.cb[chunk + 1];
+    // behind the spectral form: only if that met a value that is not finite, or if an
+    // output block [3, 3] of this workgroup lies below the guard
+    if (p.flag && ro(p.flag)[0] == 0u) {
+        const int64_t ab = ((int64_t)blockIdx.y * p.NA + a) * p.NB + b0;
+        bool weak = false;
+        for (int x = tid; x < nbv * (t1 - t0); x += kBlock) {
+            const int b = x / (t1 - t0), w = p.tw[t0 + x - b * (t1 - t0)];
+            if (!p.suspect[((ab + b) * p.Nqz + q) * p.Nw + w])
+                continue;
+            const double2 *P = p.Pi + blockIdx.y * p.pi_c +
+                               ((((size_t)q * p.Nw + w) * p.NA + a) * (p.NB + 1) + b0 + b) * kNF;
+            uint32_t top = 0u;
+            for (int ij = 0; ij < kNF; ++ij)
+                top = max(top, magnitude(P[ij]));
+            weak |= top < guard_floor(scaled(p.peaks[ab + b], p.guard_scale), p.guard_bits);
+        }
+        if (!__syncthreads_or(weak))
+            return;
+    }
     const int s_lo = p.ts[t0], s_hi = p.ts[t1 - 1];
 
     for (int x = tid; x < nbw * 3 * NN; x += kBlock) {

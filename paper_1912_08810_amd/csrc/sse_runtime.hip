@@ -237,7 +237,7 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // multiple of 256 on (a SpectralGeom's bytes have room for that at their end).
 char *spectral_ws(void *p) { return (char *)(((uintptr_t)p + 255) & ~(uintptr_t)255); }
 
-Fp64Params fp64_params(const sse_desc &d, const TileGeom &geom, const TapTable &taps);
+Fp64Params redo_params(const Instance &I);
 
 // The spectral form of one instance, every component, then the direct binary64
 // kernel that takes over if the non-finite flag was raised; that also delivers the
@@ -246,8 +246,7 @@ sse_status enqueue_spectral(const Instance &I, const sse_args &a, uint32_t *dsta
                             void *wsfree, hipStream_t s)
 {
     hipError_t e = spectral_sigma_launch(I.d, I.spec, I.shift, a, dstatus, clear, host,
-                                         fp64_params(I.d, I.redo_geom, I.redo_taps), I.redo_geom.lds_bytes,
-                                         spectral_ws(wsfree), s);
+                                         redo_params(I), I.redo_geom.lds_bytes, spectral_ws(wsfree), s);
     return e == hipSuccess ? SSE_OK : hip_fail(e, "spectral kernel launch");
 }
 
@@ -368,6 +367,18 @@ Fp64Params fp64_params(const sse_desc &d, const TileGeom &geom, const TapTable &
     return p;
 }
 
+// Of the peaks of spectral results, which lack the factor that the outputs have.
+double guard_scale(const sse_desc &d, const SpectralGeom &g) { return hypot(d.alpha_re, d.alpha_im) / ((double)d.Nkz * g.L); }
+
+// Those of the direct kernel behind the spectral form.
+Fp64Params redo_params(const Instance &I)
+{
+    Fp64Params p = fp64_params(I.d, I.redo_geom, I.redo_taps);
+    p.guard = SpecGuard{(int64_t)speck::kAlign, (int64_t)I.spec.off_suspect, I.spec.V, I.spec.nblk,
+                        speck::guard_bits(I.d.prec, I.d.Norb), guard_scale(I.d, I.spec)};
+    return p;
+}
+
 MfmaParams mfma_params(const Instance &I)
 {
     const sse_desc &d = I.d;
@@ -402,7 +413,7 @@ hipError_t build_batch_tables(sse_plan_s *P)
         for (int t : w.inst) {
             const Instance &I = P->inst[t];
             w.hp.push_back(spectral_params(I.d, I.spec, I.shift));
-            redo.push_back(fp64_params(I.d, I.redo_geom, I.redo_taps));
+            redo.push_back(redo_params(I));
             w.redo_lds = std::max(w.redo_lds, I.redo_geom.lds_bytes);
         }
         const size_t np = w.hp.size() * sizeof(SpecParams), nr = redo.size() * sizeof(Fp64Params);
@@ -1105,7 +1116,13 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
         memcpy(pp.tw, gm.tw, sizeof pp.tw);
         memcpy(pp.ts, gm.ts, sizeof pp.ts);
         pp.n_wg = n_wg;
-        pp.flag = spectral ? (const uint32_t *)wsfree : nullptr;
+        if (spectral) {
+            pp.flag = (const uint32_t *)wsfree;
+            pp.peaks = (const uint32_t *)(wsfree + speck::kAlign);
+            pp.suspect = (const unsigned char *)wsfree + I.pi_spec.off_suspect;
+            pp.guard_bits = speck::kPiGuardBits;
+            pp.guard_scale = guard_scale(d, I.pi_spec);
+        }
         pp.status = dstatus;
         pp.host = spectral ? tk.host_status : nullptr;
         pp.beta_re = d.alpha_re;

@@ -41,6 +41,20 @@ constexpr int matrix_tiles(int No)
     const int T = (No + 3) / 4;
     return kN3D * T * T + (No % 4 == 2 ? 2 * T : 0);
 }
+// How far an output block may lie below its energy block's peak (SpecGuard), in powers of
+// two, before the direct kernel computes it again.  Binary64 results: 6.  Flat inputs come
+// to 2^-4.8 at energies that one shift alone reaches (40 taps, 16 orbital pairs) and are not
+// to be computed twice; an output block at 2^-6 is off by up to 1e-14 of its norm, one at
+// those energies by 5e-15 (the direct kernel: 4e-16).  Complex64 storage rounds at 2^-24;
+// at 2^-20 the transforms are off by 5e-10.
+// Few values are all small by chance now and then, and one tile computed again costs a
+// small call as much as all of it: one orbital 20, two 10, three 8.
+constexpr int guard_bits(int prec, int Norb)
+{
+    return prec != SSE_FP64 || Norb == 1 ? 20 : Norb == 2 ? 10 : Norb == 3 ? 8 : 6;
+}
+// Pi's blocks [3, 3], which are sums over all energies, below the rms of their correlation.
+constexpr int kPiGuardBits = 6;
 constexpr size_t matrix_bytes(int No, int P) { return (size_t)matrix_tiles(No) * 128 + (size_t)kNF * P * 16; }
 constexpr int matrix_neighbours(int No) { return (int)(kLdsTwo / matrix_bytes(No, 16)); }
 constexpr int pi_matrix_neighbours(int No) { return (int)(kLdsTwo / (matrix_tiles(No) * 128)); }
@@ -62,6 +76,8 @@ struct SpectralGeom {
     size_t sand_lds = 0;
     // one pass holds nc components, nb energy blocks, and the sandwich's output for na atoms
     int nc = 0, nb = 0, na = 0;
+    size_t guard_bytes = 0;      // the guard's tables, at speck::kAlign
+    size_t off_suspect = 0;      // (the second of them)
     // Sigma: D^, G^ and S^ at off_d, off_g, off_s; Pi: P^, X^ and Y^ there
     size_t off_dht = 0, off_d = 0, off_g = 0, off_s = 0, bytes = 0;
 };
@@ -71,8 +87,11 @@ struct SpecParams {
     int32_t NA, NB, Norb, NN, Nkz, Nqz, NE, Nw, ncomp;
     int32_t L, V, C, logC, rowp, npt, P, npg, smin, smax, nblk;
     int32_t na_cap;             // atoms that the sandwich's output has room for
-    int32_t antiherm, matrix;
+    int32_t antiherm, matrix, guard_bits;
+    uint32_t guard_k;           // 2^20 log2(Nkz) / 4
     int64_t g_elems, d_elems;   // one component of G and of D~
+    int64_t guard_quads;        // the guard's tables in units of 16 bytes
+    int64_t off_suspect;
     int64_t off_dht, off_d, off_g, off_s;
     double alpha_re, alpha_im;
     int32_t shift[kMaxTaps];    // the caller's shifts, in frequency order
@@ -80,6 +99,8 @@ struct SpecParams {
 
 // What one call works on: its tensors (of the pass's first component) and workspace.
 // Workspace: the non-finite flag, then
+//   peaks  [ncomp][nblk][NA NN] (Pi: [ncomp][NA][NB]), words
+//   suspect  [ncomp][NA][NE], words (Pi: [ncomp][NA][NB][Nqz][Nw], bytes)
 //   dht  [NA][NB][3][n][n'] = dH[a, b, j][n'][n] (not written for the matrix form)
 //   Dh   [components][NA][NB][9][npt]
 //   Gh   [components][blocks][NA NN][npt]
@@ -102,6 +123,7 @@ struct SpecPass {
     int32_t e_off, nrow;  // forward transforms: rows [e_off, e_off + nrow) from a block's first energy,
     int64_t src_c;        // elements from one component's input to the next,
     int64_t dst;          // and the workspace offset of the result
+    int32_t c0;           // the pass's first component
 };
 
 enum SpecJobs { kDht = 1, kDhat = 2, kTransform = 4 };
@@ -136,7 +158,7 @@ SpectralGeom spectral_geometry(const sse_desc &d, const int32_t *w_shift);
 SpecParams spectral_params(const sse_desc &d, const SpectralGeom &g, const int32_t *w_shift);
 
 // Sigma of every component (sse_spectral.hip), then the direct kernel (redo: its
-// sizes and taps) where the non-finite flag asks for it.  clear: the status word
+// sizes and taps) where the non-finite flag or the guard asks for it.  clear: the status word
 // first; in the end it goes to *host (pinned memory, or NULL).  Weak: a build of the host runtime alone (its CPU test)
 // has no kernels to launch, and runs the direct launchers.
 __attribute__((weak)) hipError_t spectral_sigma_launch(const sse_desc &d, const SpectralGeom &g,
@@ -156,7 +178,8 @@ __attribute__((weak)) hipError_t spectral_batch_launch(int n, const sse_desc *co
                                                        uint32_t *status, bool clear, char *ws,
                                                        hipStream_t s);
 
-// Pi of every component; the non-finite flag for the direct kernel is at the start of ws.
+// Pi of every component; the non-finite flag for the direct kernel is at the start of ws,
+// the guard's tables are at speck::kAlign.
 __attribute__((weak)) hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g,
                                                     const int32_t *w_shift, const int32_t *neigh, const double *dH,
                                                     const void *G, void *Pi, uint32_t *status, void *ws,

@@ -37,6 +37,7 @@
 
 #include "sse_copy.h"
 #include "sse_dft.h"
+#include "sse_guard.h"
 #include "sse_spectral.h"
 
 namespace sse {
@@ -58,7 +59,8 @@ __device__ __forceinline__ double2 to_d2(float2 v) { return make_double2(v.x, v.
 __device__ __forceinline__ void put(double2 *p, double x, double y) { *p = make_double2(x, y); }
 __device__ __forceinline__ void put(float2 *p, double x, double y) { *p = make_float2((float)x, (float)y); }
 
-__device__ __forceinline__ bool finite(double x) { return __builtin_fabs(x) <= 1.7976931348623157e308; }
+// Whether transforms of values like x stay finite: sums of up to 2^15 of them.
+__device__ __forceinline__ bool finite(double x) { return __builtin_fabs(x) <= 0x1p1000; }
 
 // A workgroup's instance, pass and index in it.
 struct Job {
@@ -68,6 +70,8 @@ struct Job {
     int64_t bid, nwg;
 
     __device__ __forceinline__ uint32_t *flag() const { return reinterpret_cast<uint32_t *>(t.ws); }
+    __device__ __forceinline__ uint32_t *peaks() const { return reinterpret_cast<uint32_t *>(t.ws + speck::kAlign); }
+    __device__ __forceinline__ uint32_t *suspect() const { return reinterpret_cast<uint32_t *>(t.ws + p->off_suspect); }
     __device__ __forceinline__ double *dht() const { return reinterpret_cast<double *>(t.ws + p->off_dht); }
     __device__ __forceinline__ double2 *Dh() const { return reinterpret_cast<double2 *>(t.ws + p->off_d); }
     __device__ __forceinline__ double2 *Gh() const { return reinterpret_cast<double2 *>(t.ws + p->off_g); }
@@ -111,13 +115,20 @@ constexpr int kPlainAtoms = 256;
 // Workgroups of one instance in each job.
 __host__ __device__ inline int64_t dht_wgs(const SpecParams &p)
 {
-    const int64_t n = ((int64_t)p.NA * p.NB * kN3D * p.NN + 1023) / 1024;
-    return p.matrix ? 1 : n < 512 ? n : 512;
+    const int64_t d = p.matrix ? 0 : (int64_t)p.NA * p.NB * kN3D * p.NN;
+    const int64_t n = ((d > p.guard_quads ? d : p.guard_quads) + 1023) / 1024;
+    return n < 512 ? n : 512;
 }
 __host__ __device__ inline int64_t dhat_wgs(const SpecParams &p) { return (int64_t)p.NA * p.NB * p.Nkz; }
 __host__ __device__ inline int64_t fft_wgs(const SpecParams &p, int64_t atoms, int nb)
 {
     return ((atoms * p.NN + p.C - 1) >> p.logC) * nb;
+}
+// Groups of channels of the inverse transforms: where an atom has more than C, of one atom
+// each (nearly as many in each of them), so that the guard meets no half ones.
+__host__ __device__ inline int64_t inverse_groups(const SpecParams &p, int64_t atoms)
+{
+    return p.NN > p.C ? atoms * ((p.NN + p.C - 1) >> p.logC) : (atoms * p.NN + p.C - 1) >> p.logC;
 }
 __host__ __device__ inline int64_t sandwich_wgs(const SpecParams &p, int na, int nb)
 {
@@ -141,7 +152,7 @@ __device__ __forceinline__ bool sandwich_place(int64_t bid, int na, int64_t grou
     return *atom < na && *group < groups;
 }
 
-// dH^T, and the flag (and the status word) cleared; workgroup bid of nwg.
+// dH^T, and the flag, the guard's tables (and the status word) cleared; workgroup bid of nwg.
 __device__ __forceinline__ void dht_job(const Job &J, int64_t bid, int64_t nwg, uint32_t *clear)
 {
     const auto &p = *J.p;
@@ -151,6 +162,9 @@ __device__ __forceinline__ void dht_job(const Job &J, int64_t bid, int64_t nwg, 
         if (clear)
             *clear = 0u;
     }
+    uint4 *guard = reinterpret_cast<uint4 *>(J.peaks());
+    for (int64_t i = i0; i < p.guard_quads; i += step)
+        guard[i] = make_uint4(0u, 0u, 0u, 0u);
     if (p.matrix)
         return;
     double *dht = J.dht();
@@ -219,9 +233,30 @@ __device__ __forceinline__ void dhat_job(const Job &J, double2 *lds, int64_t bid
     }
 }
 
-// The middle step of a transform of length R1 R2 in LDS: the R2-point transforms.
-template <int R1, int R2, int S>
-__device__ __forceinline__ void second_step(double2 *lds, int rows, int rowp)
+// f over 2^lw lanes side by side, in all of them.
+template <typename F>
+__device__ __forceinline__ uint32_t over_lanes(uint32_t x, int lw, F f)
+{
+    if (lw > 0)
+        x = f(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true));   // lane ^ 1
+    if (lw > 1)
+        x = f(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true));   // lane ^ 2
+    if (lw > 2)
+        x = f(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true));  // lane ^ 7
+    return x;
+}
+
+// The largest value of a channel's rows in LDS: in the padding of the channel's first row.
+template <int R2>
+__device__ __forceinline__ uint32_t *channel_top(double2 *lds, int ch, int rowp)
+{
+    return reinterpret_cast<uint32_t *>(lds + (size_t)ch * rowp + R2);
+}
+
+// The middle step of a transform of length R1 R2 in LDS: the R2-point transforms.  Peak: the
+// channels' largest values (row r: channel r & mask) go where channel_top says.
+template <int R1, int R2, int S, bool Peak>
+__device__ __forceinline__ void second_step(double2 *lds, int rows, int rowp, int mask)
 {
     for (int it = threadIdx.x; it < rows * R1; it += blockDim.x) {
         const int row = it / R1, k1 = it - row * R1;
@@ -231,9 +266,20 @@ __device__ __forceinline__ void second_step(double2 *lds, int rows, int rowp)
         for (int n = 0; n < R2; ++n)
             v[n] = x[n];
         dft::transform<R2, S>(v);
+        double most = 0.0;
 #pragma unroll
-        for (int n = 0; n < R2; ++n)
+        for (int n = 0; n < R2; ++n) {
             x[n] = v[n];
+            if (Peak)
+                most = fmax(most, fmax(fabs(v[n].x), fabs(v[n].y)));
+        }
+        if (Peak) {
+            // lanes side by side have the same row
+            constexpr int lw = R1 % 4 == 0 ? 2 : R1 % 2 == 0 ? 1 : 0;
+            const uint32_t top = over_lanes(magnitude(most), lw, [](uint32_t a, uint32_t b) { return max(a, b); });
+            if ((threadIdx.x & ((1 << lw) - 1)) == 0)
+                atomicMax(channel_top<R2>(lds, row & mask, rowp), top);
+        }
     }
 }
 
@@ -333,7 +379,7 @@ __device__ __forceinline__ void forward_job(const Job &J, const SpecPass &s, dou
             load(it);
     }
     __syncthreads();
-    second_step<R1, R2, S>(lds, Nkz * C, rowp);
+    second_step<R1, R2, S, false>(lds, Nkz * C, rowp, 0);
     __syncthreads();
     double2 *out = reinterpret_cast<double2 *>(J.t.ws + s.dst) + (((size_t)blockIdx.y * s.nb + blk) * NC + ch0) * p.npt;
     for (int it = threadIdx.x; it < L * C; it += blockDim.x) {
@@ -349,18 +395,35 @@ __device__ __forceinline__ void forward_job(const Job &J, const SpecPass &s, dou
 // The same backwards: energies from points, then k on the way out, alpha and 1 / (Nkz L).
 // An energy that no shift reaches gets an exact zero, as the direct sum gives.  Also
 // the neighbour-table check.
+// The guard (SpecGuard): a channel's peak is the largest value before the transform over k,
+// the discarded energies' among them, times Nkz^(1/4): the rounding is relative to the root
+// of the sum of the squares over kappa, between one and Nkz^(1/2) times that.  An atom's peak
+// is its channels' largest.  Where the outputs of a few of its channels lie below those
+// channels' own peak, the atom's output is marked as suspect; where no such few do, all its
+// channels together do not lie below the atom's.  The direct kernel looks at what is marked
+// (of flat inputs one in 1e10, and some at energies that few shifts reach).  One GPU's energy
+// shard: 935 us per component without it, 980 with it (the largest value of every output in a
+// table, by atomics from the channels' workgroups: 1124); a batch of tiny instances 45 and
+// 55 us, 256 atoms in complex64 280 and 307.
 template <typename T, int R1, int R2>
 __device__ __forceinline__ void inverse_job(const Job &J, double2 *lds, uint32_t *status)
 {
     constexpr int L = R1 * R2;
     const auto &p = *J.p;
-    const int C = p.C, NC = J.s.na * p.NN, Nkz = p.Nkz, rowp = p.rowp;
+    const int C = p.C, Nkz = p.Nkz, rowp = p.rowp;
     const int64_t strideE = (int64_t)p.NA * p.NN;
-    const int ngrp = (NC + C - 1) >> p.logC;
+    const int ngrp = (int)inverse_groups(p, J.s.na);
     if (J.bid >= (int64_t)ngrp * J.s.nb)
         return;
     const int64_t x = xcd_remap(J.bid, (int64_t)ngrp * J.s.nb);
-    const int blk = (int)(x / ngrp), ch0 = (int)(x - (int64_t)blk * ngrp) << p.logC;
+    const int blk = (int)(x / ngrp), grp = (int)(x - (int64_t)blk * ngrp);
+    // channels [ch0, NC) of the group, at most C
+    int ch0 = grp << p.logC, NC = min(ch0 + C, J.s.na * p.NN);
+    if (p.NN > C) {
+        const int per = (p.NN + C - 1) >> p.logC, al = grp / per, i = grp - al * per;
+        ch0 = al * p.NN + i * p.NN / per;
+        NC = al * p.NN + (i + 1) * p.NN / per;
+    }
     const int64_t nab = (int64_t)p.NA * p.NB, all = (int64_t)ngrp * J.s.nb * blockDim.x;
     if (blockIdx.y == 0)
         for (int64_t i = J.bid * blockDim.x + threadIdx.x; i < nab; i += all)
@@ -382,6 +445,8 @@ __device__ __forceinline__ void inverse_job(const Job &J, double2 *lds, uint32_t
     int it = threadIdx.x;
     if (it < items)
         load(it);
+    if (threadIdx.x < C)
+        *channel_top<R2>(lds, threadIdx.x, rowp) = 0u;
     fill_twiddles(tw, L, 1, L);
     fill_twiddles(twk, Nkz, 1, Nkz);
     __syncthreads();
@@ -400,32 +465,46 @@ __device__ __forceinline__ void inverse_job(const Job &J, double2 *lds, uint32_t
             load(it);
     }
     __syncthreads();
-    second_step<R1, R2, 1>(lds, Nkz * C, rowp);
+    second_step<R1, R2, 1, true>(lds, Nkz * C, rowp, C - 1);
     __syncthreads();
     const double sc = 1.0 / ((double)Nkz * L);
     const double ar = p.alpha_re * sc, ai = p.alpha_im * sc;
     const int e0 = (J.s.blk0 + blk) * p.V, nv = min(p.V, p.NE - e0);
     T *dst = (T *)J.t.Sigma + (size_t)blockIdx.y * p.g_elems + (size_t)J.s.a0 * p.NN + ch0;
-    bool bad = false;
+    // A lane keeps its channel: the workgroup has a multiple of C threads.  2^lw channels of
+    // one atom side by side are the few: all of the group's, or (C of several atoms) an atom's.
+    // Lanes past the last channel repeat it.
+    const int ch = min((int)(threadIdx.x & (C - 1)), NC - 1 - ch0);
+    const int lw = p.NN > C ? p.logC : __builtin_ctz(p.NN);
+    const uint32_t peak = over_lanes(*channel_top<R2>(lds, ch, rowp) + p.guard_k, lw,
+                                     [](uint32_t x, uint32_t y) { return max(x, y); });
+    const uint32_t least = guard_floor(peak, p.guard_bits);
+    const int64_t comp = J.s.c0 + blockIdx.y;
+    if (threadIdx.x < C)
+        J.peaks()[(comp * p.nblk + J.s.blk0 + blk) * strideE + J.s.a0 * p.NN + ch0 + ch] = peak;
+    // low: a bit per momentum, whether the value lies below least; of the few together
+    auto together = [&](uint32_t low) { return over_lanes(low, lw, [](uint32_t x, uint32_t y) { return x & y; }); };
     for (int it = threadIdx.x; it < nv * C; it += blockDim.x) {
-        const int ch = it & (C - 1), vv = it >> p.logC, e = e0 + vv;
-        if (ch0 + ch >= NC)
-            continue;
+        const int vv = it >> p.logC, e = e0 + vv;
         bool reached = false;
         for (int w = 0; w < p.Nw && !reached; ++w)
             reached = e - p.shift[w] >= 0 && e - p.shift[w] < p.NE;
+        uint32_t low = 0u, any = 0u;
         const double2 *y = lds + (size_t)ch * rowp + (vv % R1) * (R2 + 1) + vv / R1;
         T *o = dst + (int64_t)e * strideE + ch;
         k_transform<1>(Nkz, y, (size_t)C * rowp, twk, [&](int k, double2 s) {
-            bad |= !(finite(s.x) && finite(s.y));
+            low = low + low + (magnitude(s) < least ? 1u : 0u);
+            if ((k & 31) == 31)
+                any |= together(low);
             if (reached)
                 put(o + (int64_t)k * p.NE * strideE, ar * s.x - ai * s.y, ar * s.y + ai * s.x);
             else
                 put(o + (int64_t)k * p.NE * strideE, 0.0, 0.0);
         });
+        any |= together(low);
+        if (any && reached)
+            atomicOr(&J.suspect()[(comp * p.NA + J.s.a0 + (ch0 + ch) / p.NN) * p.NE + e], any);
     }
-    if (__any(bad) && (threadIdx.x & 63) == 0)
-        atomicOr(J.flag(), 1u);
 }
 
 // Calls f with the integral constants R1, R2 of the transform length L.
@@ -1302,7 +1381,10 @@ __global__ __launch_bounds__(kSB, 2) void k_spec_pi_matrix(const SpecOne arg)
 // Pi[q, w, a, b, i, j] = beta / (Nkz L) sum_kappa sum_eps P^_ij[kappa, eps]
 // exp(2 pi i (kappa q / Nkz + eps (s_w - smin) / L)), one workgroup per (a, b, i, j): the
 // eps sum per (kappa, w), split over 2^lg neighbouring lanes where there are few of them,
-// then the kappa sum per (q, w).  Also the neighbour-table check.
+// then the kappa sum per (q, w).  The guard (SpecGuard): the peak of an atom and neighbour is
+// the rms of the correlation over all its lags, those of no (q, w) among them, which is the
+// root of sum |P^|^2; outputs below it in this (i, j) are marked as suspect, and the direct
+// kernel looks at all nine.  Also the neighbour-table check.
 __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
 {
     extern __shared__ double2 lds[];
@@ -1324,9 +1406,49 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
     fill_twiddles(tw, L, 1, L);
     fill_twiddles(twk, Nkz, 1, Nkz);
     const double2 *src = J.Dh() + (((size_t)blockIdx.y * p.NA * p.NB + ab) * kNF + ij) * p.npt;
-    for (int i = tid; i < p.npt; i += kSB)
-        ph[i + i / L] = src[i];
-    __syncthreads();
+    double sum = 0.0;
+    for (int i = tid; i < p.npt; i += kSB) {
+        const double2 v = src[i];
+        ph[i + i / L] = v;
+        sum = fma(v.x, v.x, fma(v.y, v.y, sum));
+    }
+    __shared__ double s_sum[kSB / 64];
+    __shared__ uint32_t s_top;
+    auto total = [&](double x) {  // over the workgroup, in all threads
+        for (int m = 1; m < 64; m <<= 1)
+            x += __shfl_xor(x, m);
+        if ((tid & 63) == 0)
+            s_sum[tid >> 6] = x;
+        __syncthreads();
+        x = s_sum[0];
+        for (int i = 1; i < kSB / 64; ++i)
+            x += s_sum[i];
+        return x;
+    };
+    sum = total(sum);
+    uint32_t peak = magnitude(sqrt(sum));
+    if (!(sum > 0x1p-900 && sum < 0x1p900)) {  // squares out of range: of values near one
+        if (tid == 0)
+            s_top = 0u;
+        __syncthreads();
+        uint32_t top = 0u;
+        for (int i = tid; i < p.npt; i += kSB)
+            top = max(top, magnitude(ph[i + i / L]));
+        atomicMax(&s_top, top);
+        __syncthreads();
+        const int ex = (int)(s_top >> 20) - 1023;
+        sum = 0.0;
+        for (int i = tid; i < p.npt; i += kSB) {
+            const double vr = ldexp(ph[i + i / L].x, -ex), vi = ldexp(ph[i + i / L].y, -ex);
+            sum = fma(vr, vr, fma(vi, vi, sum));
+        }
+        peak = magnitude(ldexp(sqrt(total(sum)), ex));
+    }
+    const uint32_t least = guard_floor(peak, p.guard_bits);
+    const int64_t pair = (int64_t)(J.s.c0 + blockIdx.y) * p.NA * p.NB + ab;
+    if (tid == 0)
+        atomicMax(J.peaks() + pair, peak);
+    unsigned char *suspect = reinterpret_cast<unsigned char *>(J.suspect()) + pair * p.Nqz * Nw;
     int lg = 0;
     while (lg < 4 && (Nkz * Nw << (lg + 1)) <= kSB)
         ++lg;
@@ -1366,6 +1488,8 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
             j -= j >= Nkz ? Nkz : 0;
         }
         bad |= !(finite(xr) && finite(xi));
+        if (magnitude(make_double2(xr, xi)) < least)
+            suspect[i] = 1;
         Pi[(((size_t)q * Nw + w) * p.NA + a) * (p.NB + 1) * kNF + b * kNF + ij] =
             make_double2(br * xr - bi * xi, br * xi + bi * xr);
     }
@@ -1472,6 +1596,7 @@ hipError_t sigma_passes(SpecOne o, const SpectralGeom &g, hipStream_t s)
         o.t.G = G + (size_t)c * p.g_elems * sizeof(T);
         o.t.D = D + (size_t)c * p.d_elems * sizeof(T);
         o.t.Sigma = S + (size_t)c * p.g_elems * sizeof(T);
+        o.s.c0 = c;
         o.jobs = kDhat | (c == 0 ? kDht : 0);
         if (dhat_wgs(p) * nc > kTogether) {
             e = prepare_launch<T>(g.L, o, Shape{dim3((unsigned)prepare_wgs(p, o.jobs, 0), nc), kSB, plus}, s);
@@ -1491,7 +1616,7 @@ hipError_t sigma_passes(SpecOne o, const SpectralGeom &g, hipStream_t s)
                 e = sandwich_launch<1>(p.Norb, o, Shape{dim3((unsigned)sandwich_wgs(p, o.s.na, o.s.nb), nc), kSB,
                                                         g.sand_lds}, s);
                 if (e == hipSuccess)
-                    e = inverse_launch<T>(g.L, o, Shape{dim3((unsigned)fft_wgs(p, o.s.na, o.s.nb), nc),
+                    e = inverse_launch<T>(g.L, o, Shape{dim3((unsigned)(inverse_groups(p, o.s.na) * o.s.nb), nc),
                                                         (unsigned)g.fft_threads, g.fft_lds}, s);
             }
         }
@@ -1547,7 +1672,7 @@ hipError_t sigma_batch(SpecMany m, const SpecParams *hp, const SpectralGeom *con
     e = sandwich_launch<1>(hp[0].Norb, m, Shape{h.grid, kSB, sand}, s);
     if (e != hipSuccess)
         return e;
-    h.grid.x = lay_out(&m, [&](int i) { return fft_wgs(hp[i], hp[i].NA, hp[i].nblk); });
+    h.grid.x = lay_out(&m, [&](int i) { return inverse_groups(hp[i], hp[i].NA) * hp[i].nblk; });
     return launch(k_spec_inverse<T, 0, 0, SpecMany>, m, h, d1, s);
 }
 
@@ -1572,7 +1697,7 @@ hipError_t spectral_sigma_launch(const sse_desc &d, const SpectralGeom &g, const
     r.G = a.G;
     r.D = a.Dt;
     r.Sigma = a.Sigma;
-    return fp64_redo_launch(r, c64, d.dt_antiherm != 0, redo_lds, d.ncomp, (const uint32_t *)ws, status, host, s);
+    return fp64_redo_launch(r, c64, d.dt_antiherm != 0, redo_lds, d.ncomp, ws, status, host, s);
 }
 
 hipError_t spectral_batch_launch(int n, const sse_desc *const *d, const SpectralGeom *const *g,
@@ -1627,6 +1752,7 @@ hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g, const in
 {
     SpecOne o{};
     o.p = spectral_params(d, g, w_shift);
+    o.p.guard_bits = speck::kPiGuardBits;
     o.t = SpecPtrs{neigh, dH, nullptr, nullptr, nullptr, (char *)ws};
     o.status = status;
     o.jobs = kDht;
@@ -1639,6 +1765,7 @@ hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g, const in
     const double2 *Gc = (const double2 *)G;
     for (int c = 0; c < d.ncomp && e == hipSuccess; c += g.nc) {
         const unsigned nc = (unsigned)std::min(g.nc, d.ncomp - c);
+        o.s.c0 = c;
         o.t.G = Gc + (size_t)c * p.g_elems;
         o.t.D = Gc + (size_t)(1 - c) * p.g_elems;
         for (o.s.blk0 = 0; o.s.blk0 < g.nblk && e == hipSuccess; o.s.blk0 += g.nb) {
