@@ -463,8 +463,8 @@ __device__ __forceinline__ void place_tile(const_ptr<Fp64Params> pp, int j, int 
 }
 
 // The tiles of an instance, all components, that the spectral form leaves: every one if
-// the flag at the start of its workspace is raised (it met a value that is not finite),
-// else those with an output block below the guard.  The gridDim.x workgroups that call it
+// it met a value that is not finite (kFlagAll), else, if any are marked, those with an output
+// block below the guard.  The gridDim.x workgroups that call it
 // share them: workgroup x has tiles x', x' + gridDim.x, ..., where the x' of an XCD are
 // neighbours, as their G rows are.  It lists those to look at in LDS, some at a time (2^lg
 // lanes look at one tile's suspect words, as many as leave every lane a tile), and the loop
@@ -477,6 +477,8 @@ __device__ __forceinline__ void walk_tiles(const_ptr<Fp64Params> pp, const_ptr<T
                                            double2 *lds)
 {
     __shared__ int s_next, s_n, s_i, s_list[kBlock];
+    if (ro(reinterpret_cast<const uint32_t *>((const char *)first->aux))[0] == 0u)
+        return;
     if (threadIdx.x == 0)
         s_next = s_n = s_i = 0;
     for (;;) {
@@ -487,7 +489,7 @@ __device__ __forceinline__ void walk_tiles(const_ptr<Fp64Params> pp, const_ptr<T
         const_ptr<Fp64Params> p = pp + none;
         const_ptr<TensorPtrs> t = first + none;
         const char *ws = (const char *)t->aux;
-        const bool all = ro(reinterpret_cast<const uint32_t *>(ws))[0] != 0u;
+        const bool all = ro(reinterpret_cast<const uint32_t *>(ws))[0] & kFlagAll;
         const int x = (int)xcd_remap(blockIdx.x, gridDim.x);
         const int i = __builtin_amdgcn_readfirstlane(s_i);
         if (i == __builtin_amdgcn_readfirstlane(s_n)) {

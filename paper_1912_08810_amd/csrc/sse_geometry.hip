@@ -260,9 +260,7 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
     const size_t NN = (size_t)d.Norb * d.Norb, row = (size_t)g->npt * 16;
     const size_t gb = (size_t)d.NA * NN * row, db = (size_t)d.NA * d.NB * kNF * row;
     const size_t dht = up((size_t)d.NA * d.NB * kN3D * NN * 8);
-    const size_t peaks = (size_t)d.ncomp * d.NA * d.NB * 4;
-    g->off_suspect = speck::kAlign + peaks;
-    g->guard_bytes = up(peaks + (size_t)d.ncomp * d.NA * d.NB * d.Nqz * d.Nw);
+    g->guard_bytes = up((size_t)d.ncomp * d.NA * d.NB * kNF * 4);  // peaks
     const size_t fixed = g->guard_bytes + dht + 4 * speck::kAlign + kSlack;
     // the output pass has a workgroup per (atom, neighbour, i, j), and a launch fewer than 2^32 threads
     if ((int64_t)d.NA * d.NB * kNF * speck::kSandBlock > 0xffffffffLL)

@@ -26,6 +26,10 @@ __device__ __forceinline__ uint32_t scaled(uint32_t peak, double scale)
     return magnitude(__hiloint2double((int)peak, 0) * scale);
 }
 
+// The word at the start of a spectral instance's workspace: a value was not finite, the direct
+// kernel computes all; some outputs are marked as suspect.
+constexpr uint32_t kFlagAll = 1u, kFlagSuspect = 2u;
+
 // Momentum k's bit in an energy's suspect word; more momenta than bits share them all.
 __device__ __forceinline__ uint32_t suspect_bit(int k, int Nkz) { return Nkz > 32 ? ~0u : 1u << (Nkz - 1 - k); }
 

@@ -243,9 +243,8 @@ struct PiParams {
     int32_t ncomp;     // component c: X + c x_c, Y - c x_c, Pi + c pi_c
     int64_t x_c, pi_c;
     // not NULL: nothing is computed where *flag is zero but the workgroups' outputs below the
-    // guard (SpecGuard): peaks [ncomp][NA][NB], suspect [ncomp][NA][NB][Nqz][Nw]
+    // guard (SpecGuard): peaks [ncomp][NA][NB][9]
     const uint32_t *flag, *peaks;
-    const unsigned char *suspect;
     int32_t guard_bits;
     double guard_scale;
     const uint32_t *status;  // copied to *host at the end if host is not NULL (pinned memory)

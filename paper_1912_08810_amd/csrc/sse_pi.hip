@@ -189,21 +189,21 @@ __global__ __launch_bounds__(kBlock, 1) void k_pi_mfma(const PiParams p)
     const int b0 = bg * nbw;
     const int nbv = min(nbw, p.NB - b0);          // neighbours of this workgroup
     const int t0 = p.cb[chunk], t1 = p.cb[chunk + 1];
-    // behind the spectral form: only if that met a value that is not finite, or if an
-    // output block [3, 3] of this workgroup lies below the guard
+    // behind the spectral form: only if that met a value that is not finite, or if an output
+    // block [3, 3] of this workgroup lies below the guard
     if (p.flag && ro(p.flag)[0] == 0u) {
         const int64_t ab = ((int64_t)blockIdx.y * p.NA + a) * p.NB + b0;
         bool weak = false;
         for (int x = tid; x < nbv * (t1 - t0); x += kBlock) {
             const int b = x / (t1 - t0), w = p.tw[t0 + x - b * (t1 - t0)];
-            if (!p.suspect[((ab + b) * p.Nqz + q) * p.Nw + w])
-                continue;
             const double2 *P = p.Pi + blockIdx.y * p.pi_c +
                                ((((size_t)q * p.Nw + w) * p.NA + a) * (p.NB + 1) + b0 + b) * kNF;
-            uint32_t top = 0u;
-            for (int ij = 0; ij < kNF; ++ij)
+            uint32_t top = 0u, peak = 0u;
+            for (int ij = 0; ij < kNF; ++ij) {
                 top = max(top, magnitude(P[ij]));
-            weak |= top < guard_floor(scaled(p.peaks[ab + b], p.guard_scale), p.guard_bits);
+                peak = max(peak, p.peaks[(ab + b) * kNF + ij]);
+            }
+            weak |= top < guard_floor(scaled(peak, p.guard_scale), p.guard_bits);
         }
         if (!__syncthreads_or(weak))
             return;

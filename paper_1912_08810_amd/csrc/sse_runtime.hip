@@ -1119,7 +1119,6 @@ sse_status sse_pi_submit(sse_plan_t plan, const int32_t *neigh, const double *dH
         if (spectral) {
             pp.flag = (const uint32_t *)wsfree;
             pp.peaks = (const uint32_t *)(wsfree + speck::kAlign);
-            pp.suspect = (const unsigned char *)wsfree + I.pi_spec.off_suspect;
             pp.guard_bits = speck::kPiGuardBits;
             pp.guard_scale = guard_scale(d, I.pi_spec);
         }

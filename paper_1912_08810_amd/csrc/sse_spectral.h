@@ -53,7 +53,7 @@ constexpr int guard_bits(int prec, int Norb)
 {
     return prec != SSE_FP64 || Norb == 1 ? 20 : Norb == 2 ? 10 : Norb == 3 ? 8 : 6;
 }
-// Pi's blocks [3, 3], which are sums over all energies, below the rms of their correlation.
+// Pi's blocks [3, 3], below the rms of their correlation.
 constexpr int kPiGuardBits = 6;
 constexpr size_t matrix_bytes(int No, int P) { return (size_t)matrix_tiles(No) * 128 + (size_t)kNF * P * 16; }
 constexpr int matrix_neighbours(int No) { return (int)(kLdsTwo / matrix_bytes(No, 16)); }
@@ -99,8 +99,8 @@ struct SpecParams {
 
 // What one call works on: its tensors (of the pass's first component) and workspace.
 // Workspace: the non-finite flag, then
-//   peaks  [ncomp][nblk][NA NN] (Pi: [ncomp][NA][NB]), words
-//   suspect  [ncomp][NA][NE], words (Pi: [ncomp][NA][NB][Nqz][Nw], bytes)
+//   peaks  [ncomp][nblk][NA NN] (Pi: [ncomp][NA][NB][9]), words
+//   suspect  [ncomp][NA][NE], words (Sigma)
 //   dht  [NA][NB][3][n][n'] = dH[a, b, j][n'][n] (not written for the matrix form)
 //   Dh   [components][NA][NB][9][npt]
 //   Gh   [components][blocks][NA NN][npt]

@@ -484,6 +484,7 @@ __device__ __forceinline__ void inverse_job(const Job &J, double2 *lds, uint32_t
         J.peaks()[(comp * p.nblk + J.s.blk0 + blk) * strideE + J.s.a0 * p.NN + ch0 + ch] = peak;
     // low: a bit per momentum, whether the value lies below least; of the few together
     auto together = [&](uint32_t low) { return over_lanes(low, lw, [](uint32_t x, uint32_t y) { return x & y; }); };
+    bool marked = false;
     for (int it = threadIdx.x; it < nv * C; it += blockDim.x) {
         const int vv = it >> p.logC, e = e0 + vv;
         bool reached = false;
@@ -502,9 +503,12 @@ __device__ __forceinline__ void inverse_job(const Job &J, double2 *lds, uint32_t
                 put(o + (int64_t)k * p.NE * strideE, 0.0, 0.0);
         });
         any |= together(low);
+        marked |= any && reached;
         if (any && reached)
             atomicOr(&J.suspect()[(comp * p.NA + J.s.a0 + (ch0 + ch) / p.NN) * p.NE + e], any);
     }
+    if (__any(marked) && (threadIdx.x & 63) == 0)
+        atomicOr(J.flag(), kFlagSuspect);
 }
 
 // Calls f with the integral constants R1, R2 of the transform length L.
@@ -772,7 +776,7 @@ __global__ __launch_bounds__(kSB, W) void k_spec_sandwich(const A arg)
         }
     }
     if (__any(bad) && (threadIdx.x & 63) == 0)
-        atomicOr(J.flag(), 1u);
+        atomicOr(J.flag(), kFlagAll);
 }
 
 __device__ __forceinline__ double mfma(double a, double b, double c)
@@ -1018,7 +1022,7 @@ __global__ __launch_bounds__(kSB, No <= 8 ? 3 : 2) void k_spec_matrix(const A ar
         }
     }
     if (__any(bad) && (threadIdx.x & 63) == 0)
-        atomicOr(J.flag(), 1u);
+        atomicOr(J.flag(), kFlagAll);
 }
 
 // The phonon self-energy (Eqs. (4)-(5)): P_ij[q, w] = sum_k sum_e tr(dH_i^T X[k + q, e + s_w, a]
@@ -1383,8 +1387,8 @@ __global__ __launch_bounds__(kSB, 2) void k_spec_pi_matrix(const SpecOne arg)
 // eps sum per (kappa, w), split over 2^lg neighbouring lanes where there are few of them,
 // then the kappa sum per (q, w).  The guard (SpecGuard): the peak of an atom and neighbour is
 // the rms of the correlation over all its lags, those of no (q, w) among them, which is the
-// root of sum |P^|^2; outputs below it in this (i, j) are marked as suspect, and the direct
-// kernel looks at all nine.  Also the neighbour-table check.
+// root of sum |P^|^2; the direct kernel compares its outputs with that.  Also the
+// neighbour-table check.
 __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
 {
     extern __shared__ double2 lds[];
@@ -1414,41 +1418,20 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
     }
     __shared__ double s_sum[kSB / 64];
     __shared__ uint32_t s_top;
-    auto total = [&](double x) {  // over the workgroup, in all threads
+    auto spread = [&](double x) {
         for (int m = 1; m < 64; m <<= 1)
             x += __shfl_xor(x, m);
         if ((tid & 63) == 0)
             s_sum[tid >> 6] = x;
-        __syncthreads();
-        x = s_sum[0];
+    };
+    auto root = [&] {  // of the workgroup's sum, to 6 %: half the exponent
+        double x = s_sum[0];
         for (int i = 1; i < kSB / 64; ++i)
             x += s_sum[i];
-        return x;
+        return (magnitude(x) >> 1) + (1023u << 19);
     };
-    sum = total(sum);
-    uint32_t peak = magnitude(sqrt(sum));
-    if (!(sum > 0x1p-900 && sum < 0x1p900)) {  // squares out of range: of values near one
-        if (tid == 0)
-            s_top = 0u;
-        __syncthreads();
-        uint32_t top = 0u;
-        for (int i = tid; i < p.npt; i += kSB)
-            top = max(top, magnitude(ph[i + i / L]));
-        atomicMax(&s_top, top);
-        __syncthreads();
-        const int ex = (int)(s_top >> 20) - 1023;
-        sum = 0.0;
-        for (int i = tid; i < p.npt; i += kSB) {
-            const double vr = ldexp(ph[i + i / L].x, -ex), vi = ldexp(ph[i + i / L].y, -ex);
-            sum = fma(vr, vr, fma(vi, vi, sum));
-        }
-        peak = magnitude(ldexp(sqrt(total(sum)), ex));
-    }
-    const uint32_t least = guard_floor(peak, p.guard_bits);
-    const int64_t pair = (int64_t)(J.s.c0 + blockIdx.y) * p.NA * p.NB + ab;
-    if (tid == 0)
-        atomicMax(J.peaks() + pair, peak);
-    unsigned char *suspect = reinterpret_cast<unsigned char *>(J.suspect()) + pair * p.Nqz * Nw;
+    spread(sum);
+    __syncthreads();
     int lg = 0;
     while (lg < 4 && (Nkz * Nw << (lg + 1)) <= kSB)
         ++lg;
@@ -1473,6 +1456,29 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
             A[i] = make_double2(xr, xi);
     }
     __syncthreads();
+    uint32_t peak = root();
+    if (peak < (1023u - 450u) << 20 || peak > (1023u + 450u) << 20) {  // squares out of range: of values near one
+        if (tid == 0)
+            s_top = 0u;
+        __syncthreads();
+        uint32_t top = 0u;
+        for (int i = tid; i < p.npt; i += kSB)
+            top = max(top, magnitude(ph[i + i / L]));
+        atomicMax(&s_top, top);
+        __syncthreads();
+        top = s_top;
+        const int ex = (int)(top >> 20) - 1023;
+        sum = 0.0;
+        for (int i = tid; i < p.npt; i += kSB) {
+            const double vr = ldexp(ph[i + i / L].x, -ex), vi = ldexp(ph[i + i / L].y, -ex);
+            sum = fma(vr, vr, fma(vi, vi, sum));
+        }
+        spread(sum);
+        __syncthreads();
+        peak = top == 0u ? 0u : root() + (uint32_t)(ex << 20);
+    }
+    if (tid == 0)
+        J.peaks()[(int64_t)(J.s.c0 + blockIdx.y) * p.NA * p.NB * kNF + J.bid] = peak;
     double2 *Pi = (double2 *)J.t.Sigma + (size_t)blockIdx.y * p.Nqz * Nw * p.NA * (p.NB + 1) * kNF;
     const double sc = 1.0 / ((double)Nkz * L), br = p.alpha_re * sc, bi = p.alpha_im * sc;
     bool bad = false;
@@ -1488,13 +1494,11 @@ __global__ __launch_bounds__(kSB) void k_spec_pi_out(const SpecOne arg)
             j -= j >= Nkz ? Nkz : 0;
         }
         bad |= !(finite(xr) && finite(xi));
-        if (magnitude(make_double2(xr, xi)) < least)
-            suspect[i] = 1;
         Pi[(((size_t)q * Nw + w) * p.NA + a) * (p.NB + 1) * kNF + b * kNF + ij] =
             make_double2(br * xr - bi * xi, br * xi + bi * xr);
     }
     if (__any(bad) && (tid & 63) == 0)
-        atomicOr(J.flag(), 1u);
+        atomicOr(J.flag(), kFlagAll);
 }
 
 template <typename K>
@@ -1752,7 +1756,6 @@ hipError_t spectral_pi_launch(const sse_desc &d, const SpectralGeom &g, const in
 {
     SpecOne o{};
     o.p = spectral_params(d, g, w_shift);
-    o.p.guard_bits = speck::kPiGuardBits;
     o.t = SpecPtrs{neigh, dH, nullptr, nullptr, nullptr, (char *)ws};
     o.status = status;
     o.jobs = kDht;
