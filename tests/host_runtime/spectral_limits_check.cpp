@@ -1,5 +1,6 @@
 // Launch sizes of the spectral form where an instance has many atoms or neighbours and
-// little else: fewer than 2^32 threads in every launch.
+// little else: fewer than 2^32 threads in every launch; and the geometry that a device test
+// stands on.
 #include <algorithm>
 #include <cstdio>
 #include <vector>
@@ -47,6 +48,16 @@ int main()
             NEED(sandwich(g, 1) <= kMost);
             NEED(ab * 9 * speck::kSandBlock <= kMost);
         }
+    }
+    {
+        // the device test of a workspace of some atoms at a time has three passes, the last one ragged
+        sse_desc d{};
+        d.NA = 900; d.NB = 4; d.Norb = 16; d.N3D = 3; d.Nkz = d.Nqz = 9; d.NE = 140; d.Nw = 20; d.ncomp = 1;
+        std::vector<int32_t> s(d.Nw);
+        for (int w = 0; w < d.Nw; ++w)
+            s[w] = w + 1;
+        const SpectralGeom g = spectral_geometry(d, s.data());
+        NEED(g.on && !g.matrix && g.na == 425 && g.nb == 1);
     }
     printf("%d and %d problems in the spectral form, %d failures\n", on, pi, fails);
     if (!fails && on > 100 && pi > 100)
