@@ -91,6 +91,8 @@ KERNEL_SOURCES = ["paper_1912_08810_amd/csrc/sse_spectral.hip",
                   "paper_1912_08810_amd/csrc/sse_spectral.h",
                   "paper_1912_08810_amd/csrc/sse_geometry.hip",
                   "paper_1912_08810_amd/csrc/sse_dft.h",
+                  "paper_1912_08810_amd/csrc/sse_guard.h",
+                  "paper_1912_08810_amd/csrc/sse_fp64.hip",
                   "paper_1912_08810_amd/csrc/sse_internal.h",
                   "paper_1912_08810_amd/csrc/sse_copy.h",
                   "paper_1912_08810_amd/build.py"]

@@ -287,8 +287,8 @@ bool spectral_pi_layout(const sse_desc &d, size_t budget, SpectralGeom *g)
 // The cheapest transform length whose pass fits: points computed, weighted by what
 // the transforms lose.  Of the whole call at Nkz 7, Norb 10, NB 4, complex128, L 256 and
 // 288 against 160: one workgroup per CU (64-byte pieces, 115 kB of LDS) 4 % per point,
-// 32-byte pieces (two workgroups, 57 kB) 11 %.  Device scale: L 288 in 4 blocks 81.4 ms,
-// L 160 in 8 (a ninth more points) 85.0 ms.
+// 32-byte pieces (two workgroups, 57 kB) 11 %.  Device scale: L 288 in 4 blocks 73 ms,
+// L 160 in 8 (a ninth more points) 76 ms.
 template <typename Layout>
 SpectralGeom best_geometry(const sse_desc &d, const int32_t *w_shift, bool matrix, Layout layout)
 {

@@ -19,15 +19,16 @@
 //   k_spec_sandwich  G^, D^ -> S^ (for the Norb that speck::matrix_form names
 //                    k_spec_matrix, and k_spec_pi_matrix in place of k_spec_pi)
 //   k_spec_inverse   S^ -> Sigma, and the neighbour-table check
-//   k_sse_fp64_redo  the direct kernel, if the flag was raised
+//   k_sse_fp64_redo  the direct kernel: all of it, or what the guard has marked
 // Twiddle factors are computed by each workgroup into LDS, so that nothing has to run
 // before the first launch.
 // G^ and S^ are laid out [atom, orbital pair][kappa][eps], points fastest, so every
 // pass reads and writes whole runs of points.  Rounding is that of binary64
-// transforms: relative to the largest values of a block, as in any sum over them.
+// transforms: relative to the largest values of an energy block; outputs that lie far
+// below it are computed again by the direct kernel (SpecGuard).
 // Device scale (NA = 1024, NB = 4, Norb = 10, Nkz = Nqz = 7, NE = 1000, Nw = 30, both
-// components, complex128): 1609 ms per call in the direct kernel, 73 ms here, of
-// which the transforms (at the rate of a copy, 4.4 TB/s) 26 ms, the sandwich 48 ms.
+// components, complex128): 1609 ms per call in the direct kernel, 73 ms here: the sandwich
+// 47 ms, k_spec_prepare 14.4 (3.9 TB/s), k_spec_inverse 11.5 (4.5 TB/s).
 // Inputs that are not finite, or so large that a transform overflows, raise a flag;
 // the direct kernel then recomputes Sigma (its sums meet fewer elements).
 #include <hip/hip_runtime.h>
@@ -67,7 +68,7 @@ struct Job {
     const_ptr<SpecParams> p;
     SpecPtrs t;
     SpecPass s;
-    int64_t bid, nwg;
+    int64_t bid;
 
     __device__ __forceinline__ uint32_t *flag() const { return reinterpret_cast<uint32_t *>(t.ws); }
     __device__ __forceinline__ uint32_t *peaks() const { return reinterpret_cast<uint32_t *>(t.ws + speck::kAlign); }
@@ -79,7 +80,7 @@ struct Job {
 };
 __device__ __forceinline__ Job job(const SpecOne &o)
 {
-    return Job{ro(&o.p), o.t, o.s, blockIdx.x, gridDim.x};
+    return Job{ro(&o.p), o.t, o.s, blockIdx.x};
 }
 __device__ __forceinline__ Job job(const SpecMany &m)
 {
@@ -94,7 +95,7 @@ __device__ __forceinline__ Job job(const SpecMany &m)
     }
     lo = __builtin_amdgcn_readfirstlane(lo);
     const_ptr<SpecParams> p = ro(m.params) + lo;
-    return Job{p, m.t[lo], SpecPass{0, p->nblk, 0, p->NA, -p->smax, p->L, p->g_elems, p->off_g}, x - m.start[lo], m.start[lo + 1] - m.start[lo]};
+    return Job{p, m.t[lo], SpecPass{0, p->nblk, 0, p->NA, -p->smax, p->L, p->g_elems, p->off_g}, x - m.start[lo]};
 }
 
 // tw[j] = exp(-2 pi i j m / n) for j < count.
@@ -138,7 +139,9 @@ __host__ __device__ inline int64_t sandwich_wgs(const SpecParams &p, int na, int
 // false: none.  All XCDs work on one group of points at a time (its G^ rows stay in the
 // last-level cache), an XCD on neighbouring atoms.  With few atoms, whose eighths would
 // differ (12 atoms: two XCDs idle), they are dealt out one by one: a batch of 8 to 16
-// atoms each 372 -> 334 us, 97 atoms 737 -> 703 us.
+// atoms each 372 -> 334 us, 97 atoms 737 -> 703 us.  One by one and in eighths, us per
+// component (Norb 10, NB 4, NE 270, Nkz 3): 64 atoms 204 and 211, 128 387 and 382, 256 710
+// and 708, 512 1359 and 1352, 1024 2604 and 2575.
 __device__ __forceinline__ bool sandwich_place(int64_t bid, int na, int64_t groups, int *atom, int64_t *group)
 {
     if (na < kPlainAtoms) {
@@ -607,12 +610,13 @@ __device__ __forceinline__ void pin(double &x) { asm volatile("" : "+v"(x)); }
 // one is a wait for all).  The next neighbour's G^ is copied into LDS during the
 // second half, which does not read it.
 //
-// Bound: binary64 FMA issue, and the power it takes.  At device scale (Norb = 10) the
-// vector units are busy 72% of the cycles, 1560 of 1740 vector instructions per lane
-// and neighbour are FMAs, LDS is busy 38% of the cycles, and the clock sinks from 2.4
-// to 1.9 GHz: 3.6 ms per energy block of 160, 7.0 ms before the hand pipelining (FMA
-// issue at 2.4 GHz: 1.9 ms).  Leaving out the copies, the scalar loads or the LDS
-// reads shortens it by 8 to 14% each: none of them alone is what it waits for.
+// Bound: binary64 FMA issue, and the power it takes.  NA 256, NB 4, NE 270, Nkz 3, per
+// component: Norb 9 626 us, 16 2.51 ms.  The vector units are busy 75 and 70 % of the
+// cycles, 86 and 88 % of the vector instructions are FMAs (1440 per lane and neighbour at
+// Norb 9), and the clock sinks from 2.4 to 1.8 GHz (FMA issue at 2.4 GHz: 297 us and
+// 1.31 ms).  Before the hand pipelining it took twice as long; leaving out the copies, the
+// scalar loads or the LDS reads shortens it by 8 to 14 % each (both seen at Norb 10): none of
+// them alone is what it waits for.
 template <int No, int CB, int W, typename A>
 __global__ __launch_bounds__(kSB, W) void k_spec_sandwich(const A arg)
 {
@@ -1034,10 +1038,9 @@ __global__ __launch_bounds__(kSB, No <= 8 ? 3 : 2) void k_spec_matrix(const A ar
 // e0 + smin).  As in k_spec_sandwich a workgroup takes P points of one atom and a lane
 // one point and row m: W_j[m, :] comes from LDS, U_i[n, m] from the lane's column m of X^
 // with wave-uniform dH_i, and the sum over m goes through LDS once per neighbour.
-// The same pipelining, and the same bound.  NA = 128, NE = 500, otherwise as the device-
-// scale problem, both components: 204.6 ms per call in the direct kernel, 5.4 ms here, of
-// which this kernel 3.7 ms and the four transforms 1.7 ms (Norb 10, which has a matrix
-// form by now).
+// The same pipelining, and the same bound: NA 256, NB 4, NE 270, Nkz 3, Norb 9, both
+// components, 1.25 ms; vector units busy 74 % of the cycles, 85 % of their instructions
+// FMAs.
 template <int No, int CB, int W>
 __global__ __launch_bounds__(kSB, W) void k_spec_pi(const SpecOne arg)
 {
@@ -1550,11 +1553,12 @@ hipError_t inverse_launch(int L, const SpecOne &o, const Shape &h, hipStream_t s
     return e;
 }
 
-// Columns per block and waves per SIMD of the sandwich kernel's row form: half the
-// columns keep M, S^ and D^ of a lane within 168 registers up to 10 orbitals, so that
-// three waves share a SIMD.  At Norb 10 (device scale) 3.6 ms per energy block against
-// 4.2 with all ten columns at two waves; at Norb 12 1.01 ms per call at two waves, 1.07
-// at three.
+// Columns per block and waves per SIMD of the row form: half the columns keep M, S^ and D^
+// of a lane within 168 registers up to 10 orbitals, so that three waves share a SIMD; above,
+// two waves' 256 registers hold them.  NA 256, NB 4, NE 270, Nkz 3, us per component: Norb 6
+// 214 (all columns at two waves 222), 9 626 (677), 13 1766 (three waves 3104), 16 2511
+// (14545: registers spill); Pi, both components, Norb 9 1252 (1771), 13 3460 (6542).  At
+// Norb 5 two waves are as fast as three (148 and 147).
 constexpr int col_block(int No) { return No <= 5 ? No : (No + 1) / 2; }
 constexpr int waves(int No) { return No <= 10 ? 3 : 2; }
 
